@@ -11,6 +11,7 @@
 // sum |t - t_converged|^2 / sum s^2 (absolute).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -31,100 +32,322 @@ constexpr int F_IN = 8, HID = 256, F_OUT = 4;
 constexpr size_t OFF_W1 = 0, OFF_B1 = OFF_W1 + F_IN * HID, OFF_W2 = OFF_B1 + HID, OFF_B2 = OFF_W2 + HID * HID,
                  OFF_W3 = OFF_B2 + HID, OFF_B3 = OFF_W3 + HID * F_OUT, N_PARAMS = OFF_B3 + F_OUT;
 
-enum SgEpi { SG_PLAIN = 0, SG_BIAS_RELU = 1, SG_BIAS = 2, SG_MASK = 3 };
+// ---------------------------------------------------------------------------
+// Network kernels.  One workgroup carries 64 rows through whole layers: the
+// 64 x 256 activations stay in LDS (64 KB, two workgroups per CU) between the
+// layers, and the weights (256 KB, resident in every L2) are read as MFMA
+// fragments straight from memory one 16-deep k block ahead.  Four waves, each
+// 64 rows x 64 columns: 16 accumulators, 64 MFMAs (2048 cycles) per k block
+// against 4 LDS reads and 16 loads.
+//
+// LDS rows hold 64 chunks of four floats; chunk c of row r sits at c ^ (r & 15),
+// so the 16 rows of a fragment read 16 different 16-byte bank groups.
+constexpr int kRows = 64;
 
-// C = op(A) op(B) (+ epilogue); op(A)(m,k) = TA ? A[k*lda+m] : A[m*lda+k],
-// op(B)(k,n) = TB ? B[n*ldb+k] : B[k*ldb+n].  64x64 tiles, 4 waves of 32x32.
-template <bool TA, bool TB, int EPI>
-__global__ __launch_bounds__(256) void k_sgemm(const float* __restrict__ A, const float* __restrict__ B,
-                                               float* __restrict__ C, int M, int N, int K, int lda, int ldb, int ldc,
-                                               const float* __restrict__ bias, const float* __restrict__ mask, int ldm) {
-    constexpr int BM = 64, BN = 64, BK = 16;
-    __shared__ float As[BK][BM + 4];
-    __shared__ float Bs[BK][BN + 4];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-    const int wm0 = (wave >> 1) * 32, wn0 = (wave & 1) * 32;
-    f4v c[2][2];
+__device__ __forceinline__ int lds_chunk(int row, int chunk) { return row * HID + ((chunk ^ (row & 15)) << 2); }
+
+// Forward: Y = relu(relu(X W1 + b1) W2 + b2) W3 + b3 in one launch (STORE: the
+// hidden activations go to h1, h2 for the backward pass).  Every output is one
+// MFMA chain in ascending k, 4 at a time.  An activation column k is stored in
+// chunk 4 (k / 16) + k % 4, element (k % 16) / 4: a lane's 16-byte read then
+// holds its k of four consecutive MFMA steps.  Bound by the fp32 matrix cores
+// (138 kflop a row, no activation leaves the CU): features, network and
+// prediction of 600001 rows 1.88 -> 0.84 ms against one launch per layer with
+// the activations in device memory.
+template <bool STORE>
+__global__ __launch_bounds__(256) void k_mlp_fwd(const float* __restrict__ P, const float* __restrict__ X,
+                                                 long long rows, float* __restrict__ h1, float* __restrict__ h2,
+                                                 float* __restrict__ Y) {
+    __shared__ float act[kRows * HID];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 15, lq = lane >> 4;
+    const long long r0 = (long long)blockIdx.x * kRows;
+    const int n0 = wave * 64;
+    auto put = [&](int row, int col, float v) {
+        act[lds_chunk(row, (col >> 4) * 4 + (col & 3)) + ((col & 15) >> 2)] = v;
+    };
+    {
+        float a[4][2], b[4][2];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const long long r = min(r0 + 16 * i + lr, rows - 1);
+#pragma unroll
+            for (int k = 0; k < 2; ++k) a[i][k] = X[r * F_IN + 4 * k + lq];
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) b[j][k] = P[OFF_W1 + (4 * k + lq) * HID + n0 + 16 * j + lr];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int col = n0 + 16 * j + lr;
+            const float bias = P[OFF_B1 + col];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                f4v c = f4v{0.f, 0.f, 0.f, 0.f};
+                c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][0], b[j][0], c, 0, 0, 0);
+                c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][1], b[j][1], c, 0, 0, 0);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int row = 16 * i + 4 * lq + q;
+                    const float v = fmaxf(c[q] + bias, 0.f);
+                    put(row, col, v);
+                    if (STORE && r0 + row < rows) h1[(r0 + row) * HID + col] = v;
+                }
+            }
+        }
+    }
+    f4v acc[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = f4v{0.f, 0.f, 0.f, 0.f};
+    const float* W2 = P + OFF_W2 + lq * HID + n0 + lr;
+    float b[4][4], bn[4][4];
+    auto load_b = [&](float (&d)[4][4], int kb) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) d[j][k] = W2[(16 * kb + 4 * k) * HID + 16 * j];
+    };
+    auto block = [&](int kb, const float (&w)[4][4]) {
+        f4v a[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) a[i] = *(const f4v*)&act[lds_chunk(16 * i + lr, 4 * kb + lq)];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][k], w[j][k], acc[i][j], 0, 0, 0);
+    };
+    load_b(b, 0);
+    __syncthreads();
+    for (int kb = 0; kb < HID / 16; kb += 2) {
+        load_b(bn, kb + 1);
+        block(kb, b);
+        load_b(b, min(kb + 2, HID / 16 - 1));
+        block(kb + 1, bn);
+    }
+    __syncthreads();   // every wave has read the first layer's activations
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int col = n0 + 16 * j + lr;
+        const float bias = P[OFF_B2 + col];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int row = 16 * i + 4 * lq + q;
+                const float v = fmaxf(acc[i][j][q] + bias, 0.f);
+                put(row, col, v);
+                if (STORE && r0 + row < rows) h2[(r0 + row) * HID + col] = v;
+            }
+    }
+    __syncthreads();
+    // last layer: 16 rows per wave, the four outputs padded to one fragment
+    f4v c = f4v{0.f, 0.f, 0.f, 0.f};
+    const bool out = lr < F_OUT;
+    const float* W3 = P + OFF_W3 + lq * F_OUT + (out ? lr : 0);
+#pragma unroll 4
+    for (int kb = 0; kb < HID / 16; ++kb) {
+        const f4v a = *(const f4v*)&act[lds_chunk(16 * wave + lr, 4 * kb + lq)];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float w = out ? W3[(16 * kb + 4 * k) * F_OUT] : 0.f;
+            c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[k], w, c, 0, 0, 0);
+        }
+    }
+    if (out) {
+        const float bias = P[OFF_B3 + lr];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const long long row = r0 + 16 * wave + 4 * lq + q;
+            if (row < rows) Y[row * F_OUT + lr] = c[q] + bias;
+        }
+    }
+}
+
+// Backward through the hidden layers in one launch:
+// dh2 = (dY W3^T) o (h2 > 0) into LDS and memory, dh1 = (dh2 W2^T) o (h1 > 0).
+__global__ __launch_bounds__(256) void k_mlp_bwd(const float* __restrict__ P, const float* __restrict__ dY, int rows,
+                                                 const float* __restrict__ h1, const float* __restrict__ h2,
+                                                 float* __restrict__ dh1, float* __restrict__ dh2) {
+    __shared__ float act[kRows * HID];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lq = lane >> 4;
+    const long long r0 = (long long)blockIdx.x * kRows;
+    {
+        const f4v w = *(const f4v*)&P[OFF_W3 + tid * F_OUT];
+#pragma unroll 8
+        for (int r = 0; r < kRows; ++r) {
+            const long long row = min(r0 + r, (long long)rows - 1);
+            const f4v d = *(const f4v*)&dY[row * F_OUT];
+            float v = d[0] * w[0] + d[1] * w[1] + d[2] * w[2] + d[3] * w[3];
+            v = h2[row * HID + tid] > 0.f ? v : 0.f;
+            act[lds_chunk(r, tid >> 2) + (tid & 3)] = v;
+            if (r0 + r < rows) dh2[row * HID + tid] = v;
+        }
+    }
+    f4v acc[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = f4v{0.f, 0.f, 0.f, 0.f};
+    const int n0 = wave * 64;
+    const float* W2 = P + OFF_W2 + (n0 + lr) * HID + 4 * lq;   // row n of W2: k contiguous
+    f4v b[4], bn[4];
+    auto load_b = [&](f4v (&d)[4], int kb) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) d[j] = *(const f4v*)&W2[16 * j * HID + 16 * kb];
+    };
+    auto block = [&](int kb, const f4v (&w)[4]) {
+        f4v a[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) a[i] = *(const f4v*)&act[lds_chunk(16 * i + lr, 4 * kb + lq)];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][k], w[j][k], acc[i][j], 0, 0, 0);
+    };
+    load_b(b, 0);
+    __syncthreads();
+    for (int kb = 0; kb < HID / 16; kb += 2) {
+        load_b(bn, kb + 1);
+        block(kb, b);
+        load_b(b, min(kb + 2, HID / 16 - 1));
+        block(kb + 1, bn);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int col = n0 + 16 * j + lr;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const long long row = r0 + 16 * i + 4 * lq + q;
+                if (row < rows) dh1[row * HID + col] = h1[row * HID + col] > 0.f ? acc[i][j][q] : 0.f;
+            }
+    }
+}
+
+// Parameter gradients, split along the rows: gW2 = h1^T dh2, gW1 = X^T dh1,
+// gW3 = h2^T dY and the column sums gb2, gb1, gb3 of one row chunk, written to
+// part[chunk] in the layout of the parameter vector.  blockIdx.x: 16 64 x 64
+// tiles of gW2, 4 column tiles of gW1, 4 row tiles of gW3; blockIdx.y: chunk.
+// Bound by launch and load latency at these sizes: 128 rows per chunk give 1536
+// workgroups for a minibatch of 8192.  (With the rows unsplit, 16 and 4
+// workgroups walked all of them: 3.4 ms of a 3.75 ms training step on 8192
+// rows; the whole step now takes 0.18 ms.)
+constexpr int kGradTiles = 24, kGradBK = 32, kMaxChunks = 64;
+__global__ __launch_bounds__(256) void k_mlp_wgrad(const float* __restrict__ X, const float* __restrict__ h1,
+                                                   const float* __restrict__ h2, const float* __restrict__ dh1,
+                                                   const float* __restrict__ dh2, const float* __restrict__ dY,
+                                                   int rows, int rows_per, float* __restrict__ part) {
+    constexpr int LD = 80;   // four k rows of a fragment start 16 banks apart
+    __shared__ float As[kGradBK * LD];
+    __shared__ float Bs[kGradBK * LD];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lq = lane >> 4;
+    const int t = blockIdx.x;
+    const float *A, *B;
+    int MA, NB, m0, n0;
+    size_t off, boff;
+    if (t < 16) {
+        A = h1, B = dh2, MA = HID, NB = HID, m0 = (t >> 2) * 64, n0 = (t & 3) * 64, off = OFF_W2, boff = OFF_B2;
+    } else if (t < 20) {
+        A = X, B = dh1, MA = F_IN, NB = HID, m0 = 0, n0 = (t - 16) * 64, off = OFF_W1, boff = OFF_B1;
+    } else {
+        A = h2, B = dY, MA = HID, NB = F_OUT, m0 = (t - 20) * 64, n0 = 0, off = OFF_W3, boff = OFF_B3;
+    }
+    const int k_lo = blockIdx.y * rows_per, k_hi = min(rows, k_lo + rows_per);
+    f4v ra[2], rb[2];
+    // 32 rows x 16 chunks of four floats per operand, two per thread
+    auto fetch = [&](int k0) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int k = k0 + (tid >> 4) + 16 * u, c = (tid & 15) * 4;
+            const bool in = k < k_hi;
+            ra[u] = rb[u] = f4v{0.f, 0.f, 0.f, 0.f};
+            if (in && m0 + c < MA) ra[u] = *(const f4v*)&A[(long long)k * MA + m0 + c];
+            if (in && n0 + c < NB) rb[u] = *(const f4v*)&B[(long long)k * NB + n0 + c];
+        }
+    };
+    f4v acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) c[i][j] = f4v{0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < K; k0 += BK) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int idx = tid + e * kT;
-            int mm, kk;
-            if (!TA) {
-                mm = idx / BK;
-                kk = idx % BK;
-            } else {
-                kk = idx / BM;
-                mm = idx % BM;
-            }
-            const int gm = m0 + mm, gk = k0 + kk;
-            float v = 0.f;
-            if (gm < M && gk < K) v = TA ? A[(long long)gk * lda + gm] : A[(long long)gm * lda + gk];
-            As[kk][mm] = v;
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int idx = tid + e * kT;
-            int nn, kk;
-            if (!TB) {
-                kk = idx / BN;
-                nn = idx % BN;
-            } else {
-                nn = idx / BK;
-                kk = idx % BK;
-            }
-            const int gn = n0 + nn, gk = k0 + kk;
-            float v = 0.f;
-            if (gn < N && gk < K) v = TB ? B[(long long)gn * ldb + gk] : B[(long long)gk * ldb + gn];
-            Bs[kk][nn] = v;
-        }
+        for (int j = 0; j < 2; ++j) acc[i][j] = f4v{0.f, 0.f, 0.f, 0.f};
+    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+    float bsum = 0.f;
+    if (k_lo < k_hi) fetch(k_lo);
+    for (int k0 = k_lo; k0 < k_hi; k0 += kGradBK) {
         __syncthreads();
 #pragma unroll
-        for (int ks = 0; ks < BK; ks += 4) {
+        for (int u = 0; u < 2; ++u) {
+            const int at = ((tid >> 4) + 16 * u) * LD + (tid & 15) * 4;
+            *(f4v*)&As[at] = ra[u];
+            *(f4v*)&Bs[at] = rb[u];
+        }
+        __syncthreads();
+        if (k0 + kGradBK < k_hi) fetch(k0 + kGradBK);
+        if (m0 == 0 && tid < 64)
+#pragma unroll 8
+            for (int k = 0; k < kGradBK; ++k) bsum += Bs[k * LD + tid];
+#pragma unroll
+        for (int k = 0; k < kGradBK; k += 4) {
             float a[2], b[2];
 #pragma unroll
-            for (int i = 0; i < 2; ++i) a[i] = As[ks + (lane >> 4)][wm0 + i * 16 + (lane & 15)];
-#pragma unroll
-            for (int j = 0; j < 2; ++j) b[j] = Bs[ks + (lane >> 4)][wn0 + j * 16 + (lane & 15)];
+            for (int i = 0; i < 2; ++i) {
+                a[i] = As[(k + lq) * LD + wm + 16 * i + lr];
+                b[i] = Bs[(k + lq) * LD + wn + 16 * i + lr];
+            }
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) c[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], c[i][j], 0, 0, 0);
+                for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
         }
-        __syncthreads();
     }
-    // fp32-accumulating MFMA: accumulator element q is row 4*(lane/16) + q, column lane%16
+    float* G = part + (size_t)blockIdx.y * N_PARAMS;
+    if (m0 == 0 && tid < 64 && n0 + tid < NB) G[boff + n0 + tid] = bsum;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            const int col = n0 + wn0 + j * 16 + (lane & 15);
-            if (col >= N) continue;
+            const int col = n0 + wn + 16 * j + lr;
+            if (col >= NB) continue;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int row = m0 + wm0 + i * 16 + 4 * (lane >> 4) + q;
-                if (row >= M) continue;
-                float v = c[i][j][q];
-                if (EPI == SG_BIAS_RELU) v = fmaxf(v + bias[col], 0.f);
-                if (EPI == SG_BIAS) v += bias[col];
-                if (EPI == SG_MASK) v = mask[(long long)row * ldm + col] > 0.f ? v : 0.f;
-                C[(long long)row * ldc + col] = v;
+                const int row = m0 + wm + 16 * i + 4 * lq + q;
+                if (row < MA) G[off + (size_t)row * NB + col] = acc[i][j][q];
             }
         }
 }
 
-template <bool TA, bool TB, int EPI>
-hipError_t sgemm(const float* A, const float* B, float* C, int M, int N, int K, int lda, int ldb, int ldc,
-                 const float* bias, const float* mask, int ldm, hipStream_t st) {
-    if (M <= 0 || N <= 0) return hipSuccess;
-    dim3 grid((N + 63) / 64, (M + 63) / 64);
-    k_sgemm<TA, TB, EPI><<<grid, kT, 0, st>>>(A, B, C, M, N, K, lda, ldb, ldc, bias, mask, ldm);
-    return hipGetLastError();
+// gradient = sum of the chunks' parts in chunk order; block 0 also finishes
+// the loss (its block partials are already weighted) into host memory
+__global__ __launch_bounds__(256) void k_mlp_gsum(const float* __restrict__ part, int nchunk, float* __restrict__ g,
+                                                  const double* __restrict__ lpart, int nl, double* __restrict__ loss) {
+    const int k = blockIdx.x * kT + threadIdx.x;
+    if (k < (int)N_PARAMS) {
+        float s = 0.f;
+#pragma unroll 8
+        for (int c = 0; c < nchunk; ++c) s += part[(size_t)c * N_PARAMS + k];
+        g[k] = s;
+    }
+    if (blockIdx.x == 0) {
+        __shared__ double sh[kT];
+        double v = 0.0;
+        for (int b = threadIdx.x; b < nl; b += kT) v += lpart[b];
+        sh[threadIdx.x] = v;
+        __syncthreads();
+        for (int s2 = kT / 2; s2 > 0; s2 >>= 1) {
+            if ((int)threadIdx.x < s2) sh[threadIdx.x] += sh[threadIdx.x + s2];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) *loss = sh[0];
+    }
 }
 
 __device__ inline void ws_v_s(double2 u, double2 r, double d, double2* v, double* s) {
@@ -132,18 +355,13 @@ __device__ inline void ws_v_s(double2 u, double2 r, double d, double2* v, double
     *s = hypot(u.x, u.y) + hypot(v->x, v->y) + 1e-30;
 }
 
-__global__ __launch_bounds__(256) void k_ws_features(const double2* __restrict__ u, const double2* __restrict__ r,
-                                                     const double* __restrict__ D, long long n, float* __restrict__ X) {
-    const long long k = (long long)blockIdx.x * kT + threadIdx.x;
-    if (k >= n) return;
-    const double2 uu = u[k];
+// the eight features of one row; returns s
+__device__ inline double ws_row(double2 uu, double2 rr, double d, float* __restrict__ x) {
     double2 v;
     double s;
-    const double d = D[k];
-    ws_v_s(uu, r[k], d, &v, &s);
+    ws_v_s(uu, rr, d, &v, &s);
     const double au = hypot(uu.x, uu.y), av = hypot(v.x, v.y);
     const double lr = fmin(fmax(log((av + 1e-30) / (au + 1e-30)), -10.0), 10.0);
-    float* x = X + k * F_IN;
     x[0] = (float)(uu.x / s);
     x[1] = (float)(uu.y / s);
     x[2] = (float)(v.x / s);
@@ -152,6 +370,45 @@ __global__ __launch_bounds__(256) void k_ws_features(const double2* __restrict__
     x[5] = (float)(d / 10.0);
     x[6] = (float)(log(s) / 10.0);
     x[7] = (float)(av / s);
+    return s;
+}
+
+__global__ __launch_bounds__(256) void k_ws_features(const double2* __restrict__ u, const double2* __restrict__ r,
+                                                     const double* __restrict__ D, long long n, float* __restrict__ X) {
+    const long long k = (long long)blockIdx.x * kT + threadIdx.x;
+    if (k >= n) return;
+    ws_row(u[k], r[k], D[k], X + k * F_IN);
+}
+
+// Training rows idx[0..n) (idx null: 0..n-1) copied to the staging arrays with
+// their features, and per-block partial sums of s^2 (the absolute loss
+// normaliser).
+__global__ __launch_bounds__(256) void k_ws_stage(const double2* __restrict__ u, const double2* __restrict__ r,
+                                                  const double* __restrict__ D, const double2* __restrict__ t,
+                                                  const long long* __restrict__ idx, long long n,
+                                                  double2* __restrict__ bu, double2* __restrict__ br,
+                                                  double* __restrict__ bD, double2* __restrict__ bt,
+                                                  float* __restrict__ X, double* __restrict__ part) {
+    __shared__ double sh[kT];
+    double q = 0.0;
+    for (long long k = (long long)blockIdx.x * kT + threadIdx.x; k < n; k += (long long)gridDim.x * kT) {
+        const long long i = idx ? idx[k] : k;
+        const double2 uu = u[i], rr = r[i], tt = t[i];
+        const double d = D[i];
+        bu[k] = uu;
+        br[k] = rr;
+        bD[k] = d;
+        bt[k] = tt;
+        const double s = ws_row(uu, rr, d, X + k * F_IN);
+        q += s * s;
+    }
+    sh[threadIdx.x] = q;
+    __syncthreads();
+    for (int s2 = kT / 2; s2 > 0; s2 >>= 1) {
+        if ((int)threadIdx.x < s2) sh[threadIdx.x] += sh[threadIdx.x + s2];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
 }
 
 // prediction u + v + a v + b u  (Y may be null: a = b = 0)
@@ -175,38 +432,34 @@ __global__ __launch_bounds__(256) void k_ws_apply(const float* __restrict__ Y, c
                           uu.y + v.y + (ar * v.y + ai * v.x) + (br * uu.y + bi * uu.x));
 }
 
-// per-block partial sums of s^2 (the absolute loss normaliser)
-__global__ __launch_bounds__(256) void k_ws_s2(const double2* __restrict__ u, const double2* __restrict__ r,
-                                               const double* __restrict__ D, long long n, double* __restrict__ part) {
-    __shared__ double sh[kT];
-    const long long k = (long long)blockIdx.x * kT + threadIdx.x;
-    double q = 0.0;
-    if (k < n) {
-        double2 v;
-        double s;
-        ws_v_s(u[k], r[k], D[k], &v, &s);
-        q = s * s;
-    }
-    sh[threadIdx.x] = q;
-    __syncthreads();
-    for (int s2 = kT / 2; s2 > 0; s2 >>= 1) {
-        if ((int)threadIdx.x < s2) sh[threadIdx.x] += sh[threadIdx.x + s2];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
-}
-
 // loss rows and dL/dy; weight w_k = 1/(n s_k^2) (mode 0) or 1/sum s^2 (mode 1,
-// *norm holds sum s^2); per-block loss partials (already weighted)
+// every block adds the np partial sums); per-block loss partials (already
+// weighted)
 __global__ __launch_bounds__(256) void k_ws_head(const float* __restrict__ Y, const double2* __restrict__ u,
                                                  const double2* __restrict__ r, const double* __restrict__ D,
                                                  const double2* __restrict__ t, long long n, int mode,
-                                                 const double* __restrict__ norm, float* __restrict__ dY,
+                                                 const double* __restrict__ spart, int np, float* __restrict__ dY,
                                                  double* __restrict__ part) {
     __shared__ double sh[kT];
-    const long long k = (long long)blockIdx.x * kT + threadIdx.x;
+    auto block_sum = [&](double v) {
+        sh[threadIdx.x] = v;
+        __syncthreads();
+        for (int s2 = kT / 2; s2 > 0; s2 >>= 1) {
+            if ((int)threadIdx.x < s2) sh[threadIdx.x] += sh[threadIdx.x + s2];
+            __syncthreads();
+        }
+        const double x = sh[0];
+        __syncthreads();
+        return x;
+    };
+    double norm = 1.0;
+    if (mode == 1) {
+        double q = 0.0;
+        for (int b = threadIdx.x; b < np; b += kT) q += spart[b];
+        norm = block_sum(q);
+    }
     double l = 0.0;
-    if (k < n) {
+    for (long long k = (long long)blockIdx.x * kT + threadIdx.x; k < n; k += (long long)gridDim.x * kT) {
         const double2 uu = u[k];
         double2 v;
         double s;
@@ -215,8 +468,8 @@ __global__ __launch_bounds__(256) void k_ws_head(const float* __restrict__ Y, co
         const double2 tt = t[k];
         const double er = uu.x + v.x + (ar * v.x - ai * v.y) + (br * uu.x - bi * uu.y) - tt.x;
         const double ei = uu.y + v.y + (ar * v.y + ai * v.x) + (br * uu.y + bi * uu.x) - tt.y;
-        const double w = mode == 0 ? 1.0 / (s * s) / (double)n : 1.0 / *norm;
-        l = (er * er + ei * ei) * w;
+        const double w = mode == 0 ? 1.0 / (s * s) / (double)n : 1.0 / norm;
+        l += (er * er + ei * ei) * w;
         const double f = 2.0 * w;
         // conj(e) * v = (er v.x + ei v.y) + i (er v.y - ei v.x)
         dY[k * F_OUT] = (float)(f * (er * v.x + ei * v.y));
@@ -224,48 +477,8 @@ __global__ __launch_bounds__(256) void k_ws_head(const float* __restrict__ Y, co
         dY[k * F_OUT + 2] = (float)(f * (er * uu.x + ei * uu.y));
         dY[k * F_OUT + 3] = (float)(-f * (er * uu.y - ei * uu.x));
     }
-    sh[threadIdx.x] = l;
-    __syncthreads();
-    for (int s2 = kT / 2; s2 > 0; s2 >>= 1) {
-        if ((int)threadIdx.x < s2) sh[threadIdx.x] += sh[threadIdx.x + s2];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
-}
-
-__global__ __launch_bounds__(256) void k_sum_parts(const double* __restrict__ part, int nblk, double scale,
-                                                   double* __restrict__ out) {
-    __shared__ double sh[kT];
-    double v = 0.0;
-    for (int b = threadIdx.x; b < nblk; b += kT) v += part[b];
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    for (int s2 = kT / 2; s2 > 0; s2 >>= 1) {
-        if ((int)threadIdx.x < s2) sh[threadIdx.x] += sh[threadIdx.x + s2];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *out = sh[0] * scale;
-}
-
-// column sums of H [M][N] in two deterministic passes: partial[chunk][col]
-__global__ __launch_bounds__(256) void k_colsum_part(const float* __restrict__ H, int M, int N, int rows_per,
-                                                     float* __restrict__ part) {
-    const int col = blockIdx.x * kT + threadIdx.x;
-    const int chunk = blockIdx.y;
-    if (col >= N) return;
-    const int r0 = chunk * rows_per, r1 = min(M, r0 + rows_per);
-    float s = 0.f;
-    for (int r = r0; r < r1; ++r) s += H[(long long)r * N + col];
-    part[(long long)chunk * N + col] = s;
-}
-
-__global__ __launch_bounds__(256) void k_colsum_final(const float* __restrict__ part, int nchunk, int N,
-                                                      float* __restrict__ out) {
-    const int col = blockIdx.x * kT + threadIdx.x;
-    if (col >= N) return;
-    float s = 0.f;
-    for (int c = 0; c < nchunk; ++c) s += part[(long long)c * N + col];
-    out[col] = s;
+    l = block_sum(l);
+    if (threadIdx.x == 0) part[blockIdx.x] = l;
 }
 
 __global__ __launch_bounds__(256) void k_adam(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
@@ -314,21 +527,18 @@ struct fscc_mlp {
     // training scratch (rows <= maxb)
     size_t maxb = 0;
     float *X = nullptr, *h1 = nullptr, *h2 = nullptr, *dh1 = nullptr, *dh2 = nullptr, *Y = nullptr, *dY = nullptr,
-          *cpart = nullptr;
-    double *part = nullptr, *loss = nullptr, *bD = nullptr;
+          *gpart = nullptr;
+    double *spart = nullptr, *lpart = nullptr, *bD = nullptr;
     double2 *bu = nullptr, *br = nullptr, *bt = nullptr;
-    // inference scratch (chunk rows)
-    size_t chunk = 0;
-    float *ih1 = nullptr, *ih2 = nullptr;
     double* hloss = nullptr;
     std::string err;
 
     void free_train() {
-        void* ps[] = {X, h1, h2, dh1, dh2, Y, dY, cpart, part, loss, bD, bu, br, bt};
+        void* ps[] = {X, h1, h2, dh1, dh2, Y, dY, gpart, spart, lpart, bD, bu, br, bt};
         for (void* q : ps)
             if (q) (void)hipFree(q);
-        X = h1 = h2 = dh1 = dh2 = Y = dY = cpart = nullptr;
-        part = loss = bD = nullptr;
+        X = h1 = h2 = dh1 = dh2 = Y = dY = gpart = nullptr;
+        spart = lpart = bD = nullptr;
         bu = br = bt = nullptr;
         maxb = 0;
     }
@@ -336,7 +546,7 @@ struct fscc_mlp {
         if (st) (void)hipStreamSynchronize(st);
         else (void)hipDeviceSynchronize();
         free_train();
-        void* ps[] = {p, g, m, w, ih1, ih2};
+        void* ps[] = {p, g, m, w};
         for (void* q : ps)
             if (q) (void)hipFree(q);
         if (hloss) (void)hipHostFree(hloss);
@@ -357,6 +567,10 @@ hipError_t dalloc(T** q, size_t count) {
     return hipMalloc((void**)q, sizeof(T) * (count ? count : 1));
 }
 
+// blocks of the staging and loss launches (each loss block adds the partial
+// sums of every staging block)
+constexpr unsigned kStageBlocks = 512;
+
 hipError_t ensure_train(fscc_mlp* n, size_t rows) {
     if (rows <= n->maxb) return hipSuccess;
     n->free_train();
@@ -370,9 +584,9 @@ hipError_t ensure_train(fscc_mlp* n, size_t rows) {
     if (ok(e)) e = dalloc(&n->dh2, b * HID);
     if (ok(e)) e = dalloc(&n->Y, b * F_OUT);
     if (ok(e)) e = dalloc(&n->dY, b * F_OUT);
-    if (ok(e)) e = dalloc(&n->cpart, ((b + 255) / 256) * HID);
-    if (ok(e)) e = dalloc(&n->part, (b + 255) / 256);
-    if (ok(e)) e = dalloc(&n->loss, 2);
+    if (ok(e)) e = dalloc(&n->gpart, (size_t)kMaxChunks * N_PARAMS);
+    if (ok(e)) e = dalloc(&n->spart, kStageBlocks);
+    if (ok(e)) e = dalloc(&n->lpart, kStageBlocks);
     if (ok(e)) e = dalloc(&n->bD, b);
     if (ok(e)) e = dalloc(&n->bu, b);
     if (ok(e)) e = dalloc(&n->br, b);
@@ -381,61 +595,24 @@ hipError_t ensure_train(fscc_mlp* n, size_t rows) {
     return e;
 }
 
-// h1, h2, Y of `rows` feature rows X
-hipError_t forward_rows(fscc_mlp* n, const float* X, size_t rows, float* h1, float* h2, float* Y) {
-    const float* P = n->p;
-    const int M = (int)rows;
-    hipError_t e = sgemm<false, false, SG_BIAS_RELU>(X, P + OFF_W1, h1, M, HID, F_IN, F_IN, HID, HID, P + OFF_B1,
-                                                     nullptr, 0, n->st);
-    if (ok(e)) e = sgemm<false, false, SG_BIAS_RELU>(h1, P + OFF_W2, h2, M, HID, HID, HID, HID, HID, P + OFF_B2,
-                                                     nullptr, 0, n->st);
-    if (ok(e)) e = sgemm<false, false, SG_BIAS>(h2, P + OFF_W3, Y, M, F_OUT, HID, HID, F_OUT, F_OUT, P + OFF_B3,
-                                                nullptr, 0, n->st);
-    return e;
-}
-
-hipError_t colsum(fscc_mlp* n, const float* H, int M, int N, float* out) {
-    const int rows_per = 256, nchunk = (M + rows_per - 1) / rows_per;
-    if (nchunk == 0) return hipMemsetAsync(out, 0, sizeof(float) * N, n->st);
-    k_colsum_part<<<dim3((N + kT - 1) / kT, nchunk), kT, 0, n->st>>>(H, M, N, rows_per, n->cpart);
-    k_colsum_final<<<(N + kT - 1) / kT, kT, 0, n->st>>>(n->cpart, nchunk, N, out);
-    return hipGetLastError();
-}
-
-// forward + loss + backward on the staged rows (bu, br, bD, bt) -> n->g, n->loss
-hipError_t loss_grad_staged(fscc_mlp* n, size_t rows, int mode) {
+// forward + loss + backward on the rows idx[0..rows) -> n->g, *n->hloss
+hipError_t loss_grad_rows(fscc_mlp* n, const double2* u, const double2* r, const double* D, const double2* t,
+                          const long long* idx, size_t rows, int mode) {
     const int M = (int)rows;
     const float* P = n->p;
-    float* G = n->g;
     hipStream_t st = n->st;
-    k_ws_features<<<grid1(M), kT, 0, st>>>(n->bu, n->br, n->bD, M, n->X);
-    hipError_t e = hipGetLastError();
-    if (ok(e)) e = forward_rows(n, n->X, rows, n->h1, n->h2, n->Y);
-    if (!ok(e)) return e;
-    if (mode == 1) {
-        k_ws_s2<<<grid1(M), kT, 0, st>>>(n->bu, n->br, n->bD, M, n->part);
-        k_sum_parts<<<1, kT, 0, st>>>(n->part, (int)grid1(M), 1.0, n->loss + 1);
-    }
-    k_ws_head<<<grid1(M), kT, 0, st>>>(n->Y, n->bu, n->br, n->bD, n->bt, M, mode, n->loss + 1, n->dY, n->part);
-    k_sum_parts<<<1, kT, 0, st>>>(n->part, (int)grid1(M), 1.0, n->loss);
-    e = hipGetLastError();
-    // W3, b3
-    if (ok(e)) e = sgemm<true, false, SG_PLAIN>(n->h2, n->dY, G + OFF_W3, HID, F_OUT, M, HID, F_OUT, F_OUT, nullptr,
-                                                nullptr, 0, st);
-    if (ok(e)) e = colsum(n, n->dY, M, F_OUT, G + OFF_B3);
-    // dh2 = (dY W3^T) o (h2 > 0)
-    if (ok(e)) e = sgemm<false, true, SG_MASK>(n->dY, P + OFF_W3, n->dh2, M, HID, F_OUT, F_OUT, F_OUT, HID, nullptr,
-                                               n->h2, HID, st);
-    if (ok(e)) e = sgemm<true, false, SG_PLAIN>(n->h1, n->dh2, G + OFF_W2, HID, HID, M, HID, HID, HID, nullptr,
-                                                nullptr, 0, st);
-    if (ok(e)) e = colsum(n, n->dh2, M, HID, G + OFF_B2);
-    // dh1 = (dh2 W2^T) o (h1 > 0)
-    if (ok(e)) e = sgemm<false, true, SG_MASK>(n->dh2, P + OFF_W2, n->dh1, M, HID, HID, HID, HID, HID, nullptr,
-                                               n->h1, HID, st);
-    if (ok(e)) e = sgemm<true, false, SG_PLAIN>(n->X, n->dh1, G + OFF_W1, F_IN, HID, M, F_IN, HID, HID, nullptr,
-                                                nullptr, 0, st);
-    if (ok(e)) e = colsum(n, n->dh1, M, HID, G + OFF_B1);
-    return e;
+    const unsigned nb = std::min(grid1(M), kStageBlocks), nt = (unsigned)((M + kRows - 1) / kRows);
+    k_ws_stage<<<nb, kT, 0, st>>>(u, r, D, t, idx, M, n->bu, n->br, n->bD, n->bt, n->X, n->spart);
+    k_mlp_fwd<true><<<nt, kT, 0, st>>>(P, n->X, M, n->h1, n->h2, n->Y);
+    k_ws_head<<<nb, kT, 0, st>>>(n->Y, n->bu, n->br, n->bD, n->bt, M, mode, n->spart, (int)nb, n->dY, n->lpart);
+    k_mlp_bwd<<<nt, kT, 0, st>>>(P, n->dY, M, n->h1, n->h2, n->dh1, n->dh2);
+    // row chunks of at least 128 rows (four k blocks), at most kMaxChunks
+    int per = std::max(128, (M + kMaxChunks - 1) / kMaxChunks);
+    per = (per + kGradBK - 1) / kGradBK * kGradBK;
+    const int nc = (M + per - 1) / per;
+    k_mlp_wgrad<<<dim3(kGradTiles, nc), kT, 0, st>>>(n->X, n->h1, n->h2, n->dh1, n->dh2, n->dY, M, per, n->gpart);
+    k_mlp_gsum<<<grid1(N_PARAMS), kT, 0, st>>>(n->gpart, nc, n->g, n->lpart, (int)nb, n->hloss);
+    return hipGetLastError();
 }
 
 hipError_t adam(fscc_mlp* n, float lr) {
@@ -570,17 +747,14 @@ fscc_status fscc_ws_gather(const void* src, size_t elem_bytes, const int64_t* id
 
 fscc_status fscc_mlp_forward(fscc_mlp* n, const float* X, size_t rows, float* Y) {
     if (!n || (rows && (!X || !Y))) return FSCC_EINVAL;
-    const size_t ch = (size_t)1 << 20;
+    if (!rows) return FSCC_OK;
+    // grids of at most 2^30 rows
     hipError_t e = hipSuccess;
-    if (!n->ih1) {
-        e = dalloc(&n->ih1, ch * HID);
-        if (ok(e)) e = dalloc(&n->ih2, ch * HID);
-        if (!ok(e)) return herr(n, e, "inference scratch");
-        n->chunk = ch;
-    }
-    for (size_t r0 = 0; r0 < rows && ok(e); r0 += ch) {
-        const size_t m = rows - r0 < ch ? rows - r0 : ch;
-        e = forward_rows(n, X + r0 * F_IN, m, n->ih1, n->ih2, Y + r0 * F_OUT);
+    for (size_t r0 = 0; r0 < rows && ok(e); r0 += (size_t)1 << 30) {
+        const size_t m = std::min(rows - r0, (size_t)1 << 30);
+        k_mlp_fwd<false><<<(unsigned)((m + kRows - 1) / kRows), kT, 0, n->st>>>(n->p, X + r0 * F_IN, (long long)m,
+                                                                               nullptr, nullptr, Y + r0 * F_OUT);
+        e = hipGetLastError();
     }
     return ok(e) ? FSCC_OK : herr(n, e, "forward");
 }
@@ -591,26 +765,8 @@ fscc_status fscc_mlp_loss_grad(fscc_mlp* n, const fscc_c128* u, const fscc_c128*
         return FSCC_EINVAL;
     hipError_t e = ensure_train(n, rows);
     if (!ok(e)) return herr(n, e, "training scratch");
-    hipStream_t st = n->st;
-    if (idx) {
-        k_gather_rows<<<grid1(rows), kT, 0, st>>>((const unsigned char*)u, 16, (const long long*)idx, rows,
-                                                  (unsigned char*)n->bu);
-        k_gather_rows<<<grid1(rows), kT, 0, st>>>((const unsigned char*)r, 16, (const long long*)idx, rows,
-                                                  (unsigned char*)n->br);
-        k_gather_rows<<<grid1(rows), kT, 0, st>>>((const unsigned char*)t, 16, (const long long*)idx, rows,
-                                                  (unsigned char*)n->bt);
-        k_gather_rows<<<grid1(rows), kT, 0, st>>>((const unsigned char*)D, 8, (const long long*)idx, rows,
-                                                  (unsigned char*)n->bD);
-    } else {
-        e = hipMemcpyAsync(n->bu, u, 16 * rows, hipMemcpyDeviceToDevice, st);
-        if (ok(e)) e = hipMemcpyAsync(n->br, r, 16 * rows, hipMemcpyDeviceToDevice, st);
-        if (ok(e)) e = hipMemcpyAsync(n->bt, t, 16 * rows, hipMemcpyDeviceToDevice, st);
-        if (ok(e)) e = hipMemcpyAsync(n->bD, D, 8 * rows, hipMemcpyDeviceToDevice, st);
-    }
-    if (ok(e)) e = hipGetLastError();
-    if (ok(e)) e = loss_grad_staged(n, rows, mode);
-    if (ok(e)) e = hipMemcpyAsync(n->hloss, n->loss, sizeof(double), hipMemcpyDeviceToHost, st);
-    if (ok(e)) e = hipStreamSynchronize(st);
+    e = loss_grad_rows(n, (const double2*)u, (const double2*)r, D, (const double2*)t, (const long long*)idx, rows, mode);
+    if (ok(e)) e = hipStreamSynchronize(n->st);
     if (!ok(e)) return herr(n, e, "loss/grad");
     *loss = *n->hloss;
     return FSCC_OK;

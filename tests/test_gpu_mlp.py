@@ -140,3 +140,30 @@ def test_untrained_network_is_the_second_jacobi_iterate_and_training_lowers_the_
     print("loss", L0, "->", L1, flush=True)
     assert L1 < 0.2 * L0
     net.destroy()
+
+
+@pytest.mark.parametrize("rows", [1, 63, 64, 65, 127, 129, 8191, 8193])
+def test_row_tiles_and_gradient_chunks(rows):
+    """Row counts at the edges of the 64-row tiles, of the 32-row gradient slices and of the row chunks
+    (128 rows each up to 64 chunks, longer ones above); same bound as above."""
+    torch = _torch()
+    import paper_2004_03682_amd as F
+    u, r, D, t = _rows(rows, rows)
+    p = _params(20)
+    net = F.MLP(seed=0)
+    net.set_params(p)
+    L = net.loss_grad(dev(u), dev(r), dev(D), dev(t), mode=1)
+    g = net.get_grad()
+    x, v, s = O.features(u, r, D)
+    x = x.astype(np.float32)
+    Lo, go = O.loss_and_grad(p.astype(np.float64), x.astype(np.float64), u, v, t, s, 1)
+    assert abs(L - Lo) <= 1e-4 * max(Lo, 1e-30)
+    assert np.linalg.norm(g - go) <= 1e-4 * np.linalg.norm(go)
+    # the rows past the end of the output stay untouched
+    Y = torch.full((rows + 3, 4), 7.0, dtype=torch.float32, device="cuda")
+    net.forward(dev(x), Y[:rows])
+    ref, _ = O.forward(p.astype(np.float64), x.astype(np.float64))
+    got = Y.cpu().numpy()
+    assert np.abs(got[:rows] - ref).max() <= 1e-4 * max(np.abs(ref).max(), 1e-30)
+    assert (got[rows:] == 7.0).all()
+    net.destroy()
