@@ -33,16 +33,20 @@ constexpr size_t OFF_W1 = 0, OFF_B1 = OFF_W1 + F_IN * HID, OFF_W2 = OFF_B1 + HID
                  OFF_W3 = OFF_B2 + HID, OFF_B3 = OFF_W3 + HID * F_OUT, N_PARAMS = OFF_B3 + F_OUT;
 
 // ---------------------------------------------------------------------------
-// Network kernels.  One workgroup carries 64 rows through whole layers: the
-// 64 x 256 activations stay in LDS (64 KB, two workgroups per CU) between the
-// layers, and the weights (256 KB, resident in every L2) are read as MFMA
-// fragments straight from memory one 16-deep k block ahead.  Four waves, each
-// 64 rows x 64 columns: 16 accumulators, 64 MFMAs (2048 cycles) per k block
-// against 4 LDS reads and 16 loads.
+// Network kernels.  One workgroup carries 16 * FM rows through whole layers:
+// the activations (64 KB for 64 rows, two workgroups per CU) stay in LDS
+// between the layers, and the weights (256 KB, resident in every L2) are read
+// as MFMA fragments straight from memory one 16-deep k block ahead.  Four
+// waves, each all rows x 64 columns: for 64 rows 16 accumulators, 64 MFMAs
+// (2048 cycles) per k block against 4 LDS reads and 16 loads.
 //
 // LDS rows hold 64 chunks of four floats; chunk c of row r sits at c ^ (r & 15),
 // so the 16 rows of a fragment read 16 different 16-byte bank groups.
-constexpr int kRows = 64;
+
+// Row fragments per workgroup: 64-row tiles read the weights least often;
+// fewer rows per workgroup where 64 would leave CUs without two workgroups
+// (a training step on 8192 rows: forward and backward 97 -> 52 us).
+int mlp_fm(long long rows) { return rows > 32 * 512 ? 4 : rows > 16 * 512 ? 2 : 1; }
 
 __device__ __forceinline__ int lds_chunk(int row, int chunk) { return row * HID + ((chunk ^ (row & 15)) << 2); }
 
@@ -52,12 +56,13 @@ __device__ __forceinline__ int lds_chunk(int row, int chunk) { return row * HID 
 // chunk 4 (k / 16) + k % 4, element (k % 16) / 4: a lane's 16-byte read then
 // holds its k of four consecutive MFMA steps.  Bound by the fp32 matrix cores
 // (138 kflop a row, no activation leaves the CU): features, network and
-// prediction of 600001 rows 1.88 -> 0.84 ms against one launch per layer with
+// prediction of 600001 rows 1.88 -> 0.73 ms against one launch per layer with
 // the activations in device memory.
-template <bool STORE>
-__global__ __launch_bounds__(256) void k_mlp_fwd(const float* __restrict__ P, const float* __restrict__ X,
+template <int FM, bool STORE>
+__global__ __launch_bounds__(256, 2) void k_mlp_fwd(const float* __restrict__ P, const float* __restrict__ X,
                                                  long long rows, float* __restrict__ h1, float* __restrict__ h2,
                                                  float* __restrict__ Y) {
+    constexpr int kRows = 16 * FM;
     __shared__ float act[kRows * HID];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 15, lq = lane >> 4;
     const long long r0 = (long long)blockIdx.x * kRows;
@@ -66,9 +71,9 @@ __global__ __launch_bounds__(256) void k_mlp_fwd(const float* __restrict__ P, co
         act[lds_chunk(row, (col >> 4) * 4 + (col & 3)) + ((col & 15) >> 2)] = v;
     };
     {
-        float a[4][2], b[4][2];
+        float a[FM][2], b[4][2];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < FM; ++i) {
             const long long r = min(r0 + 16 * i + lr, rows - 1);
 #pragma unroll
             for (int k = 0; k < 2; ++k) a[i][k] = X[r * F_IN + 4 * k + lq];
@@ -82,7 +87,7 @@ __global__ __launch_bounds__(256) void k_mlp_fwd(const float* __restrict__ P, co
             const int col = n0 + 16 * j + lr;
             const float bias = P[OFF_B1 + col];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < FM; ++i) {
                 f4v c = f4v{0.f, 0.f, 0.f, 0.f};
                 c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][0], b[j][0], c, 0, 0, 0);
                 c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][1], b[j][1], c, 0, 0, 0);
@@ -96,9 +101,9 @@ __global__ __launch_bounds__(256) void k_mlp_fwd(const float* __restrict__ P, co
             }
         }
     }
-    f4v acc[4][4];
+    f4v acc[FM][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[i][j] = f4v{0.f, 0.f, 0.f, 0.f};
     const float* W2 = P + OFF_W2 + lq * HID + n0 + lr;
@@ -110,13 +115,13 @@ __global__ __launch_bounds__(256) void k_mlp_fwd(const float* __restrict__ P, co
             for (int j = 0; j < 4; ++j) d[j][k] = W2[(16 * kb + 4 * k) * HID + 16 * j];
     };
     auto block = [&](int kb, const float (&w)[4][4]) {
-        f4v a[4];
+        f4v a[FM];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) a[i] = *(const f4v*)&act[lds_chunk(16 * i + lr, 4 * kb + lq)];
+        for (int i = 0; i < FM; ++i) a[i] = *(const f4v*)&act[lds_chunk(16 * i + lr, 4 * kb + lq)];
 #pragma unroll
         for (int k = 0; k < 4; ++k)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < FM; ++i)
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][k], w[j][k], acc[i][j], 0, 0, 0);
@@ -130,12 +135,22 @@ __global__ __launch_bounds__(256) void k_mlp_fwd(const float* __restrict__ P, co
         block(kb + 1, bn);
     }
     __syncthreads();   // every wave has read the first layer's activations
+    // the last layer's weights, under way during the epilogue (lanes past the
+    // four outputs read in range and take zero)
+    const uint32_t keep = lr < F_OUT ? 0xFFFFFFFFu : 0u;
+    uint32_t w3[HID / 16][4];
+    if (wave < FM)
+#pragma unroll
+        for (int kb = 0; kb < HID / 16; ++kb)
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                w3[kb][k] = ((const uint32_t*)P)[OFF_W3 + (16 * kb + 4 * k + lq) * F_OUT + (lr & 3)];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const int col = n0 + 16 * j + lr;
         const float bias = P[OFF_B2 + col];
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < FM; ++i)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int row = 16 * i + 4 * lq + q;
@@ -145,20 +160,17 @@ __global__ __launch_bounds__(256) void k_mlp_fwd(const float* __restrict__ P, co
             }
     }
     __syncthreads();
+    if (wave >= FM) return;
     // last layer: 16 rows per wave, the four outputs padded to one fragment
     f4v c = f4v{0.f, 0.f, 0.f, 0.f};
-    const bool out = lr < F_OUT;
-    const float* W3 = P + OFF_W3 + lq * F_OUT + (out ? lr : 0);
-#pragma unroll 4
+#pragma unroll
     for (int kb = 0; kb < HID / 16; ++kb) {
         const f4v a = *(const f4v*)&act[lds_chunk(16 * wave + lr, 4 * kb + lq)];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const float w = out ? W3[(16 * kb + 4 * k) * F_OUT] : 0.f;
-            c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[k], w, c, 0, 0, 0);
-        }
+        for (int k = 0; k < 4; ++k)
+            c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[k], __uint_as_float(w3[kb][k] & keep), c, 0, 0, 0);
     }
-    if (out) {
+    if (lr < F_OUT) {
         const float bias = P[OFF_B3 + lr];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -170,9 +182,11 @@ __global__ __launch_bounds__(256) void k_mlp_fwd(const float* __restrict__ P, co
 
 // Backward through the hidden layers in one launch:
 // dh2 = (dY W3^T) o (h2 > 0) into LDS and memory, dh1 = (dh2 W2^T) o (h1 > 0).
-__global__ __launch_bounds__(256) void k_mlp_bwd(const float* __restrict__ P, const float* __restrict__ dY, int rows,
+template <int FM>
+__global__ __launch_bounds__(256, 2) void k_mlp_bwd(const float* __restrict__ P, const float* __restrict__ dY, int rows,
                                                  const float* __restrict__ h1, const float* __restrict__ h2,
                                                  float* __restrict__ dh1, float* __restrict__ dh2) {
+    constexpr int kRows = 16 * FM;
     __shared__ float act[kRows * HID];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lq = lane >> 4;
     const long long r0 = (long long)blockIdx.x * kRows;
@@ -188,9 +202,9 @@ __global__ __launch_bounds__(256) void k_mlp_bwd(const float* __restrict__ P, co
             if (r0 + r < rows) dh2[row * HID + tid] = v;
         }
     }
-    f4v acc[4][4];
+    f4v acc[FM][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[i][j] = f4v{0.f, 0.f, 0.f, 0.f};
     const int n0 = wave * 64;
@@ -201,13 +215,13 @@ __global__ __launch_bounds__(256) void k_mlp_bwd(const float* __restrict__ P, co
         for (int j = 0; j < 4; ++j) d[j] = *(const f4v*)&W2[16 * j * HID + 16 * kb];
     };
     auto block = [&](int kb, const f4v (&w)[4]) {
-        f4v a[4];
+        f4v a[FM];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) a[i] = *(const f4v*)&act[lds_chunk(16 * i + lr, 4 * kb + lq)];
+        for (int i = 0; i < FM; ++i) a[i] = *(const f4v*)&act[lds_chunk(16 * i + lr, 4 * kb + lq)];
 #pragma unroll
         for (int k = 0; k < 4; ++k)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < FM; ++i)
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][k], w[j][k], acc[i][j], 0, 0, 0);
@@ -224,7 +238,7 @@ __global__ __launch_bounds__(256) void k_mlp_bwd(const float* __restrict__ P, co
     for (int j = 0; j < 4; ++j) {
         const int col = n0 + 16 * j + lr;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < FM; ++i)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const long long row = r0 + 16 * i + 4 * lq + q;
@@ -240,7 +254,7 @@ __global__ __launch_bounds__(256) void k_mlp_bwd(const float* __restrict__ P, co
 // Bound by launch and load latency at these sizes: 128 rows per chunk give 1536
 // workgroups for a minibatch of 8192.  (With the rows unsplit, 16 and 4
 // workgroups walked all of them: 3.4 ms of a 3.75 ms training step on 8192
-// rows; the whole step now takes 0.18 ms.)
+// rows; the whole step now takes 0.14 ms.)
 constexpr int kGradTiles = 24, kGradBK = 32, kMaxChunks = 64;
 __global__ __launch_bounds__(256) void k_mlp_wgrad(const float* __restrict__ X, const float* __restrict__ h1,
                                                    const float* __restrict__ h2, const float* __restrict__ dh1,
@@ -513,6 +527,15 @@ __global__ __launch_bounds__(256) void k_ws_step(const double2* __restrict__ t, 
     out[k] = make_double2(tt.x + rr.x / d, tt.y + rr.y / d);
 }
 
+template <bool STORE>
+void launch_fwd(const float* P, const float* X, long long rows, float* h1, float* h2, float* Y, hipStream_t st) {
+    const int fm = mlp_fm(rows);
+    const unsigned nt = (unsigned)((rows + 16 * fm - 1) / (16 * fm));
+    if (fm == 4) k_mlp_fwd<4, STORE><<<nt, kT, 0, st>>>(P, X, rows, h1, h2, Y);
+    else if (fm == 2) k_mlp_fwd<2, STORE><<<nt, kT, 0, st>>>(P, X, rows, h1, h2, Y);
+    else k_mlp_fwd<1, STORE><<<nt, kT, 0, st>>>(P, X, rows, h1, h2, Y);
+}
+
 unsigned grid1(long long n) { return (unsigned)((n + kT - 1) / kT); }
 
 }  // namespace
@@ -601,11 +624,15 @@ hipError_t loss_grad_rows(fscc_mlp* n, const double2* u, const double2* r, const
     const int M = (int)rows;
     const float* P = n->p;
     hipStream_t st = n->st;
-    const unsigned nb = std::min(grid1(M), kStageBlocks), nt = (unsigned)((M + kRows - 1) / kRows);
+    const unsigned nb = std::min(grid1(M), kStageBlocks);
     k_ws_stage<<<nb, kT, 0, st>>>(u, r, D, t, idx, M, n->bu, n->br, n->bD, n->bt, n->X, n->spart);
-    k_mlp_fwd<true><<<nt, kT, 0, st>>>(P, n->X, M, n->h1, n->h2, n->Y);
+    launch_fwd<true>(P, n->X, M, n->h1, n->h2, n->Y, st);
     k_ws_head<<<nb, kT, 0, st>>>(n->Y, n->bu, n->br, n->bD, n->bt, M, mode, n->spart, (int)nb, n->dY, n->lpart);
-    k_mlp_bwd<<<nt, kT, 0, st>>>(P, n->dY, M, n->h1, n->h2, n->dh1, n->dh2);
+    const int fm = mlp_fm(M);
+    const unsigned nt = (unsigned)((M + 16 * fm - 1) / (16 * fm));
+    if (fm == 4) k_mlp_bwd<4><<<nt, kT, 0, st>>>(P, n->dY, M, n->h1, n->h2, n->dh1, n->dh2);
+    else if (fm == 2) k_mlp_bwd<2><<<nt, kT, 0, st>>>(P, n->dY, M, n->h1, n->h2, n->dh1, n->dh2);
+    else k_mlp_bwd<1><<<nt, kT, 0, st>>>(P, n->dY, M, n->h1, n->h2, n->dh1, n->dh2);
     // row chunks of at least 128 rows (four k blocks), at most kMaxChunks
     int per = std::max(128, (M + kMaxChunks - 1) / kMaxChunks);
     per = (per + kGradBK - 1) / kGradBK * kGradBK;
@@ -752,8 +779,7 @@ fscc_status fscc_mlp_forward(fscc_mlp* n, const float* X, size_t rows, float* Y)
     hipError_t e = hipSuccess;
     for (size_t r0 = 0; r0 < rows && ok(e); r0 += (size_t)1 << 30) {
         const size_t m = std::min(rows - r0, (size_t)1 << 30);
-        k_mlp_fwd<false><<<(unsigned)((m + kRows - 1) / kRows), kT, 0, n->st>>>(n->p, X + r0 * F_IN, (long long)m,
-                                                                               nullptr, nullptr, Y + r0 * F_OUT);
+        launch_fwd<false>(n->p, X + r0 * F_IN, (long long)m, nullptr, nullptr, Y + r0 * F_OUT, n->st);
         e = hipGetLastError();
     }
     return ok(e) ? FSCC_OK : herr(n, e, "forward");
