@@ -537,13 +537,10 @@ void ctx_allocate(fscc_ctx* c, bool diis) {
         c->rs_tmp = (double2*)c->dalloc((size_t)std::max<int64_t>(1, ntmp) * sizeof(double2));
     }
     if (P.has02) setup_diis(c, c->diis[2], 0, P.L_S02.total, -1, P.b_D02);
-    c->part = (double*)c->dalloc(1024 * kDiisMax * sizeof(double));
-    c->part_max = (double*)c->dalloc(2048 * sizeof(double));
+    c->part = (double*)c->dalloc((size_t)kReduceBlocks * (kDiisMax + 1) * sizeof(double));
     c->coef = (double*)c->dalloc((kMaxDiis + 1) * sizeof(double));
-    c->scal = (double*)c->dalloc(4 * sizeof(double));
-    c->epart = (double*)c->dalloc(2048 * sizeof(double));
-    c->eout = (double*)c->dalloc(4 * sizeof(double));
-    hip_check(hipHostMalloc((void**)&c->hscal, 8 * sizeof(double), hipHostMallocDefault), "hipHostMalloc");
+    hip_check(hipHostMalloc((void**)&c->hscal, (8 + 2 * kReduceBlocks) * sizeof(double), hipHostMallocDefault),
+              "hipHostMalloc");
 }
 
 }  // namespace rt
@@ -1146,12 +1143,12 @@ namespace {
 
 // The update of one sector up to the device work: Jacobi step, DIIS dots,
 // bordered solve and extrapolation enqueued on the stream, the subspace's
-// slot bookkeeping done, and max|step| / dropped vectors copied to pinned
-// host memory (hscal[0..1]); update_finish reads them after a sync.
+// slot bookkeeping done; max|step| and the number of dropped vectors arrive in
+// pinned host memory (hscal[0..1]), update_finish reads them after a sync.
 void update_enqueue(fscc_ctx* ctx, fscc_sector sector, fscc_c128* t1, fscc_c128* t2, const fscc_c128* r1,
                     const fscc_c128* r2) {
     Diis& D = ctx->diis[sector];
-    const int64_t n1 = D.n1, n2 = D.n2, n = n1 + n2;
+    const int64_t n1 = D.n1, n2 = D.n2;
     const int depth = std::max(1, D.ndiis);
     std::vector<int>& ord = D.order;
     int slot;
@@ -1165,66 +1162,28 @@ void update_enqueue(fscc_ctx* ctx, fscc_sector sector, fscc_c128* t1, fscc_c128*
         ord.erase(ord.begin());
     }
     ord.push_back(slot);
-    double2* ht = D.ht + (size_t)slot * n;
-    double2* he = D.he + (size_t)slot * n;
-    int nb1 = n1 > 0 ? reduce_blocks(n1) : 0, nb2 = n2 > 0 ? reduce_blocks(n2) : 0;
-    if (ctx->real) {
-        // the same sequence on doubles (history slots hold n doubles)
-        double* dht = (double*)D.ht + (size_t)slot * n;
-        double* dhe = (double*)D.he + (size_t)slot * n;
-        if (n1 > 0)
-            hip_check(launch_djacobi((const double*)t1, (const double*)r1, (const double*)ctx->dbuf[D.b_D1], dht, dhe, n1,
-                                     ctx->part_max, nb1, ctx->st, D.shift, D.dyn_S, D.dyn_n),
-                      "jacobi 1");
-        if (n2 > 0)
-            hip_check(launch_djacobi((const double*)t2, (const double*)r2, (const double*)ctx->dbuf[D.b_D2], dht + n1,
-                                     dhe + n1, n2, ctx->part_max + nb1, nb2, ctx->st, D.shift, D.dyn_S, D.dyn_n),
-                      "jacobi 2");
-        int m = (int)ord.size();
-        std::vector<const double*> ev(m);
-        for (int j = 0; j < m; ++j) ev[j] = (const double*)D.he + (size_t)ord[j] * n;
-        int nbd = reduce_blocks(n);
-        hip_check(launch_ddots(ev.data(), m, dhe, n, ctx->part, nbd, ctx->st), "diis dots");
-        DiisOrder dord{};
-        for (int j = 0; j < m; ++j) dord.v[j] = ord[j];
-        hip_check(launch_finish_diis(ctx->part, nbd, m, ctx->part_max, nb1 + nb2, D.dB, kMaxDiis, slot, dord,
-                                     ctx->coef, ctx->scal, ctx->st),
-                  "diis solve");
-        std::vector<const double*> xs(kMaxDiis);
-        for (int q = 0; q < kMaxDiis; ++q) xs[q] = (const double*)D.ht + (size_t)q * n;
-        if (n1 > 0) hip_check(launch_dlincomb((double*)t1, xs.data(), ctx->coef, kMaxDiis, n1, ctx->st), "lincomb 1");
-        if (n2 > 0) {
-            for (int q = 0; q < kMaxDiis; ++q) xs[q] = (const double*)D.ht + (size_t)q * n + n1;
-            hip_check(launch_dlincomb((double*)t2, xs.data(), ctx->coef, kMaxDiis, n2, ctx->st), "lincomb 2");
-        }
-    } else {
-        if (n1 > 0)
-            hip_check(launch_jacobi((const double2*)t1, (const double2*)r1, (const double*)ctx->dbuf[D.b_D1], ht, he, n1,
-                                    ctx->part_max, nb1, ctx->st, D.shift, D.dyn_S, D.dyn_n),
-                      "jacobi 1");
-        if (n2 > 0)
-            hip_check(launch_jacobi((const double2*)t2, (const double2*)r2, (const double*)ctx->dbuf[D.b_D2], ht + n1,
-                                    he + n1, n2, ctx->part_max + nb1, nb2, ctx->st, D.shift, D.dyn_S, D.dyn_n),
-                      "jacobi 2");
-        int m = (int)ord.size();
-        std::vector<const double2*> ev(m);
-        for (int j = 0; j < m; ++j) ev[j] = D.he + (size_t)ord[j] * n;
-        int nbd = reduce_blocks(n);
-        hip_check(launch_dots(ev.data(), m, he, n, ctx->part, nbd, ctx->st), "diis dots");
-        DiisOrder dord{};
-        for (int j = 0; j < m; ++j) dord.v[j] = ord[j];
-        hip_check(launch_finish_diis(ctx->part, nbd, m, ctx->part_max, nb1 + nb2, D.dB, kMaxDiis, slot, dord,
-                                     ctx->coef, ctx->scal, ctx->st),
-                  "diis solve");
-        std::vector<const double2*> xs(kMaxDiis);
-        for (int s = 0; s < kMaxDiis; ++s) xs[s] = D.ht + (size_t)s * n;
-        if (n1 > 0) hip_check(launch_lincomb((double2*)t1, xs.data(), ctx->coef, kMaxDiis, n1, ctx->st), "lincomb 1");
-        if (n2 > 0) {
-            for (int s = 0; s < kMaxDiis; ++s) xs[s] = D.ht + (size_t)s * n + n1;
-            hip_check(launch_lincomb((double2*)t2, xs.data(), ctx->coef, kMaxDiis, n2, ctx->st), "lincomb 2");
-        }
-    }
-    hip_check(hipMemcpyAsync(ctx->hscal, ctx->scal, 2 * sizeof(double), hipMemcpyDeviceToHost, ctx->st), "scal");
+    UpdateArgs u{};
+    u.t1 = t1;
+    u.t2 = t2;
+    u.r1 = r1;
+    u.r2 = r2;
+    u.D1 = n1 > 0 ? (const double*)ctx->dbuf[D.b_D1] : nullptr;
+    u.D2 = n2 > 0 ? (const double*)ctx->dbuf[D.b_D2] : nullptr;
+    u.ht = D.ht;   // slots of n doubles in a real context
+    u.he = D.he;
+    u.n1 = n1;
+    u.n2 = n2;
+    u.slot = slot;
+    u.m = (int)ord.size();
+    for (int j = 0; j < u.m; ++j) u.order.v[j] = ord[j];
+    u.part = ctx->part;
+    u.B = D.dB;
+    u.coef = ctx->coef;
+    u.out = ctx->hscal;
+    u.shift = D.shift;
+    u.dyn_S = D.dyn_S;
+    u.dyn_n = D.dyn_n;
+    hip_check(launch_update(u, ctx->real, ctx->st), "amplitude update");
 }
 
 // After the stream has synchronised: subspace bookkeeping from the device's
@@ -1258,18 +1217,33 @@ fscc_status update_finish(fscc_ctx* ctx, fscc_sector sector, double* max_step) {
     return FSCC_OK;
 }
 
-// (0h,0p) energy of t1, t2: tau = t2 + t1 t1 (the first two operations of
-// the plan), sum <ij||ab> tau, result copied to hscal[4..5].
+// (0h,0p) energy of t1, t2: sum <ij||ab> tau with tau = t2 + t1 t1 formed from
+// the maps of the plan's second operation; block partials arrive in hscal + 8,
+// energy_finish adds them after a sync.
 void energy_enqueue(fscc_ctx* ctx, const fscc_c128* t1, const fscc_c128* t2) {
     Plan& P = ctx->plan;
     bind_io(ctx, t1, t2, nullptr, nullptr);
-    for (size_t k = 0; k < 2; ++k) ctx->run_op(P.ops[k], &ctx->L00.g[k]);
-    int nb = reduce_blocks(ctx->n2());
-    if (ctx->real)
-        hip_check(launch_ddot(ctx->D(P.b_oovv), ctx->D(P.b_tau), ctx->n2(), ctx->epart, nb, ctx->eout, ctx->st), "energy");
-    else
-        hip_check(launch_zdotu(ctx->B(P.b_oovv), ctx->B(P.b_tau), ctx->n2(), ctx->epart, nb, ctx->eout, ctx->st), "energy");
-    hip_check(hipMemcpyAsync(ctx->hscal + 4, ctx->eout, 2 * sizeof(double), hipMemcpyDeviceToHost, ctx->st), "e d2h");
+    const Op& o = P.ops[1];
+    if (o.name != "tau+=t1t1" || o.mapsA.size() != 2 || o.mapsB.size() != 2) throw std::logic_error("no t1 x t1 reorder");
+    GatherMaps gm{};
+    for (int t = 0; t < 2; ++t) {
+        gm.a[t] = ctx->dmap[o.mapsA[t]];
+        gm.b[t] = ctx->dmap[o.mapsB[t]];
+    }
+    hip_check(launch_energy(ctx->dbuf[P.b_oovv], t1, t2, gm, ctx->n2(), ctx->hscal + 8, reduce_blocks(ctx->n2()),
+                            ctx->real, ctx->st),
+              "energy");
+}
+
+void energy_finish(const fscc_ctx* ctx, double* e_re, double* e_im) {
+    const int nb = reduce_blocks(ctx->n2());
+    double r = 0.0, i = 0.0;
+    for (int b = 0; b < nb; ++b) {
+        r += ctx->hscal[8 + 2 * b];
+        i += ctx->hscal[8 + 2 * b + 1];
+    }
+    *e_re = r;
+    *e_im = i;
 }
 
 }  // namespace
@@ -1303,8 +1277,7 @@ fscc_status fscc_iterate(fscc_ctx* ctx, fscc_c128* t1, fscc_c128* t2, fscc_c128*
         update_enqueue(ctx, FSCC_S00, t1, t2, r1, r2);
         energy_enqueue(ctx, t1, t2);
         hip_check(hipStreamSynchronize(ctx->st), "iteration sync");
-        *e_re = ctx->hscal[4];
-        *e_im = ctx->hscal[5];
+        energy_finish(ctx, e_re, e_im);
         return update_finish(ctx, FSCC_S00, max_step);
     });
 }
@@ -1316,8 +1289,7 @@ fscc_status fscc_energy(fscc_ctx* ctx, const fscc_c128* t1, const fscc_c128* t2,
     return guarded(ctx, [&]() -> fscc_status {
         energy_enqueue(ctx, t1, t2);
         hip_check(hipStreamSynchronize(ctx->st), "energy sync");
-        *e_re = ctx->hscal[4];
-        *e_im = ctx->hscal[5];
+        energy_finish(ctx, e_re, e_im);
         return FSCC_OK;
     });
 }

@@ -1368,252 +1368,6 @@ hipError_t launch_zero(double2* dst, long long n, hipStream_t st) {
     return hipGetLastError();
 }
 
-// ---------------------------------------------------------------------------
-// reductions (deterministic: fixed grid, per-block partials, one final block)
-
-int reduce_blocks(long long n) {
-    long long b = (n + kThreads - 1) / kThreads;
-    if (b < 1) b = 1;
-    if (b > 1024) b = 1024;
-    return (int)b;
-}
-
-__device__ __forceinline__ double block_sum(double v, double* sh) {
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    for (int s = kThreads / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-        __syncthreads();
-    }
-    double r = sh[0];
-    __syncthreads();
-    return r;
-}
-
-__device__ __forceinline__ double block_max(double v, double* sh) {
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    for (int s = kThreads / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) {
-            double a = sh[threadIdx.x], b = sh[threadIdx.x + s];
-            sh[threadIdx.x] = (a > b || a != a) ? a : b;   // NaN propagates
-        }
-        __syncthreads();
-    }
-    double r = sh[0];
-    __syncthreads();
-    return r;
-}
-
-// Dynamic denominator shift of one amplitude (sector shift S < 0, exponent
-// n >= 1): Delta = S (S / (min(D, 0) + S))^n; the shifted equations are
-// R = Delta t, solved by the step (R - Delta t) / (D + Delta).
-__device__ __forceinline__ double dyn_delta(double d, double S, int n) {
-    const double q = S / (fmin(d, 0.0) + S);
-    double p = q;
-    for (int i = 1; i < n; ++i) p *= q;
-    return S * p;
-}
-
-__global__ __launch_bounds__(256) void k_jacobi(const double2* __restrict__ t, const double2* __restrict__ r,
-                                                const double* __restrict__ D, double2* __restrict__ ht,
-                                                double2* __restrict__ he, long long n, double* part_max,
-                                                double shift, double dS, int dn) {
-    __shared__ double sh[kThreads];
-    double mx = 0.0;
-    for (long long k = (long long)blockIdx.x * kThreads + threadIdx.x; k < n; k += (long long)gridDim.x * kThreads) {
-        double2 rr = r[k], tt = t[k];
-        double d = D[k];
-        if (dS != 0.0) {
-            const double dl = dyn_delta(d, dS, dn);
-            rr.x -= dl * tt.x;
-            rr.y -= dl * tt.y;
-            d += dl;
-        }
-        d -= shift;
-        double2 s = make_double2(rr.x / d, rr.y / d);
-        he[k] = s;
-        ht[k] = make_double2(tt.x + s.x, tt.y + s.y);
-        double a = sqrt(s.x * s.x + s.y * s.y);
-        mx = (a > mx || a != a) ? a : mx;
-    }
-    double b = block_max(mx, sh);
-    if (threadIdx.x == 0) part_max[blockIdx.x] = b;
-}
-
-hipError_t launch_jacobi(const double2* t, const double2* r, const double* D, double2* hist_t, double2* hist_e,
-                         long long n, double* part_max, int nblk, hipStream_t st, double shift, double dyn_S,
-                         int dyn_n) {
-    if (dyn_S != 0.0 && !(dyn_S < 0.0 && dyn_n >= 1)) return hipErrorInvalidValue;
-    k_jacobi<<<nblk, kThreads, 0, st>>>(t, r, D, hist_t, hist_e, n, part_max, shift, dyn_S, dyn_n);
-    return hipGetLastError();
-}
-
-// part[b*kDiisMax + j] = Re sum conj(e_j) enew over block b's share
-struct PtrList {
-    const double2* p[kDiisMax];
-};
-
-__global__ __launch_bounds__(256) void k_dots(PtrList e, int m, const double2* __restrict__ enew, long long n,
-                                              double* part) {
-    __shared__ double sh[kThreads];
-    double acc[kDiisMax];
-#pragma unroll
-    for (int j = 0; j < kDiisMax; ++j) acc[j] = 0.0;
-    for (long long k = (long long)blockIdx.x * kThreads + threadIdx.x; k < n; k += (long long)gridDim.x * kThreads) {
-        double2 y = enew[k];
-#pragma unroll
-        for (int j = 0; j < kDiisMax; ++j)
-            if (j < m) {
-                double2 x = e.p[j][k];
-                acc[j] += x.x * y.x + x.y * y.y;
-            }
-    }
-#pragma unroll
-    for (int j = 0; j < kDiisMax; ++j)
-        if (j < m) {
-            double b = block_sum(acc[j], sh);
-            if (threadIdx.x == 0) part[blockIdx.x * kDiisMax + j] = b;
-        }
-}
-
-hipError_t launch_dots(const double2* const* e, int m, const double2* enew, long long n, double* part, int nblk,
-                       hipStream_t st) {
-    if (m < 0 || m > kDiisMax) return hipErrorInvalidValue;
-    PtrList pl;
-    for (int j = 0; j < kDiisMax; ++j) pl.p[j] = j < m ? e[j] : nullptr;
-    k_dots<<<nblk, kThreads, 0, st>>>(pl, m, enew, n, part);
-    return hipGetLastError();
-}
-
-// Bordered Pulay system over the slots order[0..m) (oldest first) of the
-// symmetric matrix B (leading dimension ldb): Gaussian elimination with
-// partial pivoting in FP64; a pivot below 1e-14 * max|A| drops the oldest
-// slot and the solve is repeated.  coef[slot] receives the coefficients (0 for
-// slots not used).  Single-thread code; the working matrix wa ((MAXM + 1) x
-// (MAXM + 2)) and x (MAXM + 1) live in LDS (as private arrays they would be
-// scratch memory, which made the solve 20x slower).  Returns the number of
-// dropped slots.
-template <int MAXM>
-__device__ int diis_solve(const double* B, int ldb, const int* order, int m, double* coef, double* __restrict__ wa,
-                          double* __restrict__ x) {
-    auto A = [wa](int i, int j) -> double& { return wa[i * (MAXM + 2) + j]; };
-    for (int j = 0; j < ldb; ++j) coef[j] = 0.0;
-    int first = 0, dropped = 0;
-    while (true) {
-        int k = m - first;
-        if (k <= 1) {
-            coef[order[m - 1]] = 1.0;
-            break;
-        }
-        double scale = 0.0;
-        for (int i = 0; i < k; ++i) scale = fmax(scale, fabs(B[order[first + i] * ldb + order[first + i]]));
-        if (!(scale > 0.0)) scale = 1.0;
-        for (int i = 0; i < k; ++i) {
-            for (int j = 0; j < k; ++j) A(i, j) = B[order[first + i] * ldb + order[first + j]] / scale;
-            A(i, k) = -1.0;
-            A(i, k + 1) = 0.0;
-        }
-        for (int j = 0; j < k; ++j) A(k, j) = -1.0;
-        A(k, k) = 0.0;
-        A(k, k + 1) = -1.0;
-        int nn = k + 1;
-        double amax = 0.0;
-        for (int i = 0; i < nn; ++i)
-            for (int j = 0; j < nn; ++j) amax = fmax(amax, fabs(A(i, j)));
-        bool singular = false;
-        for (int c = 0; c < nn && !singular; ++c) {
-            int p = c;
-            for (int i = c + 1; i < nn; ++i)
-                if (fabs(A(i, c)) > fabs(A(p, c))) p = i;
-            if (!(fabs(A(p, c)) >= 1e-14 * amax)) {
-                singular = true;
-                break;
-            }
-            if (p != c)
-                for (int j = 0; j <= nn; ++j) {
-                    double t = A(c, j);
-                    A(c, j) = A(p, j);
-                    A(p, j) = t;
-                }
-            for (int i = c + 1; i < nn; ++i) {
-                double f = A(i, c) / A(c, c);
-                for (int j = c; j <= nn; ++j) A(i, j) -= f * A(c, j);
-            }
-        }
-        if (singular) {
-            ++first;
-            ++dropped;
-            continue;
-        }
-        for (int i = nn - 1; i >= 0; --i) {
-            double s = A(i, nn);
-            for (int j = i + 1; j < nn; ++j) s -= A(i, j) * x[j];
-            x[i] = s / A(i, i);
-        }
-        for (int i = 0; i < k; ++i) coef[order[first + i]] = x[i];
-        break;
-    }
-    return dropped;
-}
-
-// One workgroup: reduce the dot partials into row/column `newslot` of B,
-// then solve the bordered Pulay system over the slots listed in `order`
-// (oldest first) by Gaussian elimination with partial pivoting in FP64;
-// if a pivot is below 1e-14 * max|A| the oldest slot is dropped and the solve
-// repeated.  coef[slot] receives the coefficient (0 for unused slots);
-// scal[0] = max |step|, scal[1] = number of dropped slots.  A step that is
-// not finite sets coef[ldb] = 1 (the extrapolation then leaves the
-// amplitudes at their input values) and leaves B untouched; otherwise
-// coef[ldb] = 0.
-__global__ __launch_bounds__(256) void k_finish_diis(const double* __restrict__ part, int nblk, int m,
-                                                     const double* __restrict__ part_max, int nblk_max,
-                                                     double* __restrict__ B, int ldb, int newslot,
-                                                     DiisOrder ord, double* __restrict__ coef,
-                                                     double* __restrict__ scal) {
-    __shared__ double sh[kThreads];
-    __shared__ double row[kDiisMax];
-    __shared__ int order[kDiisMax];
-    __shared__ double wa[(kDiisMax + 1) * (kDiisMax + 2)], wx[kDiisMax + 1];
-    if (threadIdx.x < kDiisMax) order[threadIdx.x] = (int)threadIdx.x < m ? ord.v[threadIdx.x] : 0;
-    for (int j = 0; j < m; ++j) {
-        double v = 0.0;
-        for (int b = threadIdx.x; b < nblk; b += kThreads) v += part[b * kDiisMax + j];
-        double s = block_sum(v, sh);
-        if (threadIdx.x == 0) row[j] = s;
-    }
-    double mx = 0.0;
-    for (int b = threadIdx.x; b < nblk_max; b += kThreads) {
-        double a = part_max[b];
-        mx = (a > mx || a != a) ? a : mx;
-    }
-    mx = block_max(mx, sh);
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    scal[0] = mx;
-    if (!isfinite(mx)) {
-        for (int j = 0; j < ldb; ++j) coef[j] = 0.0;
-        coef[ldb] = 1.0;
-        scal[1] = 0.0;
-        return;
-    }
-    coef[ldb] = 0.0;
-    // row[j] pairs the new vector with the slot order[j]
-    for (int j = 0; j < m; ++j) {
-        B[newslot * ldb + order[j]] = row[j];
-        B[order[j] * ldb + newslot] = row[j];
-    }
-    int dropped = diis_solve<kDiisMax>(B, ldb, order, m, coef, wa, wx);
-    scal[1] = (double)dropped;
-}
-
-hipError_t launch_finish_diis(const double* part, int nblk, int m, const double* part_max, int nblk_max, double* B,
-                              int ldb, int newslot, const DiisOrder& order, double* coef, double* scal, hipStream_t st) {
-    if (m < 1 || m > kDiisMax) return hipErrorInvalidValue;
-    k_finish_diis<<<1, kThreads, 0, st>>>(part, nblk, m, part_max, nblk_max, B, ldb, newslot, order, coef, scal);
-    return hipGetLastError();
-}
-
 // *count += number of non-finite values among x[0..n) (the caller zeroes *count)
 __global__ __launch_bounds__(256) void k_count_nonfinite(const double* __restrict__ x, long long n,
                                                          unsigned long long* __restrict__ count) {
@@ -1661,352 +1415,6 @@ hipError_t launch_count_nonfinite(const double* x, long long n, unsigned long lo
     if (e != hipSuccess || n <= 0) return e;
     const long long blocks = std::min<long long>((n + kThreads - 1) / kThreads, 4096);
     k_count_nonfinite<<<(unsigned)blocks, kThreads, 0, st>>>(x, n, count);
-    return hipGetLastError();
-}
-
-// out = sum_j coef[j] xs[j]; coef[m] != 0 (a non-finite step) leaves out untouched
-__global__ __launch_bounds__(256) void k_lincomb(double2* __restrict__ out, PtrList xs, const double* __restrict__ coef,
-                                                 int m, long long n) {
-    long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n || coef[m] != 0.0) return;
-    double sr = 0.0, si = 0.0;
-    for (int j = 0; j < m; ++j) {
-        double c = coef[j];
-        if (c != 0.0) {
-            double2 x = xs.p[j][k];
-            sr += c * x.x;
-            si += c * x.y;
-        }
-    }
-    out[k] = make_double2(sr, si);
-}
-
-hipError_t launch_lincomb(double2* out, const double2* const* xs, const double* coef, int m, long long n,
-                          hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    if (m < 0 || m > kDiisMax) return hipErrorInvalidValue;
-    PtrList pl;
-    for (int j = 0; j < kDiisMax; ++j) pl.p[j] = j < m ? xs[j] : nullptr;
-    k_lincomb<<<(unsigned)((n + kThreads - 1) / kThreads), kThreads, 0, st>>>(out, pl, coef, m, n);
-    return hipGetLastError();
-}
-
-__global__ __launch_bounds__(256) void k_zdotu_part(const double2* __restrict__ x, const double2* __restrict__ y,
-                                                    long long n, double* part) {
-    __shared__ double sh[kThreads];
-    double sr = 0.0, si = 0.0;
-    for (long long k = (long long)blockIdx.x * kThreads + threadIdx.x; k < n; k += (long long)gridDim.x * kThreads) {
-        double2 a = x[k], b = y[k];
-        sr += a.x * b.x - a.y * b.y;
-        si += a.x * b.y + a.y * b.x;
-    }
-    double r = block_sum(sr, sh);
-    double i = block_sum(si, sh);
-    if (threadIdx.x == 0) {
-        part[2 * blockIdx.x] = r;
-        part[2 * blockIdx.x + 1] = i;
-    }
-}
-
-__global__ __launch_bounds__(256) void k_sum2(const double* __restrict__ part, int nblk, double* out) {
-    __shared__ double sh[kThreads];
-    double r = 0.0, i = 0.0;
-    for (int b = threadIdx.x; b < nblk; b += kThreads) {
-        r += part[2 * b];
-        i += part[2 * b + 1];
-    }
-    r = block_sum(r, sh);
-    i = block_sum(i, sh);
-    if (threadIdx.x == 0) {
-        out[0] = r;
-        out[1] = i;
-    }
-}
-
-hipError_t launch_zdotu(const double2* x, const double2* y, long long n, double* part, int nblk, double* out,
-                        hipStream_t st) {
-    k_zdotu_part<<<nblk, kThreads, 0, st>>>(x, y, n, part);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    k_sum2<<<1, kThreads, 0, st>>>(part, nblk, out);
-    return hipGetLastError();
-}
-
-
-// ---------------------------------------------------------------------------
-// batched Jacobi + DIIS update and energy: blockIdx.y (or x) = system; each
-// system keeps its own circular DIIS history on the device, so an iteration
-// needs no host decision and can be replayed as a graph.
-
-__global__ __launch_bounds__(256) void k_bjacobi(const double2* __restrict__ t1, const double2* __restrict__ t2,
-                                                 const double2* __restrict__ r1, const double2* __restrict__ r2,
-                                                 const double* __restrict__ D1, const double* __restrict__ D2,
-                                                 const BSeg* __restrict__ segs, const BState* __restrict__ state,
-                                                 double2* __restrict__ ht, double2* __restrict__ he,
-                                                 double* __restrict__ part_max, double shift) {
-    __shared__ double sh[kThreads];
-    const int s = blockIdx.y;
-    const BState stt = state[s];
-    if (!stt.active) {
-        if (threadIdx.x == 0) part_max[(long long)s * gridDim.x + blockIdx.x] = 0.0;
-        return;
-    }
-    const BSeg g = segs[s];
-    const long long n = g.n1 + g.n2;
-    const int slot = (stt.newest + 1) % stt.nd;
-    double2* hts = ht + g.hoff + (long long)slot * n;
-    double2* hes = he + g.hoff + (long long)slot * n;
-    double mx = 0.0;
-    for (long long k = (long long)blockIdx.x * kThreads + threadIdx.x; k < n; k += (long long)gridDim.x * kThreads) {
-        double2 rr, tt;
-        double d;
-        if (k < g.n1) {
-            rr = r1[g.off1 + k];
-            tt = t1[g.off1 + k];
-            d = D1[g.off1 + k];
-        } else {
-            rr = r2[g.off2 + k - g.n1];
-            tt = t2[g.off2 + k - g.n1];
-            d = D2[g.off2 + k - g.n1];
-        }
-        d -= shift;   // level shift: D < 0 for every amplitude, so |D| grows and the step is damped
-        const double2 st = make_double2(rr.x / d, rr.y / d);
-        hes[k] = st;
-        hts[k] = make_double2(tt.x + st.x, tt.y + st.y);
-        const double a = sqrt(st.x * st.x + st.y * st.y);
-        mx = (a > mx || a != a) ? a : mx;
-    }
-    const double b = block_max(mx, sh);
-    if (threadIdx.x == 0) part_max[(long long)s * gridDim.x + blockIdx.x] = b;
-}
-
-// live slots of system state `st` after adding the new vector: oldest first
-__device__ inline int bslots(const BState& st, int* order) {
-    const int nw = (st.newest + 1) % st.nd;
-    const int m = min(st.count + 1, st.nd);
-    for (int j = 0; j < m; ++j) order[j] = ((nw - (m - 1) + j) % st.nd + st.nd) % st.nd;
-    return m;
-}
-
-__global__ __launch_bounds__(256) void k_bdots(const BSeg* __restrict__ segs, const BState* __restrict__ state,
-                                               const double2* __restrict__ he, double* __restrict__ part) {
-    __shared__ double sh[kThreads];
-    const int s = blockIdx.y;
-    const BState stt = state[s];
-    if (!stt.active) return;
-    const BSeg g = segs[s];
-    const long long n = g.n1 + g.n2;
-    int order[8];
-    const int m = bslots(stt, order);
-    const double2* enew = he + g.hoff + (long long)order[m - 1] * n;
-    double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (long long k = (long long)blockIdx.x * kThreads + threadIdx.x; k < n; k += (long long)gridDim.x * kThreads) {
-        const double2 y = enew[k];
-        for (int j = 0; j < m; ++j) {
-            const double2 x = he[g.hoff + (long long)order[j] * n + k];
-            acc[j] += x.x * y.x + x.y * y.y;
-        }
-    }
-    for (int j = 0; j < m; ++j) {
-        const double b = block_sum(acc[j], sh);
-        if (threadIdx.x == 0) part[((long long)s * gridDim.x + blockIdx.x) * 8 + j] = b;
-    }
-}
-
-// one workgroup per system: finish the dots, update B, solve, advance the
-// circular history, apply the convergence test (max|step| < tol freezes the
-// system after this update; a non-finite step freezes it as failed)
-__global__ __launch_bounds__(256) void k_bfinish(BState* __restrict__ state, const double* __restrict__ part, int nblk,
-                                                 const double* __restrict__ part_max, double* __restrict__ Bm,
-                                                 double* __restrict__ coef, double* __restrict__ maxstep, double tol,
-                                                 int* __restrict__ active, int* __restrict__ upd) {
-    __shared__ double sh[kThreads];
-    __shared__ double row[8];
-    __shared__ double wa[9 * 10], wx[9];
-    const int s = blockIdx.x;
-    BState stt = state[s];
-    if (!stt.active) {
-        if (threadIdx.x == 0) {
-            state[s].upd = 0;
-            active[s] = 0;
-            upd[s] = 0;
-        }
-        return;
-    }
-    int order[8];
-    const int m = bslots(stt, order);
-    for (int j = 0; j < m; ++j) {
-        double v = 0.0;
-        for (int b = threadIdx.x; b < nblk; b += kThreads) v += part[((long long)s * nblk + b) * 8 + j];
-        const double r = block_sum(v, sh);
-        if (threadIdx.x == 0) row[j] = r;
-    }
-    double mx = 0.0;
-    for (int b = threadIdx.x; b < nblk; b += kThreads) {
-        const double a = part_max[(long long)s * nblk + b];
-        mx = (a > mx || a != a) ? a : mx;
-    }
-    mx = block_max(mx, sh);
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    double* B = Bm + (long long)s * 64;
-    const int nw = order[m - 1];
-    for (int j = 0; j < m; ++j) {
-        B[nw * 8 + order[j]] = row[j];
-        B[order[j] * 8 + nw] = row[j];
-    }
-    const int dropped = diis_solve<8>(B, 8, order, m, coef + (long long)s * 8, wa, wx);
-    stt.newest = nw;
-    stt.count = max(1, m - dropped);
-    stt.iters += 1;
-    stt.upd = 1;
-    if (!(mx == mx) || mx > 1.7976931348623157e308) {
-        stt.failed = 1;
-        stt.active = 0;
-        stt.upd = 0;
-    } else if (mx < tol) {
-        stt.active = 0;
-    }
-    state[s] = stt;
-    active[s] = stt.active;
-    upd[s] = stt.upd;
-    maxstep[s] = mx;
-}
-
-__global__ __launch_bounds__(256) void k_blincomb(double2* __restrict__ t1, double2* __restrict__ t2,
-                                                  const BSeg* __restrict__ segs, const BState* __restrict__ state,
-                                                  const double2* __restrict__ ht, const double* __restrict__ coef) {
-    const int s = blockIdx.y;
-    const BState stt = state[s];
-    if (!stt.upd) return;
-    const BSeg g = segs[s];
-    const long long n = g.n1 + g.n2;
-    double c[8];
-    for (int j = 0; j < 8; ++j) c[j] = j < stt.nd ? coef[s * 8 + j] : 0.0;
-    for (long long k = (long long)blockIdx.x * kThreads + threadIdx.x; k < n; k += (long long)gridDim.x * kThreads) {
-        double sr = 0.0, si = 0.0;
-        for (int j = 0; j < stt.nd; ++j)
-            if (c[j] != 0.0) {
-                const double2 x = ht[g.hoff + (long long)j * n + k];
-                sr += c[j] * x.x;
-                si += c[j] * x.y;
-            }
-        if (k < g.n1) t1[g.off1 + k] = make_double2(sr, si);
-        else t2[g.off2 + k - g.n1] = make_double2(sr, si);
-    }
-}
-
-__global__ __launch_bounds__(256) void k_benergy(const double2* __restrict__ x, const double2* __restrict__ y,
-                                                 const BSeg* __restrict__ segs, double* __restrict__ part) {
-    __shared__ double sh[kThreads];
-    const int s = blockIdx.y;
-    const BSeg g = segs[s];
-    double sr = 0.0, si = 0.0;
-    for (long long k = (long long)blockIdx.x * kThreads + threadIdx.x; k < g.n2; k += (long long)gridDim.x * kThreads) {
-        const double2 a = x[g.off2 + k], b = y[g.off2 + k];
-        sr += a.x * b.x - a.y * b.y;
-        si += a.x * b.y + a.y * b.x;
-    }
-    const double r = block_sum(sr, sh);
-    const double i = block_sum(si, sh);
-    if (threadIdx.x == 0) {
-        part[((long long)s * gridDim.x + blockIdx.x) * 2] = r;
-        part[((long long)s * gridDim.x + blockIdx.x) * 2 + 1] = i;
-    }
-}
-
-// per-system report row: E_re, E_im, max|step|, active, iterations, failed
-__global__ __launch_bounds__(256) void k_breport(const double* __restrict__ part, int nblk,
-                                                 const BState* __restrict__ state, const double* __restrict__ maxstep,
-                                                 double* __restrict__ out) {
-    __shared__ double sh[kThreads];
-    const int s = blockIdx.x;
-    double r = 0.0, i = 0.0;
-    for (int b = threadIdx.x; b < nblk; b += kThreads) {
-        r += part[((long long)s * nblk + b) * 2];
-        i += part[((long long)s * nblk + b) * 2 + 1];
-    }
-    r = block_sum(r, sh);
-    i = block_sum(i, sh);
-    if (threadIdx.x == 0) {
-        const BState st = state[s];
-        double* o = out + (long long)s * 6;
-        o[0] = r;
-        o[1] = i;
-        o[2] = maxstep[s];
-        o[3] = st.active;
-        o[4] = st.iters;
-        o[5] = st.failed;
-    }
-}
-
-hipError_t launch_batch_update(const double2* t1, const double2* t2, const double2* r1, const double2* r2,
-                               double2* t1o, double2* t2o, const double* D1, const double* D2, const BSeg* segs,
-                               BState* state, double2* ht, double2* he, double* part_max, double* part, double* Bm,
-                               double* coef, double* maxstep, double tol, double shift, int* active, int* upd,
-                               int nsys, int nblk, hipStream_t st) {
-    if (nsys <= 0) return hipSuccess;
-    dim3 grid(nblk, nsys);
-    k_bjacobi<<<grid, kThreads, 0, st>>>(t1, t2, r1, r2, D1, D2, segs, state, ht, he, part_max, shift);
-    k_bdots<<<grid, kThreads, 0, st>>>(segs, state, he, part);
-    k_bfinish<<<nsys, kThreads, 0, st>>>(state, part, nblk, part_max, Bm, coef, maxstep, tol, active, upd);
-    k_blincomb<<<grid, kThreads, 0, st>>>(t1o, t2o, segs, state, ht, coef);
-    return hipGetLastError();
-}
-
-hipError_t launch_batch_energy(const double2* oovv, const double2* tau, const BSeg* segs, const BState* state,
-                               const double* maxstep, double* part, double* out, int nsys, int nblk, hipStream_t st) {
-    if (nsys <= 0) return hipSuccess;
-    k_benergy<<<dim3(nblk, nsys), kThreads, 0, st>>>(oovv, tau, segs, part);
-    k_breport<<<nsys, kThreads, 0, st>>>(part, nblk, state, maxstep, out);
-    return hipGetLastError();
-}
-
-
-// per-system max |r / D| over the T1 and T2 segments
-__global__ __launch_bounds__(256) void k_bmaxnorm(const double2* __restrict__ r1, const double2* __restrict__ r2,
-                                                  const double* __restrict__ D1, const double* __restrict__ D2,
-                                                  const BSeg* __restrict__ segs, double* __restrict__ part) {
-    __shared__ double sh[kThreads];
-    const int s = blockIdx.y;
-    const BSeg g = segs[s];
-    const long long n = g.n1 + g.n2;
-    double mx = 0.0;
-    for (long long k = (long long)blockIdx.x * kThreads + threadIdx.x; k < n; k += (long long)gridDim.x * kThreads) {
-        double2 rr;
-        double d;
-        if (k < g.n1) {
-            rr = r1[g.off1 + k];
-            d = D1[g.off1 + k];
-        } else {
-            rr = r2[g.off2 + k - g.n1];
-            d = D2[g.off2 + k - g.n1];
-        }
-        const double a = sqrt(rr.x * rr.x + rr.y * rr.y) / fabs(d);
-        mx = (a > mx || a != a) ? a : mx;
-    }
-    const double b = block_max(mx, sh);
-    if (threadIdx.x == 0) part[(long long)s * gridDim.x + blockIdx.x] = b;
-}
-
-__global__ __launch_bounds__(256) void k_bmaxnorm_final(const double* __restrict__ part, int nblk,
-                                                        double* __restrict__ out) {
-    __shared__ double sh[kThreads];
-    const int s = blockIdx.x;
-    double mx = 0.0;
-    for (int b = threadIdx.x; b < nblk; b += kThreads) {
-        const double a = part[(long long)s * nblk + b];
-        mx = (a > mx || a != a) ? a : mx;
-    }
-    mx = block_max(mx, sh);
-    if (threadIdx.x == 0) out[s] = mx;
-}
-
-hipError_t launch_batch_maxnorm(const double2* r1, const double2* r2, const double* D1, const double* D2,
-                                const BSeg* segs, double* part, double* out, int nsys, int nblk, hipStream_t st) {
-    if (nsys <= 0) return hipSuccess;
-    k_bmaxnorm<<<dim3(nblk, nsys), kThreads, 0, st>>>(r1, r2, D1, D2, segs, part);
-    k_bmaxnorm_final<<<nsys, kThreads, 0, st>>>(part, nblk, out);
     return hipGetLastError();
 }
 

@@ -156,15 +156,6 @@ hipError_t launch_diag(double2* dst, const double* d, const double2* src, long l
 hipError_t launch_mul(double2* dst, const double* d, long long n, hipStream_t st,
                       SegBlocks sb = SegBlocks());   // dst *= d (real)
 
-// Jacobi: step = r/(D - shift); tn = t + step (written to hist_t), e = step (hist_e);
-// per-block max |step| into part_max[block].  dyn_S < 0: dynamic shifts
-// Delta = dyn_S (dyn_S / (min(D,0) + dyn_S))^dyn_n, step = (r - Delta t) / (D + Delta - shift).
-hipError_t launch_jacobi(const double2* t, const double2* r, const double* D, double2* hist_t, double2* hist_e,
-                         long long n, double* part_max, int nblk, hipStream_t st, double shift = 0.0,
-                         double dyn_S = 0.0, int dyn_n = 0);
-// sum_b part[b*stride + j] -> out[j]  (j < cols), and max over part_max
-hipError_t launch_dots(const double2* const* e, int m, const double2* enew, long long n, double* part, int nblk,
-                       hipStream_t st);
 // *count = number of non-finite doubles in x[0..n) (zeroes *count first; not
 // for code under graph capture: it records a memset)
 hipError_t launch_count_nonfinite(const double* x, long long n, unsigned long long* count, hipStream_t st);
@@ -173,20 +164,36 @@ hipError_t launch_count_nonfinite(const double* x, long long n, unsigned long lo
 // (order 4, idx = (i, j, a, b)); f = occupied then virtual one-particle energies
 hipError_t launch_dressed_denoms(const uint16_t* idx, int order, const double* f, int no, double floor, double* D,
                                  long long n, hipStream_t st);
-// coef holds ldb + 1 doubles: coef[ldb] = 1 marks a non-finite step.  The
-// live slots (oldest first) travel as a kernel argument, so that enqueueing
-// the update needs no copy from host memory.
+// Update of one system (kernels_update.hip): the step r/(D - shift) of T1 then
+// T2 (n1 + n2 elements) into history slot `slot` (ht: t + step, he: step; slots
+// of n1 + n2 elements), the bordered DIIS solve over the slots order[0..m)
+// (oldest first, the new one last; they travel as a kernel argument) on the
+// kDiisMax x kDiisMax matrix B, and the extrapolated amplitudes into t1, t2.
+// dyn_S < 0: dynamic shifts Delta = dyn_S (dyn_S / (min(D,0) + dyn_S))^dyn_n,
+// step = (r - Delta t) / (D + Delta - shift).  coef: kDiisMax + 1 doubles,
+// part: (kDiisMax + 1) * kReduceBlocks; out (pinned host): max |step|, number
+// of dropped slots.  A non-finite step leaves t1, t2 and B untouched.
+constexpr int kReduceBlocks = 1024;
 struct DiisOrder {
     int v[kDiisMax];
 };
-hipError_t launch_finish_diis(const double* part, int nblk, int m, const double* part_max, int nblk_max, double* B,
-                              int ldb, int newslot, const DiisOrder& order, double* coef, double* scal, hipStream_t st);
-// out = sum_{j<m} coef[j] xs[j], unless coef[m] != 0 (out is then left untouched)
-hipError_t launch_lincomb(double2* out, const double2* const* xs, const double* coef, int m, long long n,
-                          hipStream_t st);
-// complex dot sum_k x[k]*y[k] (no conjugation): per-block partials then final
-hipError_t launch_zdotu(const double2* x, const double2* y, long long n, double* part, int nblk, double* out,
-                        hipStream_t st);
+struct UpdateArgs {
+    void *t1, *t2;
+    const void *r1, *r2;
+    const double *D1, *D2;
+    void *ht, *he;
+    long long n1, n2;
+    int slot, m;
+    DiisOrder order;
+    double *part, *B, *coef, *out;
+    double shift, dyn_S;
+    int dyn_n;
+};
+hipError_t launch_update(const UpdateArgs& u, bool real, hipStream_t st);
+// block partials (re, im) of sum_k oovv[k] tau[k] with tau = t2 + the two-term
+// t1 x t1 reorder `maps`: part[2 * nblk] (pinned host)
+hipError_t launch_energy(const void* oovv, const void* t1, const void* t2, const GatherMaps& maps, long long n,
+                         double* part, int nblk, bool real, hipStream_t st);
 hipError_t launch_zero(double2* dst, long long n, hipStream_t st);
 
 int reduce_blocks(long long n);
@@ -209,17 +216,6 @@ hipError_t launch_dgather(double* dst, const double* src, const double* src2, Ga
 hipError_t launch_daxpby(double* dst, const double* src, long long n, double alpha, int beta, hipStream_t st);
 hipError_t launch_ddiag(double* dst, const double* d, const double* src, long long n, hipStream_t st);
 hipError_t launch_dmul(double* dst, const double* d, long long n, hipStream_t st);
-hipError_t launch_djacobi(const double* t, const double* r, const double* D, double* hist_t, double* hist_e,
-                          long long n, double* part_max, int nblk, hipStream_t st, double shift = 0.0,
-                          double dyn_S = 0.0, int dyn_n = 0);
-hipError_t launch_ddots(const double* const* e, int m, const double* enew, long long n, double* part, int nblk,
-                        hipStream_t st);
-// real form of launch_lincomb (same coef[m] convention)
-hipError_t launch_dlincomb(double* out, const double* const* xs, const double* coef, int m, long long n,
-                           hipStream_t st);
-// out[0] = sum x*y, out[1] = 0
-hipError_t launch_ddot(const double* x, const double* y, long long n, double* part, int nblk, double* out,
-                       hipStream_t st);
 
 // ---- batched update (many independent systems in concatenated vectors)
 // segment of system s: T1 part [off1, off1+n1), T2 part [off2, off2+n2);

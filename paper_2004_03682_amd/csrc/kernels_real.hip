@@ -475,129 +475,6 @@ __global__ __launch_bounds__(256) void k_dmul(double* __restrict__ dst, const do
     if (k < n) dst[k] *= d[k];
 }
 
-// ---------------------------------------------------------------------------
-// reductions (deterministic: fixed grid, per-block partials, one final block)
-
-__device__ __forceinline__ double dblock_sum(double v, double* sh) {
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    for (int s = kT / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-        __syncthreads();
-    }
-    double r = sh[0];
-    __syncthreads();
-    return r;
-}
-
-__device__ __forceinline__ double dblock_max(double v, double* sh) {
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    for (int s = kT / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) {
-            double a = sh[threadIdx.x], b = sh[threadIdx.x + s];
-            sh[threadIdx.x] = (a > b || a != a) ? a : b;
-        }
-        __syncthreads();
-    }
-    double r = sh[0];
-    __syncthreads();
-    return r;
-}
-
-__device__ __forceinline__ double ddyn_delta(double d, double S, int n) {
-    const double q = S / (fmin(d, 0.0) + S);
-    double p = q;
-    for (int i = 1; i < n; ++i) p *= q;
-    return S * p;
-}
-
-__global__ __launch_bounds__(256) void k_djacobi(const double* __restrict__ t, const double* __restrict__ r,
-                                                 const double* __restrict__ D, double* __restrict__ ht,
-                                                 double* __restrict__ he, long long n, double* part_max,
-                                                 double shift, double dS, int dn) {
-    __shared__ double sh[kT];
-    double mx = 0.0;
-    for (long long k = (long long)blockIdx.x * kT + threadIdx.x; k < n; k += (long long)gridDim.x * kT) {
-        double rr = r[k];
-        const double tt = t[k];
-        double d = D[k];
-        if (dS != 0.0) {
-            const double dl = ddyn_delta(d, dS, dn);
-            rr -= dl * tt;
-            d += dl;
-        }
-        d -= shift;
-        const double s = rr / d;
-        he[k] = s;
-        ht[k] = tt + s;
-        const double a = fabs(s);
-        mx = (a > mx || a != a) ? a : mx;
-    }
-    double b = dblock_max(mx, sh);
-    if (threadIdx.x == 0) part_max[blockIdx.x] = b;
-}
-
-struct DPtrList {
-    const double* p[kDiisMax];
-};
-
-__global__ __launch_bounds__(256) void k_ddots(DPtrList e, int m, const double* __restrict__ enew, long long n,
-                                               double* part) {
-    __shared__ double sh[kT];
-    double acc[kDiisMax];
-#pragma unroll
-    for (int j = 0; j < kDiisMax; ++j) acc[j] = 0.0;
-    for (long long k = (long long)blockIdx.x * kT + threadIdx.x; k < n; k += (long long)gridDim.x * kT) {
-        const double y = enew[k];
-#pragma unroll
-        for (int j = 0; j < kDiisMax; ++j)
-            if (j < m) acc[j] += e.p[j][k] * y;
-    }
-#pragma unroll
-    for (int j = 0; j < kDiisMax; ++j)
-        if (j < m) {
-            double b = dblock_sum(acc[j], sh);
-            if (threadIdx.x == 0) part[blockIdx.x * kDiisMax + j] = b;
-        }
-}
-
-// out = sum_j coef[j] xs[j]; coef[m] != 0 (a non-finite step) leaves out untouched
-__global__ __launch_bounds__(256) void k_dlincomb(double* __restrict__ out, DPtrList xs, const double* __restrict__ coef,
-                                                  int m, long long n) {
-    const long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n || coef[m] != 0.0) return;
-    double s = 0.0;
-    for (int j = 0; j < m; ++j) {
-        const double c = coef[j];
-        if (c != 0.0) s += c * xs.p[j][k];
-    }
-    out[k] = s;
-}
-
-__global__ __launch_bounds__(256) void k_ddot_part(const double* __restrict__ x, const double* __restrict__ y,
-                                                   long long n, double* part) {
-    __shared__ double sh[kT];
-    double s = 0.0;
-    for (long long k = (long long)blockIdx.x * kT + threadIdx.x; k < n; k += (long long)gridDim.x * kT) s += x[k] * y[k];
-    double r = dblock_sum(s, sh);
-    if (threadIdx.x == 0) {
-        part[2 * blockIdx.x] = r;
-        part[2 * blockIdx.x + 1] = 0.0;
-    }
-}
-
-__global__ __launch_bounds__(256) void k_dsum(const double* __restrict__ part, int nblk, double* out) {
-    __shared__ double sh[kT];
-    double r = 0.0;
-    for (int b = threadIdx.x; b < nblk; b += kT) r += part[2 * b];
-    r = dblock_sum(r, sh);
-    if (threadIdx.x == 0) {
-        out[0] = r;
-        out[1] = 0.0;
-    }
-}
-
 inline unsigned grid_of(long long n) { return (unsigned)((n + kT - 1) / kT); }
 
 }  // namespace
@@ -683,42 +560,6 @@ hipError_t launch_ddiag(double* dst, const double* d, const double* src, long lo
 hipError_t launch_dmul(double* dst, const double* d, long long n, hipStream_t st) {
     if (n <= 0) return hipSuccess;
     k_dmul<<<grid_of(n), kT, 0, st>>>(dst, d, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_djacobi(const double* t, const double* r, const double* D, double* hist_t, double* hist_e,
-                          long long n, double* part_max, int nblk, hipStream_t st, double shift, double dyn_S,
-                          int dyn_n) {
-    if (dyn_S != 0.0 && !(dyn_S < 0.0 && dyn_n >= 1)) return hipErrorInvalidValue;
-    k_djacobi<<<nblk, kT, 0, st>>>(t, r, D, hist_t, hist_e, n, part_max, shift, dyn_S, dyn_n);
-    return hipGetLastError();
-}
-
-hipError_t launch_ddots(const double* const* e, int m, const double* enew, long long n, double* part, int nblk,
-                        hipStream_t st) {
-    if (m < 0 || m > kDiisMax) return hipErrorInvalidValue;
-    DPtrList pl;
-    for (int j = 0; j < kDiisMax; ++j) pl.p[j] = j < m ? e[j] : nullptr;
-    k_ddots<<<nblk, kT, 0, st>>>(pl, m, enew, n, part);
-    return hipGetLastError();
-}
-
-hipError_t launch_dlincomb(double* out, const double* const* xs, const double* coef, int m, long long n,
-                           hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    if (m < 0 || m > kDiisMax) return hipErrorInvalidValue;
-    DPtrList pl;
-    for (int j = 0; j < kDiisMax; ++j) pl.p[j] = j < m ? xs[j] : nullptr;
-    k_dlincomb<<<grid_of(n), kT, 0, st>>>(out, pl, coef, m, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_ddot(const double* x, const double* y, long long n, double* part, int nblk, double* out,
-                       hipStream_t st) {
-    k_ddot_part<<<nblk, kT, 0, st>>>(x, y, n, part);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    k_dsum<<<1, kT, 0, st>>>(part, nblk, out);
     return hipGetLastError();
 }
 

@@ -228,12 +228,8 @@ struct fscc_ctx {
     double* d_fov = nullptr;                          // f_p of the occupied, then the virtual positions
     Diis diis[3];
     double* part = nullptr;
-    double* part_max = nullptr;
     double* coef = nullptr;
-    double* scal = nullptr;
-    double* hscal = nullptr;   // pinned host
-    double* epart = nullptr;
-    double* eout = nullptr;
+    double* hscal = nullptr;   // pinned host: update results [0..1], energy block partials from [8]
     double2* rs_tmp = nullptr; // residual scratch for fscc_heff
     bool prof = false;
     int prof_sel = -1;   // with prof: time only this operation (-1: all)
@@ -341,7 +337,7 @@ struct fscc_ctx {
         }
         for (void* p : seg_mem)
             if (p) (void)hipFree(p);
-        void* ps[] = {part, part_max, coef, scal, epart, eout, rs_tmp, d_idx1, d_idx2, d_fov};
+        void* ps[] = {part, coef, rs_tmp, d_idx1, d_idx2, d_fov};
         for (void* p : ps)
             if (p) (void)hipFree(p);
         if (hscal) (void)hipHostFree(hscal);

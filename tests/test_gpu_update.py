@@ -1,0 +1,86 @@
+"""Amplitude update kernels (Jacobi step, DIIS dots, bordered solve, extrapolation, energy) against numpy.
+
+The reference forms t + r/D, B_kl = Re <e_k, e_l> and solves the bordered Pulay system with numpy.  The random
+steps are independent, so B (scaled to unit diagonal) has a condition number of order one to a hundred and the
+coefficients agree to ~1e-13; 1e-10 of the largest amplitude is asked."""
+import numpy as np
+import pytest
+
+import fsgen
+
+pytestmark = pytest.mark.gpu
+
+
+def dev(x):
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return torch.from_numpy(np.ascontiguousarray(x)).to("cuda")
+
+
+def _rand(rng, n, real):
+    x = rng.normal(size=n)
+    return x if real else x + 1j * rng.normal(size=n)
+
+
+def _pulay(es):
+    m = len(es)
+    B = np.array([[np.vdot(a, b).real for b in es] for a in es])
+    A = -np.ones((m + 1, m + 1))
+    A[:m, :m] = B / np.diag(B).max()
+    A[m, m] = 0.0
+    rhs = np.zeros(m + 1)
+    rhs[m] = -1.0
+    return np.linalg.solve(A, rhs)[:m]
+
+
+# T1 and T2 lengths around one block of 256, and above the 1024-block grid of the reductions
+@pytest.mark.parametrize("nocc,nvirt,nirrep", [(2, 3, 1), (3, 5, 2), (16, 16, 1), (17, 30, 3), (14, 86, 1)])
+@pytest.mark.parametrize("real", [False, True])
+@pytest.mark.parametrize("depth", [0, 1, 2, 7, 16])
+def test_update_matches_numpy(nocc, nvirt, nirrep, real, depth):
+    import paper_2004_03682_amd as F
+    s = fsgen.make_system(nocc, nvirt, nirrep, 0.05, 77)
+    ctx = F.Context.from_system(s, precision="real_fp64" if real else "fp64")
+    ctx.diis_reset(depth)
+    D = np.concatenate([x.cpu().numpy() for x in ctx.denominators()])
+    n1 = ctx.n1
+    rng = np.random.default_rng(nocc + depth)
+    hist = []
+    for it in range(max(2, depth + 3)):
+        t, r = _rand(rng, D.size, real), 1e-3 * _rand(rng, D.size, real)
+        t1, t2 = dev(t[:n1]), dev(t[n1:])
+        dmax = ctx.update_amplitudes(t1, t2, dev(r[:n1]), dev(r[n1:]))
+        e = r / D
+        assert abs(dmax - np.abs(e).max()) <= 1e-12 * dmax
+        hist = (hist + [(t + e, e)])[-max(1, depth):]
+        if depth > 1:
+            # (vectors of fewer components than the depth are linearly dependent: see the next test)
+            if D.size * (1 if real else 2) <= depth + 1:
+                break
+            c = _pulay([x[1] for x in hist]) if len(hist) > 1 else [1.0]
+            ref = sum(a * x[0] for a, x in zip(c, hist))
+        else:
+            ref = t + e
+        got = np.concatenate([t1.cpu().numpy(), t2.cpu().numpy()])
+        assert np.abs(got - ref).max() <= 1e-10 * max(1.0, np.abs(ref).max()), it
+    ctx.destroy()
+
+
+@pytest.mark.parametrize("real", [False, True])
+@pytest.mark.parametrize("depth", [2, 8, 16])
+def test_dependent_steps_drop_to_the_newest_vector(real, depth):
+    """Equal steps make every bordered system singular: the oldest vectors are dropped until the newest is left."""
+    import paper_2004_03682_amd as F
+    s = fsgen.make_system(5, 9, 2, 0.05, 78)
+    ctx = F.Context.from_system(s, precision="real_fp64" if real else "fp64")
+    ctx.diis_reset(depth)
+    D = np.concatenate([x.cpu().numpy() for x in ctx.denominators()])
+    rng = np.random.default_rng(5)
+    r = 1e-3 * _rand(rng, D.size, real)
+    for it in range(depth + 2):
+        t = _rand(rng, D.size, real)
+        t1, t2 = dev(t[:ctx.n1]), dev(t[ctx.n1:])
+        ctx.update_amplitudes(t1, t2, dev(r[:ctx.n1]), dev(r[ctx.n1:]))
+        got = np.concatenate([t1.cpu().numpy(), t2.cpu().numpy()])
+        assert np.abs(got - (t + r / D)).max() <= 1e-14 * np.abs(t).max(), it
+    ctx.destroy()
