@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libfscc.so")
 SOURCES = ["fscc_api.hip", "batch_api.hip", "noalloc_api.hip", "kernels.hip", "kernels_real.hip", "kernels_split.hip",
-           "kernels_dl.hip", "kernels_update.hip", "mlp.hip", "probe.hip", "plan_ccsd.cpp", "host_linalg.cpp"]
+           "kernels_dl.hip", "kernels_update.hip", "kernels_fused.hip", "mlp.hip", "probe.hip", "plan_ccsd.cpp", "host_linalg.cpp"]
 # per-source extra flags: the throughput probe's accumulators stay in VGPRs
 # (no accumulator copies around its loop)
 EXTRA = {"probe.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}

@@ -1,0 +1,27 @@
+// elem_math.hpp -- the element arithmetic that the reorder and elementwise
+// kernels share.  The fused multiply-adds are written out, so that every
+// traversal and the fused launches give the same bits (left to the compiler,
+// two kernels contract the same expression differently).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+namespace fscc {
+
+__device__ __forceinline__ double2 elem_mul(double2 x, double2 y) {
+    return make_double2(__builtin_fma(x.x, y.x, -(x.y * y.y)), __builtin_fma(x.x, y.y, x.y * y.x));
+}
+__device__ __forceinline__ double elem_mul(double x, double y) { return x * y; }
+
+__device__ __forceinline__ double2 elem_scale(double ar, double ai, double2 s) {
+    return make_double2(__builtin_fma(ar, s.x, -(ai * s.y)), __builtin_fma(ar, s.y, ai * s.x));
+}
+__device__ __forceinline__ double elem_scale(double ar, double, double s) { return ar * s; }
+
+// o - d x
+__device__ __forceinline__ double2 elem_sub(double2 o, double d, double2 x) {
+    return make_double2(__builtin_fma(-d, x.x, o.x), __builtin_fma(-d, x.y, o.y));
+}
+__device__ __forceinline__ double elem_sub(double o, double d, double x) { return __builtin_fma(-d, x, o); }
+
+}  // namespace fscc

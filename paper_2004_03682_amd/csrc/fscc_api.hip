@@ -226,6 +226,7 @@ void apply_precision(fscc_ctx* c, int prec) {
                 g.mx = plan_mixed(c, ops[k], prec, pick_mcfg(ops[k]));
             }
         }
+    if (c->prec != prec) ++c->sched_gen;
     c->prec = prec;
 }
 
@@ -247,6 +248,7 @@ double op_bytes(const Plan& P, const Op& o, const std::vector<int64_t>& nnz, siz
         case OP_AXPBY: return e * (double)o.n * (2.0 + o.beta);
         case OP_DIAG: return e * (double)o.n * 3.0 + 8.0 * (double)o.n;
         case OP_MUL: return e * (double)o.n * 2.0 + 8.0 * (double)o.n;
+        case OP_REDUCE: return 0.0;
         case OP_GATHER: {
             int64_t written = o.n;
             if (o.beta) {
@@ -530,7 +532,10 @@ void ctx_allocate(fscc_ctx* c, bool diis) {
     setup_list(c, c->L02, P.ops02);
     c->L01.base = (int)P.ops.size();
     c->L02.base = (int)(P.ops.size() + P.ops01.size());
-    if (diis) setup_diis(c, c->diis[0], c->n1(), c->n2(), P.b_D1, P.b_D2);
+    if (diis) {   // a single system (a batch's plan runs every operation on its own kernel)
+        setup_diis(c, c->diis[0], c->n1(), c->n2(), P.b_D1, P.b_D2);
+        for (OpList* L : {&c->L00, &c->L01p, &c->L01, &c->L02p, &c->L02}) c->prepare_schedule(*L);
+    }
     if (P.has01) {
         setup_diis(c, c->diis[1], P.L_S1.total, P.L_S2.total, P.b_D1x, P.b_D2x);
         int64_t ntmp = std::max<int64_t>(P.L_S1.total + P.L_S2.total, P.has02 ? P.L_S02.total : 0);
@@ -1915,6 +1920,7 @@ fscc_status fscc_vvvv_out_of_core(fscc_ctx* ctx, size_t staging_bytes) {
             void* d = ctx->dalloc(bytes);
             hip_check(hipMemcpy(d, ctx->sp.host, bytes, hipMemcpyHostToDevice), "operand to device");
             ctx->dbuf[b] = d;
+            ++ctx->sched_gen;
             ctx->free_stream();
             return FSCC_OK;
         }
@@ -1966,6 +1972,10 @@ fscc_status fscc_gather_order(fscc_ctx* ctx, int tiled) {
                 o.use_rtiles = tiled == 2 && o.d_rtiles != nullptr;
                 o.use_gtiles = !o.use_rtiles && tiled >= 1 && o.d_gtiles != nullptr;
             }
+    if (ctx->gather_forced != (tiled != 0)) {
+        ctx->gather_forced = tiled != 0;
+        ++ctx->sched_gen;
+    }
     return FSCC_OK;
 }
 

@@ -13,6 +13,7 @@
 
 #include <algorithm>
 
+#include "elem_math.hpp"
 #include "kernels.hpp"
 
 namespace fscc {
@@ -1097,9 +1098,7 @@ __device__ __forceinline__ void gather_elem(double2* __restrict__ dst, const dou
             const uint32_t mb = maps.b[t][k];
             any = any || (ma != 0xFFFFFFFFu && mb != 0xFFFFFFFFu);
             double2 y = map_load(src2, mb);
-            double xr = x.x * y.x - x.y * y.y, xi = x.x * y.y + x.y * y.x;
-            x.x = xr;
-            x.y = xi;
+            x = elem_mul(x, y);
         }
         sr += x.x;
         si += x.y;
@@ -1107,7 +1106,7 @@ __device__ __forceinline__ void gather_elem(double2* __restrict__ dst, const dou
     // an accumulating gather leaves an element whose terms are all structural
     // zeros as it is (no read, no write)
     if (beta && !any) return;
-    double2 out = make_double2(ar * sr - ai * si, ar * si + ai * sr);
+    double2 out = elem_scale(ar, ai, make_double2(sr, si));
     if (beta) {
         double2 o = dst[k];
         out.x += o.x;
@@ -1256,7 +1255,7 @@ __global__ __launch_bounds__(64) void k_reorder(double2* __restrict__ dst, const
             si += y.y;
         }
         double2* d = dst + t.k0 + (long long)r * t.ld + c;
-        double2 out = make_double2(ar * sr - ai * si, ar * si + ai * sr);
+        double2 out = elem_scale(ar, ai, make_double2(sr, si));
         if (beta) {
             const double2 o = *d;
             out.x += o.x;
@@ -1309,7 +1308,7 @@ __global__ __launch_bounds__(256) void k_axpby(double2* __restrict__ dst, const 
     if (!elem_index(sb, n, &k)) return;
     double2 x = src[k];
     if (conj) x.y = -x.y;
-    double2 out = make_double2(ar * x.x - ai * x.y, ar * x.y + ai * x.x);
+    double2 out = elem_scale(ar, ai, x);
     if (beta) {
         double2 o = dst[k];
         out.x += o.x;
@@ -1329,11 +1328,7 @@ __global__ __launch_bounds__(256) void k_diag(double2* __restrict__ dst, const d
                                               const double2* __restrict__ src, long long n, SegBlocks sb) {
     long long k;
     if (!elem_index(sb, n, &k)) return;
-    double2 o = dst[k], x = src[k];
-    double dd = d[k];
-    o.x -= dd * x.x;
-    o.y -= dd * x.y;
-    dst[k] = o;
+    dst[k] = elem_sub(dst[k], d[k], src[k]);
 }
 
 hipError_t launch_diag(double2* dst, const double* d, const double2* src, long long n, hipStream_t st, SegBlocks sb) {

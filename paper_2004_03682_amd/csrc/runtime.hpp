@@ -18,6 +18,7 @@
 #include "diverge.hpp"
 #include "kernels.hpp"
 #include "plan.hpp"
+#include "schedule.hpp"
 
 namespace fscc {
 namespace rt {
@@ -99,6 +100,31 @@ struct StreamPlan {
     std::vector<std::vector<StreamChunk>> ch00, ch01, ch02;
 };
 
+// A schedule with its device tables: one fused launch per fused step
+// (items[first, first + count)), and the two-stream form (fscc_ctx::streams ==
+// 2): steps bound by the matrix cores run on the context's stream, the others
+// (fused steps, reorders, elementwise and memory-bound GEMMs) on a second
+// stream, so that the two kinds overlap where the operations' buffers allow.
+// on2[k]: step k runs on the second stream; wait[k]: the latest step of the
+// other stream that k depends on (-1: none); rec[k]: an event is recorded
+// after k for such a wait.
+struct Schedule {
+    long long gen = -1;       // fscc_ctx::sched_gen it was built for
+    std::vector<ScheduleStep> steps;
+    std::vector<Op> ops;      // the entries the steps refer to (plain: empty, the list's own)
+    std::vector<int> orig;
+    std::vector<int> item0, nitems;
+    FItem* items = nullptr;   // in mem
+    FOp* fops = nullptr;
+    void* mem = nullptr;      // items, operations, problem and tile tables
+    void* work = nullptr;     // partial tiles of the GEMMs split over workgroups
+    std::vector<char> in_fused;   // per operation
+    std::vector<char> on2, rec;
+    std::vector<int> wait;
+    std::vector<hipEvent_t> xev;
+    hipEvent_t fork = nullptr, join = nullptr;
+};
+
 struct OpList {
     std::vector<Op>* ops = nullptr;
     std::vector<GemmDev> g;
@@ -107,86 +133,33 @@ struct OpList {
     std::vector<double> ms;
     std::vector<int> calls;
     int base = 0;             // number of the first operation (fscc_op_info numbering)
-    // Two-stream schedule (fscc_ctx::streams == 2): operations that are bound
-    // by the matrix cores run on the context's stream, the others (reorders,
-    // elementwise and memory-bound GEMMs) on a second stream, so that the two
-    // kinds overlap where the operations' buffers allow.  on2[k]: operation k
-    // runs on the second stream; wait[k]: the latest operation of the other
-    // stream that k depends on (-1: none); rec[k]: an event is recorded after
-    // k for such a wait.
-    std::vector<char> on2, rec;
-    std::vector<int> wait;
-    std::vector<hipEvent_t> xev;
-    hipEvent_t fork = nullptr, join = nullptr;
+    Schedule fused, plain;    // with small operations fused; every operation on its own
 };
 
-// Dependencies of an operation list through its buffers: operation k reads
-// src, src2, every term source and, when it accumulates (beta = 1, diagonal
-// and multiply forms), dst; it writes dst.  k depends on the last writer of
-// every buffer it reads or writes (read after write, write after write) and
-// on every reader of dst since that writer (write after read).  Buffers are
-// separate allocations, so distinct ids never overlap.
-inline std::vector<std::vector<int>> op_dependencies(const std::vector<Op>& ops) {
-    std::vector<std::vector<int>> deps(ops.size());
-    std::vector<int> last_w;
-    std::vector<std::vector<int>> readers;
-    auto grow = [&](int b) {
-        if (b >= (int)last_w.size()) {
-            last_w.resize(b + 1, -1);
-            readers.resize(b + 1);
-        }
-    };
-    for (size_t k = 0; k < ops.size(); ++k) {
-        const Op& o = ops[k];
-        std::vector<int> rd;
-        for (int b : {o.src, o.src2})
-            if (b >= 0) rd.push_back(b);
-        for (int b : o.srcT)
-            if (b >= 0) rd.push_back(b);
-        if (o.beta || o.kind == OP_DIAG || o.kind == OP_MUL) rd.push_back(o.dst);
-        std::vector<int>& d = deps[k];
-        for (int b : rd) {
-            grow(b);
-            if (last_w[b] >= 0) d.push_back(last_w[b]);
-        }
-        if (o.dst >= 0) {
-            grow(o.dst);
-            if (last_w[o.dst] >= 0) d.push_back(last_w[o.dst]);
-            for (int r : readers[o.dst]) d.push_back(r);
-        }
-        std::sort(d.begin(), d.end());
-        d.erase(std::unique(d.begin(), d.end()), d.end());
-        d.erase(std::remove(d.begin(), d.end(), (int)k), d.end());
-        for (int b : rd) readers[b].push_back((int)k);
-        if (o.dst >= 0) {
-            last_w[o.dst] = (int)k;
-            readers[o.dst].clear();
-        }
-    }
-    return deps;
-}
-
-// The two-stream schedule of a list (see OpList): GEMMs with more than
-// 8 flops per algorithmic byte on the first stream, everything else on the
-// second.
-inline void build_two_stream(OpList& L) {
-    const std::vector<Op>& ops = *L.ops;
-    const size_t n = ops.size();
-    L.on2.assign(n, 0);
-    L.rec.assign(n, 0);
-    L.wait.assign(n, -1);
+// The two-stream form of a schedule: GEMMs with more than 8 flops per
+// algorithmic byte on the first stream, everything else on the second.
+inline void build_two_stream(Schedule& S, const std::vector<Op>& list) {
+    const std::vector<Op>& ops = S.ops.empty() ? list : S.ops;
+    const size_t n = S.steps.size();
+    S.on2.assign(n, 0);
+    S.rec.assign(n, 0);
+    S.wait.assign(n, -1);
+    std::vector<int> step_of(ops.size(), 0);
     for (size_t k = 0; k < n; ++k) {
-        const Op& o = ops[k];
-        L.on2[k] = !(o.kind == OP_GEMM && o.flops > 8.0 * std::max(o.bytes, 1.0));
+        for (const auto& c : S.steps[k].chains)
+            for (int j : c) step_of[j] = (int)k;
+        const int j = S.steps[k].chains[0][0];
+        const Op& o = list[S.ops.empty() ? j : S.orig[j]];
+        S.on2[k] = S.steps[k].fused || !(o.kind == OP_GEMM && o.flops > 8.0 * std::max(o.bytes, 1.0));
     }
     const std::vector<std::vector<int>> deps = op_dependencies(ops);
-    for (size_t k = 0; k < n; ++k) {
-        int w = -1;
-        for (int j : deps[k])
-            if (L.on2[j] != L.on2[k]) w = std::max(w, j);
-        L.wait[k] = w;
-        if (w >= 0) L.rec[w] = 1;
-    }
+    for (size_t j = 0; j < ops.size(); ++j)
+        for (int d : deps[j]) {
+            const int k = step_of[j], q = step_of[d];
+            if (S.on2[k] != S.on2[q]) S.wait[k] = std::max(S.wait[k], q);
+        }
+    for (size_t k = 0; k < n; ++k)
+        if (S.wait[k] >= 0) S.rec[S.wait[k]] = 1;
 }
 
 // DIIS state of one sector
@@ -237,6 +210,10 @@ struct fscc_ctx {
     // created on first use, with the default priority
     int streams = 1;
     hipStream_t st2 = nullptr;
+    // schedules are rebuilt when this changes (precision, reorder traversal,
+    // a buffer that moved)
+    long long sched_gen = 0;
+    bool gather_forced = false;   // fscc_gather_order chose a traversal: reorders keep their own kernels
     // real arithmetic (real double groups): every amplitude, integral and
     // intermediate buffer holds doubles instead of complex doubles
     bool real = false;
@@ -296,7 +273,19 @@ struct fscc_ctx {
         sp = StreamPlan();
     }
 
+    static void free_schedule(Schedule& S) {
+        if (S.mem) (void)hipFree(S.mem);
+        if (S.work) (void)hipFree(S.work);
+        for (auto& e : S.xev)
+            if (e) (void)hipEventDestroy(e);
+        if (S.fork) (void)hipEventDestroy(S.fork);
+        if (S.join) (void)hipEventDestroy(S.join);
+        S = Schedule();
+    }
+
     static void free_list(OpList& L) {
+        free_schedule(L.fused);
+        free_schedule(L.plain);
         if (L.ops)
             for (auto& o : *L.ops)
                 if (o.d_gtiles) {
@@ -312,10 +301,6 @@ struct fscc_ctx {
         }
         for (auto& e : L.ev)
             if (e) (void)hipEventDestroy(e);
-        for (auto& e : L.xev)
-            if (e) (void)hipEventDestroy(e);
-        if (L.fork) (void)hipEventDestroy(L.fork);
-        if (L.join) (void)hipEventDestroy(L.join);
     }
 
     ~fscc_ctx() {
@@ -563,8 +548,177 @@ struct fscc_ctx {
         }
     }
 
-    // timed: HIP events around every operation (or only operation prof_sel),
-    // read back lazily, so timing adds no synchronisation to the stream
+    FRef fref(int buf) const {
+        FRef r;
+        if (buf < 0) return r;
+        if (caller_buffer(plan.bufs[buf].kind)) r.io = io_number(plan.bufs[buf].kind);
+        else r.p = dbuf[buf];
+        return r;
+    }
+
+    static int io_number(BufKind k) {
+        switch (k) {
+            case BUF_IN_T1: return 0;
+            case BUF_IN_T2: return 1;
+            case BUF_OUT_R1: return 2;
+            case BUF_OUT_R2: return 3;
+            case BUF_IN_S1: return 4;
+            case BUF_IN_S2: return 5;
+            case BUF_OUT_RS1: return 6;
+            case BUF_OUT_RS2: return 7;
+            case BUF_IN_P2: return 8;
+            default: return 9;   // BUF_OUT_RP2
+        }
+    }
+
+    // The schedule of a list and its device tables (built once, again when
+    // sched_gen changes).
+    void prepare_schedule(OpList& L) {
+        Schedule& S = L.fused;
+        if (S.gen == sched_gen) return;
+        free_schedule(S);
+        const std::vector<Op>& ops = *L.ops;
+        std::vector<char> alone(ops.size(), 0);
+        for (size_t k = 0; k < ops.size(); ++k) {
+            const Op& o = ops[k];
+            // a split-precision GEMM and a reorder with a forced traversal have kernels of their own
+            if (o.kind == OP_GEMM && prec != FSCC_FP64 && L.g[k].mx && L.g[k].mx->prec == prec) alone[k] = 1;
+            if (o.kind == OP_GATHER && gather_forced) alone[k] = 1;
+        }
+        ExpandedOps x = expand_ops(ops, alone, real, (int)plan.bufs.size());
+        S.steps = build_schedule(x);
+        S.in_fused.assign(ops.size(), 0);
+        std::vector<FOp> fops;
+        std::vector<FItem> items;
+        std::vector<ZProb> probs;
+        std::vector<ZTile> tiles;
+        // tables of a GEMM, shared by its partial products and their sum: offsets until uploaded
+        struct Tab {
+            long long probs = -1, tiles = 0, work = 0;
+        };
+        std::vector<Tab> tab(ops.size());
+        long long work = 0;
+        for (const ScheduleStep& st : S.steps) {
+            S.item0.push_back((int)items.size());
+            // longest items first: GEMMs by K per wave, then sums and elementwise chains
+            std::vector<std::pair<int, FItem>> todo;
+            // two elements per thread where one would take more than the 512 workgroups resident at once
+            int64_t elements = 0;
+            for (const auto& c : st.chains) elements += x.ops[c[0]].n;
+            const int elems = elements > 512 * kFusedThreads ? 2 : 1;
+            if (st.fused)
+                for (const auto& c : st.chains)
+                    for (size_t q = 0; q < c.size(); ++q) {
+                        const Op& xo = x.ops[c[q]];
+                        const int j = x.orig[c[q]], at = (int)fops.size();
+                        const Op& o = ops[j];
+                        S.in_fused[j] = 1;
+                        FOp f;
+                        f.kind = xo.kind == OP_GEMM     ? FK_GEMM
+                                 : xo.kind == OP_REDUCE ? FK_REDUCE
+                                 : xo.kind == OP_AXPBY  ? FK_AXPBY
+                                 : xo.kind == OP_DIAG   ? FK_DIAG
+                                 : xo.kind == OP_MUL    ? FK_MUL
+                                                        : FK_GATHER;
+                        f.beta = o.beta;
+                        f.conj = o.conj;
+                        f.more = q + 1 < c.size();
+                        f.elems = elems;
+                        f.ar = o.alpha.real();
+                        f.ai = o.alpha.imag();
+                        f.dst = fref(o.dst);
+                        f.src = fref(o.src);
+                        f.src2 = fref(o.src2);
+                        f.n = o.n;
+                        f.nt = (int)o.mapsA.size();
+                        for (int t = 0; t < 4; ++t) {
+                            f.a[t] = t < (int)o.mapsA.size() ? dmap[o.mapsA[t]] : nullptr;
+                            f.b[t] = t < (int)o.mapsB.size() ? dmap[o.mapsB[t]] : nullptr;
+                            f.srct[t] = t < (int)o.srcT.size() ? fref(o.srcT[t]) : f.src;
+                        }
+                        if (o.kind == OP_GEMM) {
+                            const FusedSplit fs = fused_split(o);
+                            f.kw = fs.kw;
+                            f.split = fs.split;
+                            f.ntiles = fs.tiles;
+                            f.tA = o.tA;
+                            f.tB = o.tB;
+                            f.cA = o.cA;
+                            f.cB = o.cB;
+                            Tab& T = tab[j];
+                            int K = 0;
+                            for (const GemmProblem& p : o.probs) K = std::max(K, p.K);
+                            if (T.probs < 0) {
+                                T.probs = (long long)probs.size();
+                                T.tiles = (long long)tiles.size();
+                                for (const GemmProblem& p : o.probs) {
+                                    for (int m = 0; m < p.M; m += 16)
+                                        for (int n = 0; n < p.N; n += 16)
+                                            tiles.push_back(ZTile{(int)((long long)probs.size() - T.probs), m, n, 0});
+                                    probs.push_back(ZProb{p.a_off, p.b_off, p.c_off, p.M, p.N, p.K, p.lda, p.ldb, p.ldc});
+                                }
+                                T.work = work;
+                                if (fs.split > 1) work += (long long)fs.tiles * fs.split * 256;
+                            }
+                            // element offsets, made addresses below
+                            f.probs = (const ZProb*)nullptr + T.probs;
+                            f.tiles = (const ZTile*)nullptr + T.tiles;
+                            f.work = (void*)(uintptr_t)(T.work * esz());
+                            if (f.kind == FK_GEMM)
+                                for (int t = 0; t < fs.tiles * fs.split; t += 16 / fs.kw)
+                                    todo.push_back({1 + K / (fs.kw * fs.split), FItem{at, t}});
+                            else
+                                for (int t = 0; t < fs.tiles; t += 4) todo.push_back({0, FItem{at, t}});
+                        } else if (q == 0) {
+                            const int64_t per = (int64_t)kFusedThreads * elems;
+                            for (int64_t e = 0; e * per < o.n; ++e) todo.push_back({0, FItem{at, (int)e}});
+                        }
+                        fops.push_back(f);
+                    }
+            std::stable_sort(todo.begin(), todo.end(),
+                             [](const auto& a, const auto& b) { return a.first > b.first; });
+            for (const auto& t : todo) items.push_back(t.second);
+            S.nitems.push_back((int)items.size() - S.item0.back());
+        }
+        S.ops = std::move(x.ops);
+        S.orig = std::move(x.orig);
+        if (!items.empty()) {
+            // one allocation and one copy for all tables
+            auto up = [](size_t b) { return (b + 255) / 256 * 256; };
+            const size_t o1 = up(fops.size() * sizeof(FOp)), o2 = o1 + up(items.size() * sizeof(FItem)),
+                         o3 = o2 + up(probs.size() * sizeof(ZProb)), bytes = o3 + up(tiles.size() * sizeof(ZTile));
+            if (work > 0) S.work = dalloc((size_t)work * esz());
+            S.mem = dalloc(bytes);
+            char* m = (char*)S.mem;
+            for (FOp& f : fops) {
+                f.probs = (const ZProb*)(m + o2) + (f.probs - (const ZProb*)nullptr);
+                f.tiles = (const ZTile*)(m + o3) + (f.tiles - (const ZTile*)nullptr);
+                f.work = (char*)S.work + (uintptr_t)f.work;
+            }
+            std::vector<char> h(bytes);
+            std::memcpy(h.data(), fops.data(), fops.size() * sizeof(FOp));
+            std::memcpy(h.data() + o1, items.data(), items.size() * sizeof(FItem));
+            std::memcpy(h.data() + o2, probs.data(), probs.size() * sizeof(ZProb));
+            std::memcpy(h.data() + o3, tiles.data(), tiles.size() * sizeof(ZTile));
+            hip_check(hipMemcpy(m, h.data(), bytes, hipMemcpyHostToDevice), "fused tables");
+            S.fops = (FOp*)m;
+            S.items = (FItem*)(m + o1);
+        }
+        S.gen = sched_gen;
+    }
+
+    void run_fused(const Schedule& S, size_t k) {
+        FIo io{};
+        for (size_t b = 0; b < plan.bufs.size(); ++b)
+            if (caller_buffer(plan.bufs[b].kind)) io.p[io_number(plan.bufs[b].kind)] = dbuf[b];
+        hip_check(launch_fused(S.items + S.item0[k], S.nitems[k], S.fops, io, real, st), "fused operations");
+    }
+
+    // Runs an operation list.  timed: HIP events around every operation (or
+    // only operation prof_sel), read back lazily, so timing adds no
+    // synchronisation to the stream.  Timing an operation that runs in a fused
+    // launch, a streamed operand and a batch's plan put every operation on its
+    // own kernel.
     void run_list(OpList& L, bool timed) {
         std::vector<Op>& ops = *L.ops;
         if (timed && L.ev.size() != 2 * ops.size()) {
@@ -574,37 +728,53 @@ struct fscc_ctx {
         }
         if (timed) collect(L);
         std::vector<std::vector<StreamChunk>>* sc = stream_chunks(L);
+        bool fuse = !sc && !d_active;
+        if (fuse) {
+            prepare_schedule(L);
+            const int sel = prof_sel - L.base;
+            if (timed && (prof_sel < 0 || (sel >= 0 && sel < (int)ops.size() && L.fused.in_fused[sel]))) fuse = false;
+        }
+        if (!fuse && L.plain.steps.empty()) L.plain.steps = plain_schedule(ops.size());
+        Schedule& S = fuse ? L.fused : L.plain;
         if (streams == 2 && !sc && !d_active) {
-            run_list_two(L, timed);
+            run_steps_two(L, S, timed);
             return;
         }
-        for (size_t k = 0; k < ops.size(); ++k) {
-            const bool tk = timed && (prof_sel < 0 || prof_sel == L.base + (int)k);
-            if (tk) hip_check(hipEventRecord(L.ev[2 * k], st), "event");
-            if (sc && k < sc->size() && !(*sc)[k].empty()) run_streamed(ops[k], (*sc)[k]);
-            else run_op(ops[k], &L.g[k]);
-            if (tk) {
-                hip_check(hipEventRecord(L.ev[2 * k + 1], st), "event");
-                L.pend[k] = 1;
-            }
+        for (size_t k = 0; k < S.steps.size(); ++k) run_step(L, S, k, timed, sc);
+    }
+
+    // one step on the stream st
+    void run_step(OpList& L, Schedule& S, size_t k, bool timed, std::vector<std::vector<StreamChunk>>* sc) {
+        if (S.steps[k].fused) {
+            run_fused(S, k);
+            return;
+        }
+        int j = S.steps[k].chains[0][0];
+        if (!S.ops.empty()) j = S.orig[j];
+        const bool tk = timed && (prof_sel < 0 || prof_sel == L.base + j);
+        if (tk) hip_check(hipEventRecord(L.ev[2 * j], st), "event");
+        if (sc && j < (int)sc->size() && !(*sc)[j].empty()) run_streamed((*L.ops)[j], (*sc)[j]);
+        else run_op((*L.ops)[j], &L.g[j]);
+        if (tk) {
+            hip_check(hipEventRecord(L.ev[2 * j + 1], st), "event");
+            L.pend[j] = 1;
         }
     }
 
-    // run_list on two streams: the second stream first waits for the work
+    // The steps on two streams: the second stream first waits for the work
     // already on the context's stream, every cross-stream dependency is an
     // event wait, and the context's stream finally waits for the second, so
-    // that callers see one stream.  Operations launch on the member stream st,
-    // which is switched per operation (and restored on every exit).
-    void run_list_two(OpList& L, bool timed) {
-        std::vector<Op>& ops = *L.ops;
+    // that callers see one stream.  Steps launch on the member stream st,
+    // which is switched per step (and restored on every exit).
+    void run_steps_two(OpList& L, Schedule& S, bool timed) {
         if (!st2) hip_check(hipStreamCreateWithFlags(&st2, hipStreamNonBlocking), "second stream");
-        if (L.on2.size() != ops.size()) {
-            build_two_stream(L);
-            L.xev.assign(ops.size(), nullptr);
-            for (size_t k = 0; k < ops.size(); ++k)
-                if (L.rec[k]) hip_check(hipEventCreateWithFlags(&L.xev[k], hipEventDisableTiming), "event");
-            hip_check(hipEventCreateWithFlags(&L.fork, hipEventDisableTiming), "event");
-            hip_check(hipEventCreateWithFlags(&L.join, hipEventDisableTiming), "event");
+        if (S.on2.size() != S.steps.size()) {
+            build_two_stream(S, *L.ops);
+            S.xev.assign(S.steps.size(), nullptr);
+            for (size_t k = 0; k < S.steps.size(); ++k)
+                if (S.rec[k]) hip_check(hipEventCreateWithFlags(&S.xev[k], hipEventDisableTiming), "event");
+            hip_check(hipEventCreateWithFlags(&S.fork, hipEventDisableTiming), "event");
+            hip_check(hipEventCreateWithFlags(&S.join, hipEventDisableTiming), "event");
         }
         const hipStream_t s0 = st;
         struct Restore {
@@ -612,24 +782,18 @@ struct fscc_ctx {
             hipStream_t v;
             ~Restore() { s = v; }
         } restore{st, s0};
-        hip_check(hipEventRecord(L.fork, s0), "event");
-        hip_check(hipStreamWaitEvent(st2, L.fork, 0), "stream wait");
-        for (size_t k = 0; k < ops.size(); ++k) {
-            const hipStream_t s = L.on2[k] ? st2 : s0;
-            if (L.wait[k] >= 0) hip_check(hipStreamWaitEvent(s, L.xev[L.wait[k]], 0), "stream wait");
-            const bool tk = timed && (prof_sel < 0 || prof_sel == L.base + (int)k);
-            if (tk) hip_check(hipEventRecord(L.ev[2 * k], s), "event");
+        hip_check(hipEventRecord(S.fork, s0), "event");
+        hip_check(hipStreamWaitEvent(st2, S.fork, 0), "stream wait");
+        for (size_t k = 0; k < S.steps.size(); ++k) {
+            const hipStream_t s = S.on2[k] ? st2 : s0;
+            if (S.wait[k] >= 0) hip_check(hipStreamWaitEvent(s, S.xev[S.wait[k]], 0), "stream wait");
             st = s;
-            run_op(ops[k], &L.g[k]);
+            run_step(L, S, k, timed, nullptr);
             st = s0;
-            if (tk) {
-                hip_check(hipEventRecord(L.ev[2 * k + 1], s), "event");
-                L.pend[k] = 1;
-            }
-            if (L.rec[k]) hip_check(hipEventRecord(L.xev[k], s), "event");
+            if (S.rec[k]) hip_check(hipEventRecord(S.xev[k], s), "event");
         }
-        hip_check(hipEventRecord(L.join, st2), "event");
-        hip_check(hipStreamWaitEvent(s0, L.join, 0), "stream wait");
+        hip_check(hipEventRecord(S.join, st2), "event");
+        hip_check(hipStreamWaitEvent(s0, S.join, 0), "stream wait");
     }
 };
 

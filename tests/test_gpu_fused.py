@@ -1,0 +1,61 @@
+"""Fused launches of small operations (k_fused): residuals against the dense oracle at sizes around the 16 x 16 tiles,
+the 1024-element chunks and the K split over waves and workgroups (K = o v^2 / 2 up to 4.5 k here), in complex and
+real arithmetic; and against the same operations on kernels of their own (profiling puts every operation there).
+Both sums have at most a few thousand terms of size <= max|R|, so 1e-12 of max|R| is asked, as in the parity tests."""
+import numpy as np
+import pytest
+
+import fsgen
+import layout_ref as LR
+from oracle import ccsd
+
+pytestmark = pytest.mark.gpu
+
+
+def _dev(x):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+
+def _random_t(s, rng, real):
+    no, nv = s.nocc, s.nvirt
+    go, gv = s.irrep[:no], s.irrep[no:]
+    t1 = 0.05 * (rng.normal(size=(no, nv)) + 1j * rng.normal(size=(no, nv)))
+    t2 = 0.05 * (rng.normal(size=(no, no, nv, nv)) + 1j * rng.normal(size=(no, no, nv, nv)))
+    t2 = t2 - t2.transpose(1, 0, 2, 3)
+    t2 = t2 - t2.transpose(0, 1, 3, 2)
+    t1 *= go[:, None] == gv[None, :]
+    t2 *= ((go[:, None, None, None] + go[None, :, None, None] - gv[None, None, :, None] - gv[None, None, None, :])
+           % s.nirrep == 0)
+    return (t1.real + 0j, t2.real + 0j) if real else (t1, t2)
+
+
+@pytest.mark.parametrize("real", [False, True])
+@pytest.mark.parametrize("nocc,nvirt,nirrep", [(2, 3, 1), (3, 15, 1), (4, 16, 1), (5, 17, 1), (6, 33, 2), (9, 32, 1),
+                                               (8, 37, 3), (12, 26, 5)])
+def test_fused_residual_matches_oracle_and_single_kernels(nocc, nvirt, nirrep, real):
+    import torch
+    import paper_2004_03682_amd as F
+    s = fsgen.make_system(nocc, nvirt, nirrep, 0.05, 91, real=real)
+    ctx = F.Context.from_system(s, precision="real_fp64" if real else "fp64")
+    for C in fsgen.CLASSES:
+        buf, _ = fsgen.class_buffer(s, C)
+        ctx.set_integrals(C, _dev(fsgen.real_buffer(buf) if real else buf))
+    t1, t2 = _random_t(s, np.random.default_rng(nvirt), real)
+    p1, p2 = LR.pack_t1(s, t1), LR.pack_t2(s, t2)
+    if real:
+        p1, p2 = p1.real, p2.real
+    d1, d2 = _dev(p1), _dev(p2)
+    runs = []
+    for prof in (False, True):
+        ctx.profile(prof)
+        r1, r2 = torch.full_like(d1, 3.0), torch.full_like(d2, 3.0)
+        ctx.build_residual(d1, d2, r1, r2)
+        runs.append((r1.cpu().numpy(), r2.cpu().numpy()))
+    R1, R2 = ccsd.residual(ccsd.Dense(s), t1, t2)
+    scale = max(np.abs(R1).max(), np.abs(R2).max())
+    ref = LR.pack_t1(s, R1), LR.pack_t2(s, R2)
+    for r in runs:
+        for a, b in zip(r, ref):
+            assert a.size == 0 or np.abs(a - b).max() <= 1e-12 * scale
+    ctx.destroy()
