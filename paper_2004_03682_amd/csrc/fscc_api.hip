@@ -22,9 +22,6 @@
 namespace fscc {
 namespace rt {
 
-// Default tile shape from a cost model: padded MFMA work at a per-shape
-// efficiency, against operand re-reads (A once per column tile, B once per
-// row tile) at HBM speed.  fscc_autotune() replaces it by measurement.
 // Shape limits of the vector-ALU forms (the MFMA tiles and the skinny form
 // take any shape).
 bool cfg_ok(const Op& o, int cfg, bool real) {
@@ -48,53 +45,135 @@ bool cfg_ok(const Op& o, int cfg, bool real) {
     return true;
 }
 
-double cfg_cost(const Op& o, int cfg) {
-    static const double eff[ZCFG_N] = {1.0, 1.4, 1.4, 1.6, 1.8, 1.8, 1.0, 1.0, 1.0, 1.3, 1.3, 1.0, 1.3, 1.3};
-    if (cfg == ZCFG_TALL || cfg == ZCFG_RED || cfg == ZCFG_DOT) {
-        // streaming forms: every operand element read once, exact work on the
-        // vector ALUs
-        double fl = 0.0, by = 0.0;
-        for (auto& p : o.probs) {
-            fl += 8.0 * p.M * p.N * (double)std::max(p.K, 1);
-            by += 16.0 * ((double)p.M * p.K + (double)p.K * p.N + (1.0 + o.beta) * p.M * p.N);
-        }
-        return std::max(fl / 20e12, by / 6e12) + (cfg == ZCFG_RED ? 4e-6 : 0.0);
-    }
-    if (cfg == ZCFG_SKINNY) {
-        // exact work on the vector ALUs (~20 TFLOP/s from LDS); A re-read once
-        // per 32-column block, B once per 64-row block
-        double fl = 0.0, by = 0.0;
-        for (auto& p : o.probs) {
-            const double tm = (p.M + ZSKINNY_BM - 1) / ZSKINNY_BM, tn = (p.N + ZSKINNY_BN - 1) / ZSKINNY_BN;
-            fl += 8.0 * p.M * p.N * (double)std::max(p.K, 1);
-            by += 16.0 * ((double)p.M * p.K * tn + (double)p.N * p.K * tm + 2.0 * p.M * p.N);
-        }
-        return std::max(fl / 20e12, by / 4e12) + 4e-6;
-    }
+// K chunks per problem of an MFMA tile (chunks of about 256, as many as give
+// the launch 2048 workgroups); 1 everywhere: not split.
+std::vector<int> splitk_chunks(const Op& o, int cfg) {
     int bm, bn;
     zcfg_tile(cfg, &bm, &bn);
-    double fl = 0.0, by = 0.0;
+    long long tiles = 0;
+    int maxK = 0;
     for (auto& p : o.probs) {
-        double tm = (p.M + bm - 1) / bm, tn = (p.N + bn - 1) / bn;
-        fl += 8.0 * tm * bm * tn * bn * (double)std::max(p.K, 1);
-        by += 16.0 * ((double)p.M * p.K * tn + (double)p.K * p.N * tm) + 16.0 * (double)p.M * p.N;
+        tiles += (long long)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn);
+        maxK = std::max(maxK, p.K);
     }
-    return std::max(fl * eff[cfg] / 60e12, by / 5e12);
+    const long long target = 2048;
+    const int S = tiles > 0 ? (int)std::min<long long>(512, (target + tiles - 1) / tiles) : 1;
+    std::vector<int> c(o.probs.size(), 1);
+    if (S > 1 && maxK >= 512)
+        for (size_t q = 0; q < o.probs.size(); ++q) c[q] = std::max(1, std::min(S, (o.probs[q].K + 255) / 256));
+    return c;
 }
 
-int pick_cfg(const Op& o, bool real) {
-    int best = ZCFG_64x64;
-    double bc = cfg_cost(o, best);
-    for (int c = 0; c < ZCFG_N; ++c) {
-        if (!cfg_ok(o, c, real)) continue;
-        double x = cfg_cost(o, c);
-        if (x < bc * 0.95) {
-            best = c;
-            bc = x;
+// Estimated seconds of a GEMM operation in one kernel form (lds: LDS_STAGED or
+// LDS_DIRECT for the MFMA tiles).  The constants were fitted to the times of
+// every candidate of 522 operations of 14 systems (10-40 occupied, 67-300
+// virtual spinors, 1-16 irreps, complex and real): the choices below take 3 %
+// more time than the fastest candidate of every operation (the estimate
+// before, which counted work and bytes but neither latency nor idle CUs: 15 %
+// at the largest system, a factor of two and more at the small ones and in
+// the (0h,1p) sector).
+double cfg_cost(const Op& o, int cfg, bool split, int lds, bool real) {
+    const double es = real ? 8.0 : 16.0;
+    double fl = 0.0, by = 0.0;
+    for (auto& p : o.probs) {
+        fl += (real ? 2.0 : 8.0) * p.M * p.N * (double)std::max(p.K, 1);
+        by += es * ((double)p.M * p.K + (double)p.K * p.N + (1.0 + o.beta) * p.M * p.N);
+    }
+    if (cfg == ZCFG_TALL) {
+        // one row per thread: rows past the first miss coalescing, 8 k per latency
+        long long wg = 0;
+        int K = 1, N = 1;
+        for (auto& p : o.probs) {
+            wg += (p.M + ZTALL_ROWS - 1) / ZTALL_ROWS;
+            K = std::max(K, p.K);
+            N = std::max(N, p.N);
+        }
+        const double chain = (double)((wg + 1023) / 1024) * ((K + 7) / 8) * ((N + 7) / 8) * 2.5e-6;
+        return 5e-6 + std::max(std::max(by / 2.5e12, fl / 20e12), chain);
+    }
+    if (cfg == ZCFG_RED) return 10e-6 + std::max(by / 4.6e12, fl / 15e12);
+    if (cfg == ZCFG_DOT) {
+        long long wg = 0;
+        int K = 1;
+        for (auto& p : o.probs) {
+            wg += (p.N + ZDOT_ROWS - 1) / ZDOT_ROWS;
+            K = std::max(K, p.K);
+        }
+        const double chain = (double)((wg + 511) / 512) * ((K + ZDOT_KC - 1) / ZDOT_KC) * 1.6e-6;
+        return 5e-6 + std::max(std::max(by / 5.5e12, fl / 20e12), chain);
+    }
+    if (cfg == ZCFG_SKINNY) {
+        // A re-read once per 32-column block, B once per 64-row block
+        double re = 0.0;
+        for (auto& p : o.probs) {
+            const double tm = (p.M + ZSKINNY_BM - 1) / ZSKINNY_BM, tn = (p.N + ZSKINNY_BN - 1) / ZSKINNY_BN;
+            re += es * ((double)p.M * p.K * tn + (double)p.N * p.K * tm);
+        }
+        return 10e-6 + std::max(re / 2e12, fl / 15e12);
+    }
+    // MFMA tiles.  Workgroups resident per CU (by LDS and registers)
+    static const int occ_staged[ZCFG_N] = {2, 3, 3, 5, 5, 5, 1, 1, 1, 3, 3, 1, 2, 3};
+    static const int occ_direct[ZCFG_N] = {2, 1, 1, 6, 4, 5, 1, 1, 1, 3, 3, 1, 2, 3};
+    int bm, bn;
+    zcfg_tile(cfg, &bm, &bn);
+    const std::vector<int> chunks = split ? splitk_chunks(o, cfg) : std::vector<int>(o.probs.size(), 1);
+    const bool parts = *std::max_element(chunks.begin(), chunks.end()) > 1;
+    // matrix-core cycles of one 16-deep slice of a tile on a SIMD (64 per
+    // instruction; a SIMD whose wave is past the edge idles)
+    const double slice = 64.0 * 4 * (real ? 1 : 3) * (bm * bn / 1024.0);
+    double tiles = 0.0, slices = 0.0, longest = 0.0, cache = 0.0, partial = 0.0;
+    for (size_t q = 0; q < o.probs.size(); ++q) {
+        const GemmProblem& p = o.probs[q];
+        if (p.M <= 0 || p.N <= 0) continue;
+        const int len = (p.K + chunks[q] - 1) / chunks[q], nc = p.K > 0 ? (p.K + len - 1) / len : 0;
+        const double sl = (len + 15) / 16, t = (double)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn) * nc;
+        tiles += t;
+        slices += t * sl;
+        longest = std::max(longest, sl);
+        cache += t * sl * 16 * (bm + bn) * es;
+        if (parts) partial += (double)nc * p.M * p.N * es;
+    }
+    if (tiles == 0.0) return 5e-6;
+    const double per_cu = tiles / 256.0, occ = lds == LDS_DIRECT ? occ_direct[cfg] : occ_staged[cfg];
+    const double w = std::max(1.0, std::min(occ, per_cu)), rounds = std::ceil(per_cu / w);
+    const double latency = lds == LDS_DIRECT ? 1.65e-6 : 2.05e-6;   // of one slice
+    const double t_mfma = slices * slice / 256.0 / 2.3e9 / (lds == LDS_DIRECT ? 0.80 : 0.69);
+    const double t_lat = std::max((per_cu <= w ? 1.0 : per_cu / w) * (slices / tiles) * latency, longest * latency);
+    const double t_hbm = by / 4.6e12, most = std::max(std::max(t_mfma, t_lat), t_hbm);
+    double t = std::max(most, cache / 9.25e12) + 0.25 * (t_mfma + t_lat + t_hbm - most);
+    t += 5e-6 + rounds * 1.4e-6;
+    if (parts) t += 4.5e-6 + 2.0 * partial / 4e12;
+    return t;
+}
+
+// The cheapest form by cfg_cost.  Not considered, since never the fastest where
+// the fit looked: 128x16 and 16x128 tiles and the skinny form.
+GemmChoice pick_form(const Op& o, bool real) {
+    GemmChoice best;
+    double bc = 1e30;
+    if (o.probs.empty()) return best;
+    for (int cfg : {ZCFG_64x64, ZCFG_32x32, ZCFG_64x16, ZCFG_16x64, ZCFG_32x64, ZCFG_64x32, ZCFG_64x64R, ZCFG_64x32R,
+                    ZCFG_TALL, ZCFG_RED, ZCFG_DOT}) {
+        if (!cfg_ok(o, cfg, real)) continue;
+        const bool mfma = cfg != ZCFG_TALL && cfg != ZCFG_RED && cfg != ZCFG_DOT;
+        bool can_split = false;
+        if (mfma)
+            for (int c : splitk_chunks(o, cfg)) can_split = can_split || c > 1;
+        for (int lds : {(int)LDS_DIRECT, (int)LDS_STAGED}) {
+            if (lds == LDS_DIRECT && !mfma) continue;
+            for (int sp = 0; sp <= (can_split ? 1 : 0); ++sp) {
+                const double c = cfg_cost(o, cfg, sp != 0, lds, real);
+                if (c < bc) {
+                    bc = c;
+                    best = GemmChoice{cfg, sp != 0 || cfg == ZCFG_RED, lds};
+                }
+            }
         }
     }
     return best;
 }
+
+int pick_cfg(const Op& o, bool real) { return pick_form(o, real).cfg; }
 
 // Workgroups of one launch are handed to the 8 XCDs round-robin (block b runs on
 // XCD b % 8) and each XCD has its own L2.  Permute the logical tile sequence so
@@ -325,11 +404,10 @@ void plan_gemm_host(bool real, const Op& o, int cfg, int bk, bool allow_split, b
             const int need = (p.K + cap - 1) / cap;
             Sq[q] = std::max(1, std::max(need, allow_split ? std::min(S, (p.K + 127) / 128) : 1));
         }
-    } else if (cfg != ZCFG_TALL && cfg != ZCFG_DOT && allow_split && S > 1 && maxK >= 512)
-        for (size_t q = 0; q < o.probs.size(); ++q) {
-            Sq[q] = std::max(1, std::min(S, (o.probs[q].K + 255) / 256));
-            split |= Sq[q] > 1;
-        }
+    } else if (cfg != ZCFG_TALL && cfg != ZCFG_DOT && allow_split) {
+        Sq = splitk_chunks(o, cfg);
+        for (int c : Sq) split |= c > 1;
+    }
     std::vector<ZProb>& pr = h.pr;
     std::vector<int> psys;
     std::vector<ZTile> tl;
@@ -396,14 +474,11 @@ void plan_gemm(fscc_ctx* c, const Op& o, GemmDev& g, int cfg, int bk, bool allow
 }
 
 
-// Cost-model default of a GEMM operation before (or without) autotuning:
-// pick_cfg's tile with 16-deep K slices and split-K allowed, in the
-// direct-to-LDS form wherever that tile has one (the form the autotuner
-// keeps for the large contractions).
+// Cost-model default of a GEMM operation before (or without) autotuning.
 void plan_gemm_default(fscc_ctx* c, const Op& o, GemmDev& g) {
-    const int cfg = pick_cfg(o, c->real);
-    plan_gemm(c, o, g, cfg, 16, true);
-    if (zcfg_has_dl(cfg)) g.lds = LDS_DIRECT;
+    const GemmChoice f = pick_form(o, c->real);
+    plan_gemm(c, o, g, f.cfg, 16, f.split);
+    g.lds = f.lds;
 }
 
 void setup_list(fscc_ctx* c, OpList& L, std::vector<Op>& ops) {

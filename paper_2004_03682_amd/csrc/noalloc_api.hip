@@ -91,6 +91,9 @@ fscc_status fscc_zgemm_noalloc(int cfg, int bk, int tA, int tB, int cA, int cB, 
         // (same kernel, one K chunk per tile)
         if (plan_bytes(h) > kScratchBytes && h.g.split && allow_split)
             plan_gemm_host(false, o, form, bk, false, cfg < 0 || m3, h);
+        // a form of the cost model's choosing whose tables do not fit: the
+        // largest tile, which has the fewest
+        if (cfg < 0 && plan_bytes(h) > kScratchBytes) plan_gemm_host(false, o, ZCFG_64x64, bk, false, true, h);
         if (plan_bytes(h) > kScratchBytes)
             return free_call_fail(FSCC_EINVAL, "fscc_zgemm_noalloc: plan needs " + std::to_string(plan_bytes(h)) +
                                                    " bytes of scratch, more than the static " +

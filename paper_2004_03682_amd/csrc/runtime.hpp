@@ -832,7 +832,13 @@ fscc_status guarded(fscc_ctx* c, F f) {
 }
 
 bool cfg_ok(const Op& o, int cfg, bool real = false);
-double cfg_cost(const Op& o, int cfg);
+// the cost model's choice for a GEMM operation: tile, split-K allowed, LDS staging
+struct GemmChoice {
+    int cfg = ZCFG_64x64;
+    bool split = false;
+    int lds = LDS_STAGED;
+};
+GemmChoice pick_form(const Op& o, bool real);
 int pick_cfg(const Op& o, bool real = false);
 std::vector<ZTile> xcd_order(const std::vector<ZTile>& logical);
 void free_gemm(GemmDev& g);
