@@ -1708,6 +1708,7 @@ fscc_status fscc_autotune(fscc_ctx* ctx, int level) {
     if (level < 0 || level > 2) return fail(ctx, FSCC_EINVAL, "autotune level must be 0, 1 or 2");
     return guarded(ctx, [&]() -> fscc_status {
         Plan& P = ctx->plan;
+        ++ctx->sched_gen;   // tables are freed and rebuilt: a graph captured with them is stale
         std::vector<OpList*> lists = {&ctx->L00, &ctx->L01, &ctx->L02};
         if (level == 0) {
             for (OpList* L : lists)

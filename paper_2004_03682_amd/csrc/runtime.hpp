@@ -210,8 +210,8 @@ struct fscc_ctx {
     // created on first use, with the default priority
     int streams = 1;
     hipStream_t st2 = nullptr;
-    // schedules are rebuilt when this changes (precision, reorder traversal,
-    // a buffer that moved)
+    // schedules are rebuilt, and a batch's graph captured again, when this
+    // changes (precision, reorder traversal, tuning, a buffer that moved)
     long long sched_gen = 0;
     bool gather_forced = false;   // fscc_gather_order chose a traversal: reorders keep their own kernels
     // real arithmetic (real double groups): every amplitude, integral and

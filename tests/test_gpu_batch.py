@@ -295,3 +295,24 @@ def test_autotuned_batch_converges_like_single_systems():
         assert abs(res["E"][k] - g["E"]) <= 1e-9
         ctx.destroy()
     b.destroy()
+
+
+def test_graph_is_captured_again_after_tuning():
+    """fscc_autotune on the batch's executor frees and rebuilds the tables a captured graph points to: the next step
+    has to capture again (same iterates as the eager path, to rounding)."""
+    torch = _torch()
+    systems = [fsgen.make_system(*p) for p in (SPECS[3], SPECS[1])]
+    b, e = make_batch(systems), make_batch(systems)
+    z = lambda n: torch.zeros(n, dtype=torch.complex128, device="cuda")  # noqa: E731
+    x = [z(b.n1), z(b.n2), z(b.n1), z(b.n2)]
+    y = [t.clone() for t in x]
+    b.reset(6, 1e-12)
+    e.reset(6, 1e-12)
+    for it in range(4):
+        if it == 2:
+            b.context().autotune(1)
+        rep, ref = b.step(*x, use_graph=True), e.step(*y, use_graph=False)
+        assert np.abs(rep[:, :3] - ref[:, :3]).max() <= 1e-10, it
+    assert (x[1] - y[1]).abs().max().item() <= 1e-10
+    b.destroy()
+    e.destroy()
