@@ -327,7 +327,6 @@ double op_bytes(const Plan& P, const Op& o, const std::vector<int64_t>& nnz, siz
         case OP_AXPBY: return e * (double)o.n * (2.0 + o.beta);
         case OP_DIAG: return e * (double)o.n * 3.0 + 8.0 * (double)o.n;
         case OP_MUL: return e * (double)o.n * 2.0 + 8.0 * (double)o.n;
-        case OP_REDUCE: return 0.0;
         case OP_GATHER: {
             int64_t written = o.n;
             if (o.beta) {

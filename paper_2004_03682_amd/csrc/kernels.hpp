@@ -195,40 +195,47 @@ hipError_t launch_update(const UpdateArgs& u, bool real, hipStream_t st);
 hipError_t launch_energy(const void* oovv, const void* t1, const void* t2, const GatherMaps& maps, long long n,
                          double* part, int nblk, bool real, hipStream_t st);
 // ---- fused launch of many small operations (kernels_fused.hip)
-constexpr int kFusedThreads = 1024;
+constexpr int kFusedThreads = 256;
 constexpr int kFusedIo = 10;
-// a buffer: its address, or the number of a caller's buffer (passed per launch)
-struct FRef {
-    const void* p = nullptr;
-    long long io = -1;
-};
+// a buffer: its address, or 1 + the number of a caller's buffer (passed per
+// launch), or 0 (none)
+typedef uintptr_t FRef;
 struct FIo {
     void* p[kFusedIo];
 };
-enum { FK_AXPBY = 0, FK_DIAG, FK_MUL, FK_GATHER, FK_GEMM, FK_REDUCE };
-// one operation; more: the next descriptor continues on the same destination
-// elements.  Gather term t reads srct[t]; b[t] set: times src2 (all terms or
-// none); elems (of a chain's first descriptor): 1 or 2 elements per thread.  A GEMM gives each of the ntiles 16 x 16 tiles split x kw waves (kw =
-// 1, 2, 4, 8 or 16); split > 1: the parts of a tile go to work[tile][part][256],
-// and an FK_REDUCE with the same tables adds them.
+enum { FK_AXPBY = 0, FK_DIAG, FK_MUL, FK_GATHER, FK_GEMM };
+// One operation; more: the next descriptor continues on the same destination
+// elements.  Gather term t reads src[t]; b[t] set (bil): times src2 (all terms
+// or none); the other elementwise forms read src[0] and src2.  A GEMM (src[0] times
+// src2) gives each of the ntiles 16 x 16 tiles split x kw waves (kw = 1, 2 or
+// 4); split > 1 (kw = 4): the parts of a tile go to work[tile][part][256], and
+// the last of them to arrive (counted in arrived[tile], which it clears
+// again) adds them in order.
 struct FOp {
-    int kind = 0, nt = 0, beta = 0, conj = 0, more = 0, tA = 0, tB = 0, cA = 0, cB = 0, kw = 1, ntiles = 0, split = 1, elems = 1,
-        pad = 0;
-    double ar = 0.0, ai = 0.0;
-    FRef dst, src, src2, srct[4];
-    const uint32_t* a[4] = {};
-    const uint32_t* b[4] = {};
-    long long n = 0;
-    const ZProb* probs = nullptr;
-    const ZTile* tiles = nullptr;
-    void* work = nullptr;
+    int8_t kind, nt, beta, conj, more, tA, tB, cA, cB, kw, bil;
+    int split, ntiles, n;
+    double ar, ai;
+    FRef dst, src2, src[4];
+    union {
+        struct {
+            const uint32_t* a[4];
+            const uint32_t* b[4];
+        } g;
+        struct {
+            const ZProb* probs;
+            const ZTile* tiles;
+            void* work;
+            int* arrived;
+        } m;
+    };
 };
-// one workgroup: elements [first * kFusedThreads * elems, ...) of the
-// chain that starts at ops[op], the 16 / kw units (tile, part) from unit
-// `first` of a GEMM, or the four tiles from tile `first` of a reduction
+// one workgroup: elements [first * kFusedThreads, ...) of the chain of nops
+// operations that starts at ops[op], or the 4 / kw units (tile, part) from unit `first`
+// of a GEMM
 struct FItem {
-    int op, first;
+    int op, first, nops, pad;
 };
+constexpr int kMaxChain = 8;
 hipError_t launch_fused(const FItem* items, int nitems, const FOp* ops, const FIo& io, bool real, hipStream_t st);
 
 hipError_t launch_zero(double2* dst, long long n, hipStream_t st);

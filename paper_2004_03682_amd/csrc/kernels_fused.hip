@@ -6,25 +6,31 @@
 // at a time: the 56 operations of a small system's residual are bound by
 // that, not by work (8 occupied and 24 virtual spinors: 0.55 ms for 146 Mflop).
 // The host (schedule.hpp) puts all operations whose inputs are ready into one
-// list of work items; every workgroup takes one item:
-//   * 1024 or 2048 destination elements of a chain of elementwise operations and
+// list of work items; every workgroup (four waves, one per SIMD) takes one item:
+//   * 256 destination elements of a chain of elementwise operations and
 //     reorders with one destination (tau = t2, then += t1 t1; the
 //     contributions to a residual), the values kept in registers from one
-//     operation to the next,
-//   * output tiles of 16 x 16 of a small GEMM, 16 waves over 16/kw tiles.  The kw
+//     operation to the next, or
+//   * output tiles of 16 x 16 of a small GEMM, 4 waves over 4/kw tiles.  The kw
 //     waves of a tile share its K range, every wave loads its fragments
-//     straight from memory (the operands sit in the L2) eight at a time with
-//     the next eight under way, and the partial tiles are summed through LDS
-//     in wave order.  A longer K range is split over workgroups as well, or
-//   * the sum of such parts, as an operation of its own in a later launch.
+//     straight from memory (the operands sit in the L2) with two rounds of
+//     loads under way, and the partial tiles are summed through LDS in wave
+//     order.  A longer K range is split over workgroups as well; the workgroup
+//     that finishes a tile's last part adds the parts in order.
 // Complex and real (T = double2, double).  Results are deterministic.
 //
-// Measured (whole iteration, before -> after): 8 occupied / 24 virtual spinors
-// 601 -> 168 us (10 launches of 5-15 us instead of 56), real 13 / 67 in three
-// irreps 706 -> 249 us, 20 / 120 in eight irreps 1004 -> 638 us; what is left
-// of a launch is its start (4.5 us) and five dependent memory latencies.
+// A launch of 16-wave workgroups took 11-13 us at 8 occupied / 24 virtual
+// spinors, of which 9 were the matrix pipes of the few CUs that had the tiles:
+// 16 waves of 64 k share four pipes.  With one wave per SIMD, so that a tile's
+// K range reaches over four CUs, and with descriptors and maps loaded ahead of
+// the chains the launches take 6-9 us; what is left are the start and five
+// dependent memory latencies.  Measured (whole iteration; every operation its
+// own launch, 16-wave workgroups, this): 8/24 in one irrep 601, 168, 123 us;
+// real 13/67 in three 706, 217, 186 us; 20/120 in eight 1004, 560, 536 us; the
+// (0,2) sector step of 20/200 in eight 304, 273, 249 us.
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
 #include <cstdint>
 
 #include "elem_math.hpp"
@@ -35,10 +41,37 @@ namespace {
 
 typedef double dbl4 __attribute__((ext_vector_type(4)));
 constexpr int kWaves = kFusedThreads / 64;
+static_assert(kWaves == 4, "one wave per SIMD, 4 / kw tiles");
 
+// Descriptors in LDS: the workgroup copies all operations of its item at once
+// (one memory latency however long the chain), with the callers' buffers put
+// in, and reads each into scalar registers when its turn comes.
+constexpr int kOpWords = sizeof(FOp) / 8;
+constexpr int kRefWord = offsetof(FOp, dst) / 8;   // dst, src2, src[4]
+static_assert(sizeof(FOp) % 8 == 0 && offsetof(FOp, src2) == (kRefWord + 1) * 8 && offsetof(FOp, src) == (kRefWord + 2) * 8,
+              "buffer references in a row");
+
+__device__ __forceinline__ void stage_ops(const FOp* __restrict__ ops, int n, const FIo& io, unsigned long long* lds) {
+    const unsigned long long* w = (const unsigned long long*)ops;
+    for (int k = threadIdx.x; k < n * kOpWords; k += kFusedThreads) {
+        unsigned long long x = w[k];
+        const int f = k % kOpWords - kRefWord;
+        if (f >= 0 && f < 6 && x != 0 && x <= (unsigned long long)kFusedIo) x = (unsigned long long)io.p[x - 1];
+        lds[k] = x;
+    }
+}
+__device__ __forceinline__ FOp staged_op(const unsigned long long* lds) {
+    struct Words {
+        int w[2 * kOpWords];
+    } u;
+    const int* p = (const int*)lds;
+#pragma unroll
+    for (int k = 0; k < 2 * kOpWords; ++k) u.w[k] = __builtin_amdgcn_readfirstlane(p[k]);
+    return __builtin_bit_cast(FOp, u);
+}
 template <typename T>
-__device__ __forceinline__ T* ptr(const FRef& r, const FIo& io) {
-    return (T*)(r.io >= 0 ? io.p[r.io] : r.p);
+__device__ __forceinline__ T* ptr(FRef r) {
+    return (T*)r;
 }
 
 __device__ __forceinline__ double2 mapped(const double2* __restrict__ s, uint32_t m) {
@@ -70,119 +103,90 @@ __device__ __forceinline__ void scale(double2& o, double d) {
 }
 __device__ __forceinline__ void scale(double& o, double d) { o *= d; }
 
-// E destination elements per thread (kFusedThreads apart) through a chain of
-// operations: the loads of all elements are under way together, so a workgroup
-// pays the memory latencies of the chain once for all of them (two elements,
-// where one per thread would take more than the workgroups resident at once;
-// four need more registers than a 1024-thread workgroup has).
-template <int E, typename T>
-__device__ void fused_elements(const FOp* __restrict__ op, const FIo& io, long long k0) {
-    constexpr int TG = E == 1 ? 4 : 2;   // terms whose sources are under way together
-    T v[E];
-    bool held[E], in[E];   // v holds the element's value; the element exists
-    long long at[E];
-    const long long n = op->n;
-    T* dst = ptr<T>(op->dst, io);
+// maps of a reorder's terms at a thread's element
+struct Maps {
+    uint32_t a[4], b[4];
+};
+__device__ __forceinline__ void load_maps(Maps& m, const FOp& o, int at) {
+    if (o.kind != FK_GATHER) return;
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const long long k = k0 + (long long)e * kFusedThreads;
-        in[e] = k < n;
-        at[e] = in[e] ? k : n - 1;   // past the end: the last element's loads, nothing stored
-        held[e] = false;
-        v[e] = T{};
+    for (int t = 0; t < 4; ++t) {
+        m.a[t] = t < o.nt ? o.g.a[t][at] : 0xFFFFFFFFu;
+        m.b[t] = o.bil && t < o.nt ? o.g.b[t][at] : 0u;
     }
-    auto old = [&](int e) {
-        if (!held[e]) v[e] = dst[at[e]];
-        held[e] = true;
-    };
-    for (;; ++op) {
-        const FOp o = *op;
-        const T* src = ptr<const T>(o.src, io);
+}
+
+// One destination element per thread through a chain of operations.  The
+// memory latencies are what a chain costs, so the sources of all terms are
+// under way together, and with them the next operation's maps.  (Several
+// chunks per workgroup, the next one's maps loaded ahead: no faster.)
+template <typename T>
+__device__ void fused_elements(const unsigned long long* __restrict__ lds, FOp o, int k) {
+    const int at = min(k, o.n - 1);   // past the end: the last element's loads, nothing stored
+    T* dst = ptr<T>(o.dst);
+    const bool in = k < o.n;
+    T v{};
+    bool have = false, held = false;   // v holds the element's value; it has changed
+    Maps m;
+    load_maps(m, o, at);
+    for (;;) {
+        if (!have && (o.beta || o.kind == FK_DIAG || o.kind == FK_MUL)) v = dst[at];
+        have = true;
+        Maps mn;
+        auto next = [&] {
+            if (o.more) load_maps(mn, staged_op(lds + kOpWords), at);
+        };
         if (o.kind == FK_GATHER) {
-            // the maps of all terms, then the sources of TG terms at a time
-            const T* src2 = ptr<const T>(o.src2, io);
-            const bool bil = o.b[0] != nullptr;
-            uint32_t ma[4][E], mb[4][E];
-            T s[E];
-            bool any[E];
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                s[e] = T{};
-                any[e] = false;
-            }
+            T x[4], y[4];
 #pragma unroll
             for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int e = 0; e < E; ++e) {
-                    ma[t][e] = t < o.nt ? o.a[t][at[e]] : 0xFFFFFFFFu;
-                    mb[t][e] = bil && t < o.nt ? o.b[t][at[e]] : 0u;
+                if (t < o.nt) {
+                    x[t] = mapped(ptr<const T>(o.src[t]), m.a[t]);
+                    if (o.bil) y[t] = mapped(ptr<const T>(o.src2), m.b[t]);
                 }
+            next();
+            T s{};
+            bool any = false;
 #pragma unroll
-            for (int t = 0; t < 4; t += TG) {
-                if (t >= o.nt) break;
-                T x[TG][E], y[TG][E];
-#pragma unroll
-                for (int u = 0; u < TG; ++u)
-#pragma unroll
-                    for (int e = 0; e < E; ++e) {
-                        x[u][e] = mapped(ptr<const T>(o.srct[t + u], io), ma[t + u][e]);
-                        if (bil) y[u][e] = mapped(src2, mb[t + u][e]);
-                    }
-#pragma unroll
-                for (int u = 0; u < TG; ++u)
-                    if (t + u < o.nt)
-#pragma unroll
-                        for (int e = 0; e < E; ++e) {
-                            any[e] = any[e] || (ma[t + u][e] != 0xFFFFFFFFu && mb[t + u][e] != 0xFFFFFFFFu);
-                            T z = x[u][e];
-                            if (o.conj) conjugate(z);
-                            if (bil) z = elem_mul(z, y[u][e]);
-                            add(s[e], z);
-                        }
-            }
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                // an accumulating gather leaves an element whose terms are
-                // all structural zeros as it is
-                if (o.beta && !any[e]) continue;
-                T out = elem_scale(o.ar, o.ai, s[e]);
-                if (o.beta) {
-                    old(e);
-                    add(out, v[e]);
+            for (int t = 0; t < 4; ++t)
+                if (t < o.nt) {
+                    any = any || (m.a[t] != 0xFFFFFFFFu && m.b[t] != 0xFFFFFFFFu);
+                    T z = x[t];
+                    if (o.conj) conjugate(z);
+                    if (o.bil) z = elem_mul(z, y[t]);
+                    add(s, z);
                 }
-                v[e] = out;
-                held[e] = true;
+            // an accumulating gather leaves an element whose terms are all
+            // structural zeros as it is
+            if (!o.beta || any) {
+                T out = elem_scale(o.ar, o.ai, s);
+                if (o.beta) add(out, v);
+                v = out;
+                held = true;
             }
         } else if (o.kind == FK_AXPBY) {
-            T x[E];
-#pragma unroll
-            for (int e = 0; e < E; ++e) x[e] = src[at[e]];
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                if (o.conj) conjugate(x[e]);
-                T out = elem_scale(o.ar, o.ai, x[e]);
-                if (o.beta) {
-                    old(e);
-                    add(out, v[e]);
-                }
-                v[e] = out;
-                held[e] = true;
-            }
+            T x = ptr<const T>(o.src[0])[at];
+            next();
+            if (o.conj) conjugate(x);
+            T out = elem_scale(o.ar, o.ai, x);
+            if (o.beta) add(out, v);
+            v = out;
+            held = true;
         } else {
-            const double* d = ptr<const double>(o.src2, io);
-            const bool diag = o.kind == FK_DIAG;
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                old(e);
-                if (diag) v[e] = elem_sub(v[e], d[at[e]], src[at[e]]);
-                else scale(v[e], d[at[e]]);
-            }
+            const double f = ptr<const double>(o.src2)[at];
+            T x{};
+            if (o.kind == FK_DIAG) x = ptr<const T>(o.src[0])[at];
+            next();
+            if (o.kind == FK_DIAG) v = elem_sub(v, f, x);
+            else scale(v, f);
+            held = true;
         }
         if (!o.more) break;
+        lds += kOpWords;
+        o = staged_op(lds);
+        m = mn;
     }
-#pragma unroll
-    for (int e = 0; e < E; ++e)
-        if (held[e] && in[e]) dst[at[e]] = v[e];
+    if (held && in) dst[at] = v;
 }
 
 // Accumulators of one 16 x 16 tile.  Complex: three real products (p = Ar Br,
@@ -217,112 +221,160 @@ struct AccOf<double> {
 };
 
 // output element e (0..255) of a tile, in the order in which the accumulators
-// hold it: element q of a lane is row 4 q + lane / 16, column lane % 16
+// hold it: element q of a lane is row 4 q + lane / 16, column lane % 16;
+// nullptr past the edge
 template <typename T>
-__device__ __forceinline__ void tile_store(const FOp& o, T* C, const ZTile& tl, const ZProb& pr, int e, T s) {
+__device__ __forceinline__ T* tile_at(T* C, const ZTile& tl, const ZProb& pr, int e) {
     const int row = tl.m0 + (e >> 6) * 4 + ((e & 63) >> 4), col = tl.n0 + (e & 15);
-    if (row >= pr.M || col >= pr.N) return;
-    T* p = C + pr.c_off + (long long)row * pr.ldc + col;
-    T out = elem_scale(o.ar, o.ai, s);
-    if (o.beta) add(out, *p);
-    *p = out;
+    return row < pr.M && col < pr.N ? C + pr.c_off + (long long)row * pr.ldc + col : nullptr;
 }
 
-// Units [first, first + 16/kw) of a GEMM: unit = (tile, K part of `split`).
+__device__ __forceinline__ void part_store(double* p, double x) {
+    __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double part_load(const double* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void part_store(double2* p, double2 x) {
+    part_store(&p->x, x.x);
+    part_store(&p->y, x.y);
+}
+__device__ __forceinline__ double2 part_load(const double2* p) {
+    return make_double2(part_load(&p->x), part_load(&p->y));
+}
+
+// Units [first, first + 4/kw) of a GEMM: unit = (tile, K part of `split`).
 template <typename T>
-__device__ void fused_gemm(const FOp* __restrict__ op, const FIo& io, int first, T* __restrict__ red) {
-    const FOp o = *op;
+__device__ void fused_gemm(const FOp o, int first, T* __restrict__ red) {
+    // steps per round of loads; three rounds of registers.  Four steps for
+    // complex as well would take the kernel over 128 registers: 3 % slower at
+    // 8/24 and 20/120 for the waves that are then not resident.
+    constexpr int R = sizeof(T) == 16 ? 2 : 4;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kw = o.kw, g = wave / kw, unit = first + g;
     const bool live = unit < o.ntiles * o.split;   // uniform per wave
     const int tile = unit / o.split, part = unit % o.split;
+    const int e0 = tid - g * kw * 64, es = kw * 64;   // the thread's elements of its tile: e0, e0 + es, ..
+    T* C = ptr<T>(o.dst);
+    T* at = nullptr;   // of the first of them, and what it held
+    T old{};
     ZTile tl{};
     ZProb pr{};
     if (live) {
-        tl = o.tiles[tile];
-        pr = o.probs[tl.prob];
+        tl = o.m.tiles[tile];
+        pr = o.m.probs[tl.prob];
         const int lr = lane & 15, lq = lane >> 4;
         const int waves = kw * o.split, chunk = ((pr.K + waves - 1) / waves + 3) & ~3;
         const int kb = min(pr.K, (part * kw + wave % kw) * chunk), ke = min(pr.K, kb + chunk);
         const long long ska = o.tA ? pr.lda : 1, skb = o.tB ? 1 : pr.ldb;
         const long long sma = o.tA ? 1 : pr.lda, snb = o.tB ? pr.ldb : 1;
         // rows and columns past the edge read the last one; they reach no stored output
-        const T* pa = ptr<const T>(o.src, io) + pr.a_off + min(tl.m0 + lr, pr.M - 1) * sma;
-        const T* pb = ptr<const T>(o.src2, io) + pr.b_off + min(tl.n0 + lr, pr.N - 1) * snb;
+        const T* pa = ptr<const T>(o.src[0]) + pr.a_off + min(tl.m0 + lr, pr.M - 1) * sma;
+        const T* pb = ptr<const T>(o.src2) + pr.b_off + min(tl.n0 + lr, pr.N - 1) * snb;
         const bool cA = o.cA, cB = o.cB;
         typename AccOf<T>::type c;
         clear(c);
-        // 16 k per round: step s of lane group q takes k0 + 4 s + q; k past the
-        // end reads the last one and counts as zero in both operands
-        auto load = [&](T (&a)[4], T (&b)[4], int k0) {
+        // R steps of 4 k per round: step s of lane group q takes k0 + 4 s + q;
+        // k past the end reads the last one and counts as zero in both operands
+        auto load = [&](T (&a)[R], T (&b)[R], int k0) {
+            if (k0 >= ke) return;
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
+            for (int s = 0; s < R; ++s) {
                 const int k = min(k0 + 4 * s + lq, ke - 1);
                 a[s] = pa[k * ska];
                 b[s] = pb[k * skb];
             }
         };
-        auto work = [&](T (&a)[4], T (&b)[4], int k0) {
-            const bool edge = k0 + 16 > ke;
+        auto work = [&](T (&a)[R], T (&b)[R], int k0) {
+            if (k0 >= ke) return;
+            const bool edge = k0 + 4 * R > ke;
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
+            for (int s = 0; s < R; ++s) {
                 if (edge && k0 + 4 * s + lq >= ke) a[s] = b[s] = T{};
                 if (cA) conjugate(a[s]);
                 if (cB) conjugate(b[s]);
                 mma(c, a[s], b[s]);
             }
         };
-        if (kb < ke) {
-            T a0[4], b0[4], a1[4], b1[4];
-            load(a0, b0, kb);
-            for (int k0 = kb; k0 < ke; k0 += 32) {
-                if (k0 + 16 < ke) load(a1, b1, k0 + 16);
-                work(a0, b0, k0);
-                if (k0 + 16 < ke) {
-                    if (k0 + 32 < ke) load(a0, b0, k0 + 32);
-                    work(a1, b1, k0 + 16);
-                }
-            }
+        T a0[R], b0[R], a1[R], b1[R], a2[R], b2[R];
+        load(a0, b0, kb);
+        load(a1, b1, kb + 4 * R);
+        // the destination, long before its value is needed
+        at = tile_at(C, tl, pr, e0);
+        if (o.beta && o.split == 1 && at) old = *at;
+        for (int k0 = kb; k0 < ke; k0 += 12 * R) {
+            load(a2, b2, k0 + 8 * R);
+            work(a0, b0, k0);
+            load(a0, b0, k0 + 12 * R);
+            work(a1, b1, k0 + 4 * R);
+            load(a1, b1, k0 + 16 * R);
+            work(a2, b2, k0 + 8 * R);
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) put(&red[(wave * 4 + q) * 64 + lane], c, q);
     }
     __syncthreads();
-    if (!live) return;
-    T* C = ptr<T>(o.dst, io);
-    T* W = (T*)o.work + (long long)unit * 256;
-    for (int e = tid - g * kw * 64; e < 256; e += kw * 64) {
-        T s{};
-        for (int w = 0; w < kw; ++w) add(s, red[(g * kw + w) * 256 + e]);
-        if (o.split > 1) W[e] = s;
-        else tile_store(o, C, tl, pr, e, s);
+    if (o.split == 1) {
+        if (!live) return;
+        for (int e = e0; e < 256; e += es) {
+            if (e > e0) {
+                at = tile_at(C, tl, pr, e);
+                if (o.beta && at) old = *at;
+            }
+            if (!at) continue;
+            T s{};
+            for (int w = 0; w < kw; ++w) add(s, red[(g * kw + w) * 256 + e]);
+            T out = elem_scale(o.ar, o.ai, s);
+            if (o.beta) add(out, old);
+            *at = out;
+        }
+        return;
     }
-}
-
-// Second pass of a GEMM whose K range is split over workgroups: four tiles per
-// workgroup, the parts added in order.
-template <typename T>
-__device__ void fused_reduce(const FOp* __restrict__ op, const FIo& io, int first) {
-    const FOp o = *op;
-    const int tile = first + (threadIdx.x >> 8), e = threadIdx.x & 255;
-    if (tile >= o.ntiles) return;
-    const ZTile tl = o.tiles[tile];
-    const ZProb pr = o.probs[tl.prob];
-    const T* W = (const T*)o.work + (long long)tile * o.split * 256 + e;
+    // Split over workgroups (kw = 4: one part of one tile, one element per
+    // thread; the grid has no dead part): the parts meet in memory.  Parts and
+    // counter are accessed by device-scope atomics only, which no cache holds
+    // back, so no fence has to write back or drop the L2 (fences here: 10-15
+    // us for the whole launch).  A part is complete before its workgroup is
+    // counted, and only the workgroup counted last reads.
+    T* W = (T*)o.m.work + (long long)tile * o.split * 256 + tid;
     T s{};
-    for (int p = 0; p < o.split; ++p) add(s, W[p * 256]);
-    tile_store(o, ptr<T>(o.dst, io), tl, pr, e, s);
+#pragma unroll
+    for (int w = 0; w < 4; ++w) add(s, red[w * 256 + tid]);
+    part_store(W + part * 256, s);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    int* last = (int*)red;
+    if (tid == 0)
+        *last = __hip_atomic_fetch_add(&o.m.arrived[tile], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == o.split - 1;
+    __syncthreads();
+    if (!*last) return;
+    if (tid == 0) __hip_atomic_store(&o.m.arrived[tile], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
+    if (o.beta && at) old = *at;
+    s = T{};
+#pragma unroll 8
+    for (int p = 0; p < o.split; ++p) add(s, part_load(W + p * 256));
+    if (!at) return;
+    T out = elem_scale(o.ar, o.ai, s);
+    if (o.beta) add(out, old);
+    *at = out;
 }
 
 template <typename T>
-__global__ __launch_bounds__(1024) void k_fused(const FItem* __restrict__ items, const FOp* __restrict__ ops, FIo io) {
+__global__ __launch_bounds__(kFusedThreads, 4) void k_fused(const FItem* __restrict__ items, const FOp* __restrict__ ops,
+                                                         FIo io) {
     __shared__ T red[kWaves * 256];
+    unsigned long long* lds = (unsigned long long*)red;
+    static_assert(kMaxChain * sizeof(FOp) <= sizeof red, "descriptors fit");
     const FItem it = items[blockIdx.x];
-    const FOp* o = ops + it.op;
-    if (o->kind == FK_GEMM) fused_gemm<T>(o, io, it.first, red);
-    else if (o->kind == FK_REDUCE) fused_reduce<T>(o, io, it.first);
-    else if (o->elems == 1) fused_elements<1, T>(o, io, (long long)it.first * kFusedThreads + threadIdx.x);
-    else fused_elements<2, T>(o, io, (long long)it.first * (2 * kFusedThreads) + threadIdx.x);
+    stage_ops(ops + it.op, it.nops, io, lds);
+    __syncthreads();
+    const FOp o = staged_op(lds);
+    if (o.kind == FK_GEMM) {
+        __syncthreads();   // the partial tiles take the descriptor's place
+        fused_gemm<T>(o, it.first, red);
+    } else {
+        fused_elements<T>(lds, o, it.first * kFusedThreads + (int)threadIdx.x);
+    }
 }
 
 }  // namespace

@@ -47,7 +47,6 @@ enum OpKind {
     OP_AXPBY,    // dst[k] = alpha*cj(src[k]) + beta*dst[k]
     OP_DIAG,     // dst[k] -= d[k] * src[k]   (d real)
     OP_MUL,      // dst[k] *= d[k]            (d real)
-    OP_REDUCE,   // second pass of a fused GEMM split along K (schedules only)
 };
 
 struct Op {

@@ -111,12 +111,10 @@ struct StreamPlan {
 struct Schedule {
     long long gen = -1;       // fscc_ctx::sched_gen it was built for
     std::vector<ScheduleStep> steps;
-    std::vector<Op> ops;      // the entries the steps refer to (plain: empty, the list's own)
-    std::vector<int> orig;
     std::vector<int> item0, nitems;
     FItem* items = nullptr;   // in mem
     FOp* fops = nullptr;
-    void* mem = nullptr;      // items, operations, problem and tile tables
+    void* mem = nullptr;      // items, operations, problem and tile tables, arrival counters
     void* work = nullptr;     // partial tiles of the GEMMs split over workgroups
     std::vector<char> in_fused;   // per operation
     std::vector<char> on2, rec;
@@ -139,7 +137,7 @@ struct OpList {
 // The two-stream form of a schedule: GEMMs with more than 8 flops per
 // algorithmic byte on the first stream, everything else on the second.
 inline void build_two_stream(Schedule& S, const std::vector<Op>& list) {
-    const std::vector<Op>& ops = S.ops.empty() ? list : S.ops;
+    const std::vector<Op>& ops = list;
     const size_t n = S.steps.size();
     S.on2.assign(n, 0);
     S.rec.assign(n, 0);
@@ -149,7 +147,7 @@ inline void build_two_stream(Schedule& S, const std::vector<Op>& list) {
         for (const auto& c : S.steps[k].chains)
             for (int j : c) step_of[j] = (int)k;
         const int j = S.steps[k].chains[0][0];
-        const Op& o = list[S.ops.empty() ? j : S.orig[j]];
+        const Op& o = list[j];
         S.on2[k] = S.steps[k].fused || !(o.kind == OP_GEMM && o.flops > 8.0 * std::max(o.bytes, 1.0));
     }
     const std::vector<std::vector<int>> deps = op_dependencies(ops);
@@ -549,11 +547,9 @@ struct fscc_ctx {
     }
 
     FRef fref(int buf) const {
-        FRef r;
-        if (buf < 0) return r;
-        if (caller_buffer(plan.bufs[buf].kind)) r.io = io_number(plan.bufs[buf].kind);
-        else r.p = dbuf[buf];
-        return r;
+        if (buf < 0) return 0;
+        if (caller_buffer(plan.bufs[buf].kind)) return 1 + io_number(plan.bufs[buf].kind);
+        return (FRef)dbuf[buf];
     }
 
     static int io_number(BufKind k) {
@@ -585,59 +581,46 @@ struct fscc_ctx {
             if (o.kind == OP_GEMM && prec != FSCC_FP64 && L.g[k].mx && L.g[k].mx->prec == prec) alone[k] = 1;
             if (o.kind == OP_GATHER && gather_forced) alone[k] = 1;
         }
-        ExpandedOps x = expand_ops(ops, alone, real, (int)plan.bufs.size());
-        S.steps = build_schedule(x);
+        S.steps = build_schedule(ops, small_ops(ops, alone, real));
         S.in_fused.assign(ops.size(), 0);
         std::vector<FOp> fops;
         std::vector<FItem> items;
         std::vector<ZProb> probs;
         std::vector<ZTile> tiles;
-        // tables of a GEMM, shared by its partial products and their sum: offsets until uploaded
-        struct Tab {
-            long long probs = -1, tiles = 0, work = 0;
-        };
-        std::vector<Tab> tab(ops.size());
-        long long work = 0;
+        long long work = 0, arrived = 0;   // elements of partial tiles, counters of their tiles
         for (const ScheduleStep& st : S.steps) {
             S.item0.push_back((int)items.size());
-            // longest items first: GEMMs by K per wave, then sums and elementwise chains
+            // longest items first: GEMMs by K per wave, then elementwise chains
             std::vector<std::pair<int, FItem>> todo;
-            // two elements per thread where one would take more than the 512 workgroups resident at once
-            int64_t elements = 0;
-            for (const auto& c : st.chains) elements += x.ops[c[0]].n;
-            const int elems = elements > 512 * kFusedThreads ? 2 : 1;
             if (st.fused)
                 for (const auto& c : st.chains)
                     for (size_t q = 0; q < c.size(); ++q) {
-                        const Op& xo = x.ops[c[q]];
-                        const int j = x.orig[c[q]], at = (int)fops.size();
+                        const int j = c[q], at = (int)fops.size();
                         const Op& o = ops[j];
                         S.in_fused[j] = 1;
-                        FOp f;
-                        f.kind = xo.kind == OP_GEMM     ? FK_GEMM
-                                 : xo.kind == OP_REDUCE ? FK_REDUCE
-                                 : xo.kind == OP_AXPBY  ? FK_AXPBY
-                                 : xo.kind == OP_DIAG   ? FK_DIAG
-                                 : xo.kind == OP_MUL    ? FK_MUL
-                                                        : FK_GATHER;
-                        f.beta = o.beta;
-                        f.conj = o.conj;
+                        FOp f{};
+                        f.kind = o.kind == OP_GEMM    ? FK_GEMM
+                                 : o.kind == OP_AXPBY ? FK_AXPBY
+                                 : o.kind == OP_DIAG  ? FK_DIAG
+                                 : o.kind == OP_MUL   ? FK_MUL
+                                                      : FK_GATHER;
+                        f.beta = o.beta != 0;
+                        f.conj = o.conj != 0;
                         f.more = q + 1 < c.size();
-                        f.elems = elems;
                         f.ar = o.alpha.real();
                         f.ai = o.alpha.imag();
                         f.dst = fref(o.dst);
-                        f.src = fref(o.src);
                         f.src2 = fref(o.src2);
-                        f.n = o.n;
+                        f.n = (int)o.n;
                         f.nt = (int)o.mapsA.size();
+                        f.bil = !o.mapsB.empty();
                         for (int t = 0; t < 4; ++t) {
-                            f.a[t] = t < (int)o.mapsA.size() ? dmap[o.mapsA[t]] : nullptr;
-                            f.b[t] = t < (int)o.mapsB.size() ? dmap[o.mapsB[t]] : nullptr;
-                            f.srct[t] = t < (int)o.srcT.size() ? fref(o.srcT[t]) : f.src;
+                            f.src[t] = fref(t < (int)o.srcT.size() ? o.srcT[t] : o.src);
+                            f.g.a[t] = t < (int)o.mapsA.size() ? dmap[o.mapsA[t]] : nullptr;
+                            f.g.b[t] = t < (int)o.mapsB.size() ? dmap[o.mapsB[t]] : nullptr;
                         }
                         if (o.kind == OP_GEMM) {
-                            const FusedSplit fs = fused_split(o);
+                            const FusedSplit fs = fused_split(o, real);
                             f.kw = fs.kw;
                             f.split = fs.split;
                             f.ntiles = fs.tiles;
@@ -645,33 +628,26 @@ struct fscc_ctx {
                             f.tB = o.tB;
                             f.cA = o.cA;
                             f.cB = o.cB;
-                            Tab& T = tab[j];
-                            int K = 0;
-                            for (const GemmProblem& p : o.probs) K = std::max(K, p.K);
-                            if (T.probs < 0) {
-                                T.probs = (long long)probs.size();
-                                T.tiles = (long long)tiles.size();
-                                for (const GemmProblem& p : o.probs) {
-                                    for (int m = 0; m < p.M; m += 16)
-                                        for (int n = 0; n < p.N; n += 16)
-                                            tiles.push_back(ZTile{(int)((long long)probs.size() - T.probs), m, n, 0});
-                                    probs.push_back(ZProb{p.a_off, p.b_off, p.c_off, p.M, p.N, p.K, p.lda, p.ldb, p.ldc});
-                                }
-                                T.work = work;
-                                if (fs.split > 1) work += (long long)fs.tiles * fs.split * 256;
+                            // numbers of the first entries, made addresses below
+                            f.m = {(const ZProb*)(uintptr_t)probs.size(), (const ZTile*)(uintptr_t)tiles.size(),
+                                   (void*)(uintptr_t)work, (int*)(uintptr_t)arrived};
+                            int K = 0, p = 0;
+                            for (const GemmProblem& q2 : o.probs) {
+                                K = std::max(K, q2.K);
+                                for (int m = 0; m < q2.M; m += 16)
+                                    for (int n = 0; n < q2.N; n += 16) tiles.push_back(ZTile{p, m, n, 0});
+                                probs.push_back(ZProb{q2.a_off, q2.b_off, q2.c_off, q2.M, q2.N, q2.K, q2.lda, q2.ldb, q2.ldc});
+                                ++p;
                             }
-                            // element offsets, made addresses below
-                            f.probs = (const ZProb*)nullptr + T.probs;
-                            f.tiles = (const ZTile*)nullptr + T.tiles;
-                            f.work = (void*)(uintptr_t)(T.work * esz());
-                            if (f.kind == FK_GEMM)
-                                for (int t = 0; t < fs.tiles * fs.split; t += 16 / fs.kw)
-                                    todo.push_back({1 + K / (fs.kw * fs.split), FItem{at, t}});
-                            else
-                                for (int t = 0; t < fs.tiles; t += 4) todo.push_back({0, FItem{at, t}});
+                            if (fs.split > 1) {
+                                work += (long long)fs.tiles * fs.split * 256;
+                                arrived += fs.tiles;
+                            }
+                            for (int t = 0; t < fs.tiles * fs.split; t += 4 / fs.kw)
+                                todo.push_back({1 + K / (fs.kw * fs.split), FItem{at, t, 1, 0}});
                         } else if (q == 0) {
-                            const int64_t per = (int64_t)kFusedThreads * elems;
-                            for (int64_t e = 0; e * per < o.n; ++e) todo.push_back({0, FItem{at, (int)e}});
+                            for (int64_t e = 0; e * kFusedThreads < o.n; ++e)
+                                todo.push_back({0, FItem{at, (int)e, (int)c.size(), 0}});
                         }
                         fops.push_back(f);
                     }
@@ -680,23 +656,24 @@ struct fscc_ctx {
             for (const auto& t : todo) items.push_back(t.second);
             S.nitems.push_back((int)items.size() - S.item0.back());
         }
-        S.ops = std::move(x.ops);
-        S.orig = std::move(x.orig);
         if (!items.empty()) {
             // one allocation and one copy for all tables
             auto up = [](size_t b) { return (b + 255) / 256 * 256; };
             const size_t o1 = up(fops.size() * sizeof(FOp)), o2 = o1 + up(items.size() * sizeof(FItem)),
-                         o3 = o2 + up(probs.size() * sizeof(ZProb)), bytes = o3 + up(tiles.size() * sizeof(ZTile));
+                         o3 = o2 + up(probs.size() * sizeof(ZProb)), o4 = o3 + up(tiles.size() * sizeof(ZTile)),
+                         bytes = o4 + (size_t)arrived * sizeof(int);
             if (work > 0) S.work = dalloc((size_t)work * esz());
             S.mem = dalloc(bytes);
             char* m = (char*)S.mem;
-            for (FOp& f : fops) {
-                f.probs = (const ZProb*)(m + o2) + (f.probs - (const ZProb*)nullptr);
-                f.tiles = (const ZTile*)(m + o3) + (f.tiles - (const ZTile*)nullptr);
-                f.work = (char*)S.work + (uintptr_t)f.work;
-            }
-            std::vector<char> h(bytes);
-            std::memcpy(h.data(), fops.data(), fops.size() * sizeof(FOp));
+            for (FOp& f : fops)
+                if (f.kind == FK_GEMM) {
+                    f.m.probs = (const ZProb*)(m + o2) + (uintptr_t)f.m.probs;
+                    f.m.tiles = (const ZTile*)(m + o3) + (uintptr_t)f.m.tiles;
+                    f.m.work = (char*)S.work + (uintptr_t)f.m.work * esz();
+                    f.m.arrived = (int*)(m + o4) + (uintptr_t)f.m.arrived;
+                }
+            std::vector<char> h(bytes, 0);   // the counters start at zero
+            std::memcpy(h.data(), (const void*)fops.data(), fops.size() * sizeof(FOp));
             std::memcpy(h.data() + o1, items.data(), items.size() * sizeof(FItem));
             std::memcpy(h.data() + o2, probs.data(), probs.size() * sizeof(ZProb));
             std::memcpy(h.data() + o3, tiles.data(), tiles.size() * sizeof(ZTile));
@@ -750,7 +727,6 @@ struct fscc_ctx {
             return;
         }
         int j = S.steps[k].chains[0][0];
-        if (!S.ops.empty()) j = S.orig[j];
         const bool tk = timed && (prof_sel < 0 || prof_sel == L.base + j);
         if (tk) hip_check(hipEventRecord(L.ev[2 * j], st), "event");
         if (sc && j < (int)sc->size() && !(*sc)[j].empty()) run_streamed((*L.ops)[j], (*sc)[j]);

@@ -75,11 +75,13 @@ struct ScheduleStep {
 // reads its operands once per 16 x 16 output tile.
 //   * traffic of all tiles <= 48 MB (5 us at the rate the L2s deliver) and
 //     padded work <= 0.4 Gflop (8 us at half the matrix peak): above, the
-//     grouped tiles with operands shared through LDS are faster;
+//     grouped tiles with operands shared through LDS are faster (twice both:
+//     20/120 in eight irreps 0.7 % slower).  A real operation has less work
+//     to share a launch's cost, and twice the traffic pays: 13/67 in three
+//     irreps 207 us at 48 MB and 0.2 Gflop, 186 us at 96 MB and 0.4 Gflop;
 //   * elementwise operations and reorders of up to 2^19 elements: above,
 //     their own launch costs less than 5 % of their time.
 inline bool fusable(const Op& o, bool real) {
-    if (o.kind == OP_REDUCE) return true;
     if (o.kind != OP_GEMM) return o.n <= (1 << 19);
     double bytes = 0.0, flops = 0.0;
     for (const GemmProblem& p : o.probs) {
@@ -87,87 +89,51 @@ inline bool fusable(const Op& o, bool real) {
         bytes += tiles * p.K * 32 * (real ? 8 : 16);
         flops += tiles * p.K * 256 * (real ? 2 : 8);
     }
-    return bytes <= 48e6 && flops <= (real ? 0.2e9 : 0.4e9);
+    return bytes <= (real ? 96e6 : 48e6) && flops <= 0.4e9;
 }
 
-// Waves of a 16 x 16 tile of a fused GEMM: kw waves in a workgroup, times
-// split workgroups.  K is split down to 64 per wave (four rounds of loads)
-// while the tiles alone do not give the chip its 4096 waves.  A CU works on
-// 1024 k of a tile for 5 us; longer ranges go over workgroups in parts of
-// about 512, at the price of a second pass.
+// Waves of a 16 x 16 tile of a fused GEMM: kw waves in a workgroup, one per
+// SIMD, times split workgroups.  The matrix pipe of a SIMD takes 1.3 us for 64
+// k of a complex tile (192 k of a real one), so K is split down to that while
+// the tiles alone do not give the chip its 4096 waves.  Parts of a tile on
+// other workgroups have to meet through memory (2 us), so that split is for
+// tiles that would keep a CU for longer than that (real 13/67, split above
+// 1024 or 512 k: 208, 203 us; complex 8/24, above 512 or 256: no difference).
 struct FusedSplit {
     int kw = 1, split = 1, tiles = 0;
 };
-inline FusedSplit fused_split(const Op& o) {
+inline FusedSplit fused_split(const Op& o, bool real) {
     FusedSplit f;
     int K = 0;
     for (const GemmProblem& p : o.probs) {
         f.tiles += ((p.M + 15) / 16) * ((p.N + 15) / 16);
         K = std::max(K, p.K);
     }
-    while (f.kw < 16 && K > 64 * f.kw && (long long)f.tiles * f.kw < 4096) f.kw *= 2;
-    if (f.kw == 16 && K > 1024) f.split = std::min((K + 511) / 512, std::max(1, 512 / std::max(1, f.tiles)));
+    const int kwave = real ? 128 : 64;
+    while (f.kw < 4 && K > kwave * f.kw && (long long)f.tiles * f.kw < 4096) f.kw *= 2;
+    if (f.kw == 4 && K > 512)
+        f.split = std::min((K + 4 * kwave - 1) / (4 * kwave), std::max(1, 1024 / std::max(1, f.tiles)));
     return f;
 }
 
-// The list as the schedule sees it: a fused GEMM that is split over workgroups
-// becomes its partial products (into a buffer of its own, number nbufs + i) and
-// their sum.  orig[k]: the operation that entry k comes from.
-struct ExpandedOps {
-    std::vector<Op> ops;
-    std::vector<int> orig;
-    std::vector<char> small;
-};
-inline ExpandedOps expand_ops(const std::vector<Op>& ops, const std::vector<char>& alone, bool real, int nbufs) {
-    ExpandedOps x;
-    for (size_t k = 0; k < ops.size(); ++k) {
-        const Op& o = ops[k];
-        const bool small = !alone[k] && fusable(o, real);
-        // the schedule needs the buffers and sizes only, not the tables
-        Op e;
-        e.kind = o.kind;
-        e.name = o.name;
-        e.dst = o.dst;
-        e.src = o.src;
-        e.src2 = o.src2;
-        e.srcT = o.srcT;
-        e.beta = o.beta;
-        e.n = o.n;
-        if (small && o.kind == OP_GEMM && fused_split(o).split > 1) {
-            Op r;
-            r.kind = OP_REDUCE;
-            r.name = o.name;
-            r.dst = o.dst;
-            r.src = nbufs;
-            r.beta = o.beta;
-            e.dst = nbufs++;
-            e.beta = 0;
-            x.ops.push_back(e);
-            x.ops.push_back(r);
-            x.orig.insert(x.orig.end(), 2, (int)k);
-            x.small.insert(x.small.end(), 2, 1);
-        } else {
-            x.ops.push_back(e);
-            x.orig.push_back((int)k);
-            x.small.push_back(small);
-        }
-    }
-    return x;
+// The operations that may share a launch.
+inline std::vector<char> small_ops(const std::vector<Op>& ops, const std::vector<char>& alone, bool real) {
+    std::vector<char> small(ops.size());
+    for (size_t k = 0; k < ops.size(); ++k) small[k] = !alone[k] && fusable(ops[k], real);
+    return small;
 }
 
-// The schedule of an expanded list (steps hold its entry numbers).
+// The schedule of an operation list.
 // Elementwise operations on the same destination are chained when nothing
 // reads the destination between them and the chains can still be ordered.
 // Then, repeatedly: all fusable chains that are ready form one fused step; if
 // there are none, every other ready operation follows as a step of its own, in
 // list order.
-inline std::vector<ScheduleStep> build_schedule(const ExpandedOps& x) {
-    constexpr size_t kMaxChain = 8;
-    const std::vector<Op>& ops = x.ops;
-    const std::vector<char>& small = x.small;
+inline std::vector<ScheduleStep> build_schedule(const std::vector<Op>& ops, const std::vector<char>& small) {
+    constexpr size_t kChain = 8;   // most operations of a chain (their descriptors share a workgroup's LDS)
     const int n = (int)ops.size();
     const std::vector<std::vector<int>> deps = op_dependencies(ops);
-    auto elementwise = [&](int k) { return small[k] && ops[k].kind != OP_GEMM && ops[k].kind != OP_REDUCE; };
+    auto elementwise = [&](int k) { return small[k] && ops[k].kind != OP_GEMM; };
     auto reads = [&](int k, int b) {
         const Op& o = ops[k];
         return o.src == b || o.src2 == b || std::find(o.srcT.begin(), o.srcT.end(), b) != o.srcT.end();
@@ -205,7 +171,7 @@ inline std::vector<ScheduleStep> build_schedule(const ExpandedOps& x) {
                 read_since = true;
             }
         }
-        if (elementwise(k) && w >= 0 && !read_since && elementwise(w) && ops[w].n == ops[k].n && !reads(k, ops[k].dst) && chain[node[w]].size() < kMaxChain &&
+        if (elementwise(k) && w >= 0 && !read_since && elementwise(w) && ops[w].n == ops[k].n && !reads(k, ops[k].dst) && chain[node[w]].size() < kChain &&
             chain[node[w]].back() == w) {
             node[k] = node[w];
             if (!orderable(k)) node[k] = -1;

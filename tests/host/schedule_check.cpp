@@ -19,11 +19,10 @@ static bool touches(const Op& o, int b) {
     return false;
 }
 
-static int check(const std::vector<Op>& list, const std::vector<char>& alone, bool real, int nbufs, int* nsteps,
+static int check(const std::vector<Op>& list, const std::vector<char>& alone, bool real, int* nsteps,
                  int* nfused) {
-    const ExpandedOps x = expand_ops(list, alone, real, nbufs);
-    const std::vector<ScheduleStep> st = build_schedule(x);
-    const std::vector<Op>& ops = x.ops;
+    const std::vector<Op>& ops = list;
+    const std::vector<ScheduleStep> st = build_schedule(ops, small_ops(ops, alone, real));
     const int n = (int)ops.size();
     std::vector<int> step(n, -1), pos(n, -1), chain(n, -1);
     int bad = 0, id = 0;
@@ -39,31 +38,17 @@ static int check(const std::vector<Op>& list, const std::vector<char>& alone, bo
                 step[c[q]] = (int)k;
                 pos[c[q]] = (int)q;
                 chain[c[q]] = id;
-                const int j = x.orig[c[q]];
+                const int j = c[q];
                 if (st[k].fused && (alone[j] || !fusable(list[j], real))) ++bad;
-                if (!st[k].fused && o.kind == OP_REDUCE) ++bad;
-                if (c.size() > 1 && (o.kind == OP_GEMM || o.kind == OP_REDUCE || o.dst != ops[c[0]].dst || o.n != ops[c[0]].n)) ++bad;
+                if (c.size() > 1 && (o.kind == OP_GEMM || o.dst != ops[c[0]].dst || o.n != ops[c[0]].n)) ++bad;
             }
             ++id;
         }
     }
-    // entries are the operations in order; a split GEMM is partial products into a new buffer, then their sum
-    int next = 0, buf = nbufs;
-    for (size_t j = 0; j < list.size(); ++j) {
-        if (next >= n || x.orig[next] != (int)j) return bad + 1;
-        const bool split = next + 1 < n && x.orig[next + 1] == (int)j;
-        if (split) {
-            if (list[j].kind != OP_GEMM || ops[next].dst != buf || ops[next + 1].src != buf ||
-                ops[next + 1].kind != OP_REDUCE || ops[next + 1].beta != list[j].beta || ops[next].beta)
-                ++bad;
-            ++buf;
-        }
-        if (ops[next + split].dst != list[j].dst || ops[next].src != list[j].src || ops[next].src2 != list[j].src2) ++bad;
-        const FusedSplit f = fused_split(list[j]);
-        if (f.kw < 1 || f.kw > 16 || (f.kw & (f.kw - 1)) || f.split < 1) ++bad;
-        next += 1 + split;
+    for (const Op& o : list) {
+        const FusedSplit f = fused_split(o, real);
+        if (f.kw < 1 || f.kw > 4 || (f.kw & (f.kw - 1)) || f.split < 1 || (f.split > 1 && f.kw != 4)) ++bad;
     }
-    if (next != n) ++bad;
     for (int k = 0; k < n; ++k) {
         if (step[k] < 0) ++bad;
         // two operations of which one writes a buffer the other touches keep their order
@@ -92,7 +77,7 @@ extern "C" int schedule_check(int nocc, int nvirt, int G, const int32_t* irrep, 
         std::vector<char> alone(L->size(), 0);
         if (keep_every > 0)
             for (size_t k = 0; k < alone.size(); k += keep_every) alone[k] = 1;
-        bad += check(*L, alone, real != 0, (int)P.bufs.size(), &steps[i], &fused[i]);
+        bad += check(*L, alone, real != 0, &steps[i], &fused[i]);
         count[i] = (int)L->size();
         ++i;
     }

@@ -1,5 +1,5 @@
 """Fused launches of small operations (k_fused): residuals against the dense oracle at sizes around the 16 x 16 tiles,
-the 1024-element chunks and the K split over waves and workgroups (K = o v^2 / 2 up to 4.5 k here), in complex and
+the 256-element chunks and the K split over waves and workgroups (K = o v^2 / 2 up to 4.5 k here), in complex and
 real arithmetic; and against the same operations on kernels of their own (profiling puts every operation there).
 Both sums have at most a few thousand terms of size <= max|R|, so 1e-12 of max|R| is asked, as in the parity tests."""
 import numpy as np
@@ -58,4 +58,34 @@ def test_fused_residual_matches_oracle_and_single_kernels(nocc, nvirt, nirrep, r
     for r in runs:
         for a, b in zip(r, ref):
             assert a.size == 0 or np.abs(a - b).max() <= 1e-12 * scale
+    ctx.destroy()
+
+
+@pytest.mark.parametrize("real", [False, True])
+def test_parts_of_a_tile_meet_in_order_on_every_pass(real):
+    """Tiles split over workgroups (K = 2.3 k and 4.6 k): the counters of arrived parts are clear again after each pass,
+    and the parts are added in order whoever comes last, so every pass gives the same bits."""
+    import torch
+    import paper_2004_03682_amd as F
+    s = fsgen.make_system(8, 34, 1, 0.05, 92, real=real)
+    ctx = F.Context.from_system(s, precision="real_fp64" if real else "fp64")
+    for C in fsgen.CLASSES:
+        buf, _ = fsgen.class_buffer(s, C)
+        ctx.set_integrals(C, _dev(fsgen.real_buffer(buf) if real else buf))
+    t1, t2 = _random_t(s, np.random.default_rng(34), real)
+    p1, p2 = LR.pack_t1(s, t1), LR.pack_t2(s, t2)
+    if real:
+        p1, p2 = p1.real, p2.real
+    d1, d2 = _dev(p1), _dev(p2)
+    first = None
+    for _ in range(20):
+        r1, r2 = torch.full_like(d1, 3.0), torch.full_like(d2, 3.0)
+        ctx.build_residual(d1, d2, r1, r2)
+        got = r1.cpu(), r2.cpu()
+        first = first or got
+        assert torch.equal(got[0], first[0]) and torch.equal(got[1], first[1])
+    R1, R2 = ccsd.residual(ccsd.Dense(s), t1, t2)
+    scale = max(np.abs(R1).max(), np.abs(R2).max())
+    for a, b in zip(first, (LR.pack_t1(s, R1), LR.pack_t2(s, R2))):
+        assert np.abs(a.numpy() - b).max() <= 1e-12 * scale
     ctx.destroy()
