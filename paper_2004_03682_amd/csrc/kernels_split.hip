@@ -41,6 +41,13 @@ __device__ inline uint32_t bf16_bits(float f) {
 }
 __device__ inline double bf16_value(uint32_t h) { return (double)__uint_as_float(h << 16); }
 
+typedef __attribute__((address_space(3))) void lds_void;
+
+// every load of this thread has arrived (also in the LDS)
+__device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+// this wave's LDS reads are done, then the workgroup barrier
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 }  // namespace
 
 template <bool BF>
@@ -119,8 +126,20 @@ __global__ __launch_bounds__(256) void k_split(const double2* __restrict__ src, 
 // operand layout itself), one k block ahead; only A goes through LDS.  This
 // takes the B stores and B fragment reads off the LDS, which otherwise
 // carries more bytes per MFMA than it can serve.
+//
+// bf16 without BD: both operands go straight from memory into the LDS
+// (16 bytes per lane; the swizzle is in the source addresses), and the next k
+// block's loads start as soon as the last fragments of this one are in
+// registers, behind the matrix work of the leading piece of A and the FP64
+// sums.  Without the staging registers a 64 x 64 tile fits twice on a CU (248
+// instead of 296 registers), so one workgroup's loads, LDS reads and FP64
+// sums overlap the other's matrix work.  What bounds it then is the traffic
+// from the L2 (7.5-10 TB/s over all tiles).  Per call at 30 occupied / 200
+// virtual spinors in eight irreps, before -> after: W.U and ring (64 x 64)
+// 251 -> 176 us each (27 Gflop), t1-dressed ovvv (32 x 32) 253 -> 118 us,
+// ladder (64 x 32) 254 -> 231 us.
 template <bool BF, int BM, int BN, int WM, int WN, int ROLE, bool BD>
-__global__ __launch_bounds__(256) void k_zgemm_split(const void* __restrict__ Av, long long sA,
+__global__ __launch_bounds__(256, (BF && !BD ? (BM + BN == 128 ? 2 : BM + BN == 96 ? 3 : 4) : 1)) void k_zgemm_split(const void* __restrict__ Av, long long sA,
                                                      const void* __restrict__ Bv, long long sB,
                                                      double2* __restrict__ C, const MProb* __restrict__ probs,
                                                      const ZTile* __restrict__ tiles, double ar, double ai, int beta) {
@@ -161,8 +180,29 @@ __global__ __launch_bounds__(256) void k_zgemm_split(const void* __restrict__ Av
     const int lr = lane & 15, kq = lane >> 4;
     auto swz = [](int r) { return BF ? (((r >> 1) + (r >> 3)) & 3) : 0; };   // r: row mod 16
     const int sl = swz(lr);
-    u4v ra[AVT], rb[BD ? 1 : BVT];
+    constexpr bool DMA = BF && !BD;
+    u4v ra[DMA ? 1 : AVT], rb[BD || DMA ? 1 : BVT];
     u4v gb[NPC][2][FN][FV];   // BD: the next k block's B fragments
+    // DMA: chunk v = 256 u + thread of an operand's stage is plane v / (4 rows),
+    // row (v / 4) mod rows, position v mod 4 in the row
+    auto dma = [&](const unsigned char* g, unsigned char* l) {
+        __builtin_amdgcn_global_load_lds((const void*)g, (lds_void*)l, 16, 0, 0);
+    };
+    auto offset_in = [&](int rows) {
+        const int w = tid % (rows * 4), r = w >> 2;
+        return (long long)(r * ROWB + (((w & 3) ^ swz(r & 15)) * 16));
+    };
+    const unsigned char* dA = Ab + (DMA ? offset_in(BM) : 0);
+    const unsigned char* dB = Bb + (DMA ? offset_in(BN) : 0);
+    auto issue = [&](int kb) {
+        static_assert(!DMA || (AVEC % kT == 0 && BVEC % kT == 0 && VPR == 4), "whole load instructions");
+#pragma unroll
+        for (int u = 0; u < AVT; ++u)
+            dma(dA + (long long)((u * kT + wave * 64) / (BM * VPR)) * sA * ES + kb * stepA, ldsA + (u * kT + wave * 64) * 16);
+#pragma unroll
+        for (int u = 0; u < BVT; ++u)
+            dma(dB + (long long)((u * kT + wave * 64) / (BN * VPR)) * sB * ES + kb * stepB, ldsB + (u * kT + wave * 64) * 16);
+    };
     auto load = [&](int kb) {
 #pragma unroll
         for (int u = 0; u < AVT; ++u) {
@@ -224,11 +264,19 @@ __global__ __launch_bounds__(256) void k_zgemm_split(const void* __restrict__ Av
 #pragma unroll
             for (int q = 0; q < 4; ++q) dr[i][j][q] = di[i][j][q] = 0.0;
 
-    if (nkb > 0) load(0);
+    if (nkb > 0) {
+        if constexpr (DMA) issue(0);
+        else load(0);
+    }
     for (int kb = 0; kb < nkb; ++kb) {
-        __syncthreads();
-        store();
-        __syncthreads();
+        if constexpr (DMA) {
+            wait_loads();
+            lds_barrier();
+        } else {
+            __syncthreads();
+            store();
+            __syncthreads();
+        }
         // fragments: lane (lr, kq) holds k = 8*kq .. 8*kq+7 of row/column lr
         u4v fb[NPC][2][FN][FV];
         if constexpr (BD) {
@@ -241,8 +289,15 @@ __global__ __launch_bounds__(256) void k_zgemm_split(const void* __restrict__ Av
 #pragma unroll
                         for (int h = 0; h < FV; ++h) fb[pc][ri][j][h] = gb[pc][ri][j][h];
         }
-        if (kb + 1 < nkb) load(kb + 1);
-        if (!wave_live) continue;
+        if constexpr (!DMA)
+            if (kb + 1 < nkb) load(kb + 1);
+        if (!wave_live) {
+            if constexpr (DMA) {
+                lds_barrier();
+                if (kb + 1 < nkb) issue(kb + 1);
+            }
+            continue;
+        }
         if constexpr (!BD) {
 #pragma unroll
             for (int pc = 0; pc < NPC; ++pc)
@@ -276,6 +331,11 @@ __global__ __launch_bounds__(256) void k_zgemm_split(const void* __restrict__ Av
                     for (int h = 0; h < FV; ++h)
                         fa[ri][i][h] = *(const u4v*)(ldsA + ((2 * pa + ri) * BM + wm0 + i * 16 + lr) * PITCH +
                                                      ((kq * FV + h) ^ sl) * 16);
+            if constexpr (DMA)
+                if (pa == 0) {   // the stage is read: the next k block may replace it
+                    lds_barrier();
+                    if (kb + 1 < nkb) issue(kb + 1);
+                }
 #pragma unroll
             for (int pb = NPC - 1 - pa; pb >= 0; --pb) {
 #pragma unroll

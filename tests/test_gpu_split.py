@@ -78,6 +78,16 @@ def test_split_gemm_long_k_and_edges(prec):
         assert np.all(err <= bound + 1e-15 * np.abs(ref)), (prec, M, N, K, beta)
 
 
+@pytest.mark.parametrize("cfg", range(8))
+@pytest.mark.parametrize("K", [32, 33, 64, 65, 96, 1000])
+def test_split_bf16_k_blocks_follow_each_other(cfg, K):
+    # one stage, refilled behind the last matrix work of each k block: counts around one, two and three blocks, with
+    # waves that have no rows (M = 17) or columns (N = 33) and only help to load
+    for (M, N) in [(17, 33), (64, 97)]:
+        err, bound, _ = _run("split_bf16", cfg, M, N, K, 0, 1, 0, 0, 0, seed=K)
+        assert np.all(err <= bound), (cfg, M, N, K, float((err / bound).max()))
+
+
 def test_split_bf16_accuracy_statistics():
     # typical element error: far below the worst-case bound (pieces and pair order working)
     err, bound, _ = _run("split_bf16", 0, 96, 96, 1024, 0, 1, 0, 0, 0, seed=3)
