@@ -580,6 +580,8 @@ struct fscc_ctx {
             // a split-precision GEMM and a reorder with a forced traversal have kernels of their own
             if (o.kind == OP_GEMM && prec != FSCC_FP64 && L.g[k].mx && L.g[k].mx->prec == prec) alone[k] = 1;
             if (o.kind == OP_GATHER && gather_forced) alone[k] = 1;
+            // a large reorder for which tuning found a better traversal keeps it
+            if (o.kind == OP_GATHER && (o.use_rtiles || o.use_gtiles) && !fusable(o, real)) alone[k] = 1;
         }
         S.steps = build_schedule(ops, small_ops(ops, alone, real));
         S.in_fused.assign(ops.size(), 0);

@@ -80,7 +80,7 @@ struct ScheduleStep {
 //     to share a launch's cost, and twice the traffic pays: 13/67 in three
 //     irreps 207 us at 48 MB and 0.2 Gflop, 186 us at 96 MB and 0.4 Gflop;
 //   * elementwise operations and reorders of up to 2^19 elements: above,
-//     their own launch costs less than 5 % of their time.
+//     their own launch costs less than 5 % of their time (chains: small_ops).
 inline bool fusable(const Op& o, bool real) {
     if (o.kind != OP_GEMM) return o.n <= (1 << 19);
     double bytes = 0.0, flops = 0.0;
@@ -116,18 +116,24 @@ inline FusedSplit fused_split(const Op& o, bool real) {
     return f;
 }
 
-// The operations that may share a launch.
+// What may share a launch: 0: an operation on its own kernel, 1: any small
+// one, 2: a larger elementwise operation or reorder, in a chain only: a chain
+// reads and writes its destination once (r2 of 40 occupied / 300 virtual
+// spinors in 16 irreps collects five terms in 179 us instead of 218; the
+// iteration 5040 -> 4999 us, 29/174 in seven irreps 4321 -> 4255, the (0,1)
+// sector step 1860 -> 1780).
 inline std::vector<char> small_ops(const std::vector<Op>& ops, const std::vector<char>& alone, bool real) {
-    std::vector<char> small(ops.size());
-    for (size_t k = 0; k < ops.size(); ++k) small[k] = !alone[k] && fusable(ops[k], real);
+    std::vector<char> small(ops.size(), 0);
+    for (size_t k = 0; k < ops.size(); ++k)
+        if (!alone[k]) small[k] = fusable(ops[k], real) ? 1 : ops[k].kind != OP_GEMM ? 2 : 0;
     return small;
 }
 
 // The schedule of an operation list.
 // Elementwise operations on the same destination are chained when nothing
 // reads the destination between them and the chains can still be ordered.
-// Then, repeatedly: all fusable chains that are ready form one fused step; if
-// there are none, every other ready operation follows as a step of its own, in
+// Then, repeatedly: all small operations and all chains that are ready form one
+// fused step; if there are none, every other ready operation follows as a step of its own, in
 // list order.
 inline std::vector<ScheduleStep> build_schedule(const std::vector<Op>& ops, const std::vector<char>& small) {
     constexpr size_t kChain = 8;   // most operations of a chain (their descriptors share a workgroup's LDS)
@@ -199,7 +205,7 @@ inline std::vector<ScheduleStep> build_schedule(const std::vector<Op>& ops, cons
     for (int left = m; left > 0;) {
         std::vector<int> fuse, single;
         for (int c = 0; c < m; ++c)
-            if (ready(c)) (small[chain[c][0]] ? fuse : single).push_back(c);
+            if (ready(c)) (small[chain[c][0]] == 1 || chain[c].size() > 1 ? fuse : single).push_back(c);
         if (!fuse.empty()) {
             ScheduleStep s;
             s.fused = true;

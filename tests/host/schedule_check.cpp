@@ -39,7 +39,7 @@ static int check(const std::vector<Op>& list, const std::vector<char>& alone, bo
                 pos[c[q]] = (int)q;
                 chain[c[q]] = id;
                 const int j = c[q];
-                if (st[k].fused && (alone[j] || !fusable(list[j], real))) ++bad;
+                if (st[k].fused && (alone[j] || !(fusable(list[j], real) || (c.size() > 1 && o.kind != OP_GEMM)))) ++bad;
                 if (c.size() > 1 && (o.kind == OP_GEMM || o.dst != ops[c[0]].dst || o.n != ops[c[0]].n)) ++bad;
             }
             ++id;
