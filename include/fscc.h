@@ -319,8 +319,10 @@ fscc_status fscc_profile(fscc_ctx *ctx, int enable);
 /* While profiling is enabled, record events only around operation k
  * (k = -1: every operation, the default).  Events are read back when the
  * next residual evaluation starts or by fscc_op_info / fscc_profile, so
- * profiling adds no stream synchronisation; timing one operation leaves the
- * others' launch sequence untouched.  FSCC_EINVAL if k is not an operation. */
+ * profiling adds no stream synchronisation.  An operation that normally runs
+ * in a launch shared with others cannot be timed there: selecting one (or -1)
+ * puts every operation of its list on its own kernel, and selecting any other
+ * leaves the launch sequence untouched.  FSCC_EINVAL if k is not an operation. */
 fscc_status fscc_profile_select(fscc_ctx *ctx, int k);
 fscc_status fscc_op_count(const fscc_ctx *ctx, int *count);
 /* Kind and algorithmic bytes of one call of operation k (host outputs):
@@ -384,8 +386,9 @@ fscc_status fscc_autotune_cached(const fscc_ctx *ctx, int *from_cache);
  * along its rows; a term without an affine form on a tile uses its map
  * (gathers with a second operand fall back to tiled = 1).  Complex contexts;
  * a real context always uses storage order.  The results are bitwise
- * identical.  Replaces the choice fscc_autotune(ctx, 1) made.  FSCC_EINVAL for
- * another value. */
+ * identical.  Replaces the choice fscc_autotune(ctx, 1) made.  With 0, reorders
+ * that share a launch with other operations do so in storage order; with 1 or
+ * 2 every reorder runs on its own kernel.  FSCC_EINVAL for another value. */
 fscc_status fscc_gather_order(fscc_ctx *ctx, int tiled);
 
 /* MFMA tile ids of fscc_zgemm / fscc_gemm_config may carry this bit: the
