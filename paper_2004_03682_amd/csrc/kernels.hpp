@@ -236,6 +236,7 @@ struct FItem {
     int op, first, nops, pad;
 };
 constexpr int kMaxChain = 8;
+hipError_t load_fused(bool real);
 hipError_t launch_fused(const FItem* items, int nitems, const FOp* ops, const FIo& io, bool real, hipStream_t st);
 
 hipError_t launch_zero(double2* dst, long long n, hipStream_t st);

@@ -379,6 +379,13 @@ __global__ __launch_bounds__(kFusedThreads, 4) void k_fused(const FItem* __restr
 
 }  // namespace
 
+// Loads the kernel's code onto the current device, which its first launch would
+// do otherwise (some milliseconds, once per process).
+hipError_t load_fused(bool real) {
+    hipFuncAttributes a;
+    return hipFuncGetAttributes(&a, real ? (const void*)k_fused<double> : (const void*)k_fused<double2>);
+}
+
 hipError_t launch_fused(const FItem* items, int nitems, const FOp* ops, const FIo& io, bool real, hipStream_t st) {
     if (nitems <= 0) return hipSuccess;
     if (real) k_fused<double><<<nitems, kFusedThreads, 0, st>>>(items, ops, io);

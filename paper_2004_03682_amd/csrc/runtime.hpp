@@ -680,6 +680,7 @@ struct fscc_ctx {
             std::memcpy(h.data() + o2, probs.data(), probs.size() * sizeof(ZProb));
             std::memcpy(h.data() + o3, tiles.data(), tiles.size() * sizeof(ZTile));
             hip_check(hipMemcpy(m, h.data(), bytes, hipMemcpyHostToDevice), "fused tables");
+            hip_check(load_fused(real), "fused kernel");
             S.fops = (FOp*)m;
             S.items = (FItem*)(m + o1);
         }

@@ -117,7 +117,8 @@ inline FusedSplit fused_split(const Op& o, bool real) {
 }
 
 // What may share a launch: 0: an operation on its own kernel, 1: any small
-// one, 2: a larger elementwise operation or reorder, in a chain only: a chain
+// one, 2: a larger elementwise operation or reorder (up to 2^30 elements, the
+// kernel counts in 32 bits), in a chain only: a chain
 // reads and writes its destination once (r2 of 40 occupied / 300 virtual
 // spinors in 16 irreps collects five terms in 179 us instead of 218; the
 // iteration 5040 -> 4999 us, 29/174 in seven irreps 4321 -> 4255, the (0,1)
@@ -125,7 +126,7 @@ inline FusedSplit fused_split(const Op& o, bool real) {
 inline std::vector<char> small_ops(const std::vector<Op>& ops, const std::vector<char>& alone, bool real) {
     std::vector<char> small(ops.size(), 0);
     for (size_t k = 0; k < ops.size(); ++k)
-        if (!alone[k]) small[k] = fusable(ops[k], real) ? 1 : ops[k].kind != OP_GEMM ? 2 : 0;
+        if (!alone[k]) small[k] = fusable(ops[k], real) ? 1 : ops[k].kind != OP_GEMM && ops[k].n <= (1 << 30) ? 2 : 0;
     return small;
 }
 

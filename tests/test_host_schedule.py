@@ -1,5 +1,5 @@
 """Launch schedules of the operation lists, on the CPU: small operations share fused launches and chains, and every
-operation still runs after everything it depends on (dependencies re-derived from the buffers in the checker),
+operation still runs after everything it depends on (dependencies re-derived from the buffers in C++),
 for small systems where everything is fused, large ones where little is, and with operations kept on their own
 kernels."""
 import ctypes
@@ -17,7 +17,7 @@ CSRC = os.path.join(os.path.dirname(HERE), "paper_2004_03682_amd", "csrc")
 
 
 @pytest.fixture(scope="module")
-def checker(tmp_path_factory):
+def lib(tmp_path_factory):
     gxx = shutil.which("g++")
     if gxx is None:
         pytest.skip("g++ not available")
@@ -35,7 +35,7 @@ SYSTEMS = [(2, 3, 1, 0), (8, 24, 1, 0), (6, 14, 4, 5), (9, 37, 5, 6), (13, 67, 3
 @pytest.mark.parametrize("real", [0, 1])
 @pytest.mark.parametrize("keep_every", [0, 1, 3])
 @pytest.mark.parametrize("spec", SYSTEMS)
-def test_schedules_respect_every_dependency(checker, spec, keep_every, real):
+def test_schedules_respect_every_dependency(lib, spec, keep_every, real):
     nocc, nvirt, nirrep, nact = spec
     s = fsgen.make_system(nocc, nvirt, nirrep, 0.05, 11, nact=nact)
     irr = np.ascontiguousarray(s.irrep, dtype=np.int32)
@@ -43,7 +43,7 @@ def test_schedules_respect_every_dependency(checker, spec, keep_every, real):
     act = np.ascontiguousarray(s.active, dtype=np.int32)
     steps, fused, count = ((ctypes.c_int * 5)() for _ in range(3))
     ptr = lambda a: a.ctypes.data_as(ctypes.c_void_p)  # noqa: E731
-    bad = checker.schedule_check(nocc, nvirt, nirrep, ptr(irr), ptr(eps), len(act), ptr(act), keep_every, real, steps,
+    bad = lib.schedule_check(nocc, nvirt, nirrep, ptr(irr), ptr(eps), len(act), ptr(act), keep_every, real, steps,
                                  fused, count)
     assert bad == 0
     print(list(count), list(steps), list(fused))
