@@ -177,22 +177,23 @@ __global__ __launch_bounds__(256) void k_step(const T* __restrict__ t1, const T*
 // Bordered Pulay system over the slots order[0..m) (oldest first) of the
 // symmetric matrix B (leading dimension ldb): Gaussian elimination with
 // partial pivoting in FP64; a pivot below 1e-14 * max|A| drops the oldest
-// slot and the solve is repeated.  coef[slot] receives the coefficients (0 for
-// slots not used).  One wave: lane i holds row i in registers, the pivot row
-// is broadcast lane by lane, so a step costs a pivot search, one division and
-// one update per column (a single thread walking the matrix in LDS took 45 us
-// at nine vectors).  B, order and coef are in LDS; every lane of the wave
-// calls it and gets the number of dropped slots.
+// slot and the solve is repeated.  One wave: lane i holds row i in registers,
+// the pivot row is broadcast lane by lane, so a step costs a pivot search, one
+// division and one update per column (a single thread walking the matrix in
+// LDS took 45 us at nine vectors).  B and order are in LDS and only read.
+// Every lane of the wave calls it, gets the number of dropped slots and, in
+// *coef, the coefficient of slot `lane` (0 for a slot not used): the unknowns
+// go from lane to lane through registers, so no lane reads memory that another
+// has just written.
 template <int MAXM>
 __device__ int diis_solve(const double* B, int ldb, const int* order, int m, double* coef) {
     constexpr int SPAN = MAXM < 16 ? 8 : 16;   // lanes 0..MAXM hold rows: butterflies over 2 * SPAN lanes
     static_assert(MAXM < 2 * SPAN, "rows in one butterfly");
     const int lane = threadIdx.x & 63;
-    if (lane < ldb) coef[lane] = 0.0;
     for (int first = 0;; ++first) {
         const int k = m - first;
         if (k <= 1) {
-            if (lane == 0) coef[order[m - 1]] = 1.0;
+            *coef = lane == order[m - 1] ? 1.0 : 0.0;
             return first;
         }
         const int mine = order[first + min(lane, k - 1)];
@@ -243,15 +244,15 @@ __device__ int diis_solve(const double* B, int ldb, const int* order, int m, dou
             rhs -= f * lane_value(rhs, p);
         }
         if (singular) continue;
-        double x = 0.0;   // lane c: the unknown of column c
+        double mycoef = 0.0;
 #pragma unroll
         for (int c = MAXM; c >= 0; --c) {
             if (c >= k && c < MAXM) continue;
             const double xc = lane_value(rhs, piv[c]) / lane_value(a[c], piv[c]);
-            if (lane == c) x = xc;
+            if (c < k && lane == order[first + c]) mycoef = xc;   // column c is slot order[first + c]
             rhs -= a[c] * xc;
         }
-        if (lane < k) coef[mine] = x;
+        *coef = mycoef;
         return first;
     }
 }
@@ -267,7 +268,7 @@ __global__ __launch_bounds__(1024) void k_finish(const double* __restrict__ part
                                                 double* __restrict__ B, int newslot, DiisOrder ord,
                                                 double* __restrict__ coef, double* __restrict__ out) {
     constexpr int N = kDiisMax;
-    __shared__ double row[N + 1], Bs[N * N], cs[N];
+    __shared__ double row[N + 1], Bs[N * N];
     __shared__ int order[N];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     if (tid < N) order[tid] = tid < m ? ord.v[tid] : 0;
@@ -297,8 +298,9 @@ __global__ __launch_bounds__(1024) void k_finish(const double* __restrict__ part
     }
     __syncthreads();
     if (wave != 0) return;
-    const int dropped = !finite ? 0 : m <= 8 ? diis_solve<8>(Bs, N, order, m, cs) : diis_solve<N>(Bs, N, order, m, cs);
-    if (lane < N) coef[lane] = finite ? cs[lane] : 0.0;
+    double c = 0.0;   // of slot `lane`
+    const int dropped = !finite ? 0 : m <= 8 ? diis_solve<8>(Bs, N, order, m, &c) : diis_solve<N>(Bs, N, order, m, &c);
+    if (lane < N) coef[lane] = c;
     if (lane == 0) {
         coef[N] = finite ? 0.0 : 1.0;
         out[0] = mx;
@@ -494,7 +496,7 @@ __global__ __launch_bounds__(256) void k_bfinish(BState* __restrict__ state, con
                                                  double* __restrict__ coef, double* __restrict__ maxstep, double tol,
                                                  int* __restrict__ active, int* __restrict__ upd) {
     __shared__ double sh[kThreads];
-    __shared__ double row[8], Bs[64], cs[8];
+    __shared__ double row[8], Bs[64];
     __shared__ int ord[8];
     const int s = blockIdx.x;
     BState stt = state[s];
@@ -533,8 +535,9 @@ __global__ __launch_bounds__(256) void k_bfinish(BState* __restrict__ state, con
     }
     __syncthreads();
     if (threadIdx.x >= 64) return;
-    const int dropped = diis_solve<8>(Bs, 8, ord, m, cs);
-    if (threadIdx.x < 8) coef[(long long)s * 8 + threadIdx.x] = cs[threadIdx.x];
+    double c;   // of slot threadIdx.x
+    const int dropped = diis_solve<8>(Bs, 8, ord, m, &c);
+    if (threadIdx.x < 8) coef[(long long)s * 8 + threadIdx.x] = c;
     if (threadIdx.x != 0) return;
     stt.newest = nw;
     stt.count = max(1, m - dropped);

@@ -84,3 +84,41 @@ def test_dependent_steps_drop_to_the_newest_vector(real, depth):
         got = np.concatenate([t1.cpu().numpy(), t2.cpu().numpy()])
         assert np.abs(got - (t + r / D)).max() <= 1e-14 * np.abs(t).max(), it
     ctx.destroy()
+
+
+@pytest.mark.parametrize("nocc,nvirt,nirrep,repeat", [(2, 3, 1, 0), (4, 7, 1, 0), (4, 7, 1, 5)])
+@pytest.mark.parametrize("real", [False, True])
+@pytest.mark.parametrize("depth", [2, 3, 8, 9, 16])
+def test_every_slot_of_the_history_takes_its_coefficient(nocc, nvirt, nirrep, repeat, real, depth):
+    """The slots in use turn round the history twice, and with `repeat` every fifth step equals the one before: the
+    solve then drops the vectors up to the first of the two and the newest alone remains, in whatever slot it lies.
+    Vectors are compared while they are fewer than their components (the smallest system has 9 or 18)."""
+    import paper_2004_03682_amd as F
+    s = fsgen.make_system(nocc, nvirt, nirrep, 0.05, 79)
+    ctx = F.Context.from_system(s, precision="real_fp64" if real else "fp64")
+    D = np.concatenate([x.cpu().numpy() for x in ctx.denominators()])
+    comps = D.size * (1 if real else 2)
+    depth = min(depth, comps - 2)
+    ctx.diis_reset(depth)
+    n1 = ctx.n1
+    rng = np.random.default_rng(100 * nocc + depth)
+    hist = []
+    r = None
+    for it in range(2 * depth + 3):
+        t = _rand(rng, D.size, real)
+        if not (repeat and it % repeat == repeat - 1):
+            r = 1e-3 * _rand(rng, D.size, real)
+        t1, t2 = dev(t[:n1]), dev(t[n1:])
+        ctx.update_amplitudes(t1, t2, dev(r[:n1]), dev(r[n1:]))
+        e = r / D
+        same = [j for j, x in enumerate(hist) if np.array_equal(x[1], e)]
+        hist = (hist[same[-1] + 1:] if same else hist) + [(t + e, e)]
+        hist = hist[-depth:]
+        c = _pulay([x[1] for x in hist]) if len(hist) > 1 else [1.0]
+        ref = sum(a * x[0] for a, x in zip(c, hist))
+        got = np.concatenate([t1.cpu().numpy(), t2.cpu().numpy()])
+        # the vectors' condition: a few components more than vectors leave ~1e4 (squared in B, times 1e-16)
+        cond = np.linalg.cond(np.array([np.concatenate([x[1].real, x[1].imag]) / np.linalg.norm(x[1]) for x in hist]))
+        tol = 1e-10 + 1e-14 * cond ** 2
+        assert np.abs(got - ref).max() <= tol * max(1.0, np.abs(ref).max()), (it, cond)
+    ctx.destroy()
