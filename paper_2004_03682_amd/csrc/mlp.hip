@@ -254,7 +254,10 @@ __global__ __launch_bounds__(256, 2) void k_mlp_bwd(const float* __restrict__ P,
 // Bound by launch and load latency at these sizes: 128 rows per chunk give 1536
 // workgroups for a minibatch of 8192.  (With the rows unsplit, 16 and 4
 // workgroups walked all of them: 3.4 ms of a 3.75 ms training step on 8192
-// rows; the whole step now takes 0.14 ms.)
+// rows; the whole step now takes 0.14 ms.)  A column sum adds the sums of its
+// 32-row slices, so its longest chain of roundings is 32 + n / 2048 + 64 for n
+// rows (in one running sum it would be n / 64 + 64, which costs two digits at
+// half a million rows).
 constexpr int kGradTiles = 24, kGradBK = 32, kMaxChunks = 64;
 __global__ __launch_bounds__(256) void k_mlp_wgrad(const float* __restrict__ X, const float* __restrict__ h1,
                                                    const float* __restrict__ h2, const float* __restrict__ dh1,
@@ -306,9 +309,12 @@ __global__ __launch_bounds__(256) void k_mlp_wgrad(const float* __restrict__ X, 
         }
         __syncthreads();
         if (k0 + kGradBK < k_hi) fetch(k0 + kGradBK);
-        if (m0 == 0 && tid < 64)
+        if (m0 == 0 && tid < 64) {
+            float s = 0.f;
 #pragma unroll 8
-            for (int k = 0; k < kGradBK; ++k) bsum += Bs[k * LD + tid];
+            for (int k = 0; k < kGradBK; ++k) s += Bs[k * LD + tid];
+            bsum += s;
+        }
 #pragma unroll
         for (int k = 0; k < kGradBK; k += 4) {
             float a[2], b[2];

@@ -167,3 +167,28 @@ def test_row_tiles_and_gradient_chunks(rows):
     assert np.abs(got[:rows] - ref).max() <= 1e-4 * max(np.abs(ref).max(), 1e-30)
     assert (got[rows:] == 7.0).all()
     net.destroy()
+
+
+@pytest.mark.parametrize("log2n", [5, 13, 17, 19])
+def test_bias_gradients_of_large_minibatches(log2n):
+    """2^k copies of one row, relative loss: the weight of a row is 2^-k, so in exact arithmetic the gradient is that
+    of the single row.  A bias gradient is summed in slices of 32 rows, over the slices of a chunk (1/64 of the rows,
+    128 at least) and over the chunks: that many roundings of 2^-24 of the sum of magnitudes at most."""
+    _torch()
+    import paper_2004_03682_amd as F
+    n = 1 << log2n
+    u, r, D, t = (x[7:8] for x in _rows(3, 8))
+    net = F.MLP(seed=0)
+    net.set_params(_params(30))
+    net.loss_grad(dev(u), dev(r), dev(D), dev(t), mode=0)
+    one = net.get_grad().astype(np.float64)
+    net.loss_grad(dev(np.repeat(u, n)), dev(np.repeat(r, n)), dev(np.repeat(D, n)), dev(np.repeat(t, n)), mode=0)
+    got = net.get_grad().astype(np.float64)
+    per = max(128, n // 64)
+    bound = (32 + per // 32 + n // per) * 2.0 ** -24
+    b1, b2, b3 = 8 * 256, 8 * 256 + 256 + 256 * 256, 8 * 256 + 256 + 256 * 256 + 256 + 256 * 4
+    for at, count in ((b1, 256), (b2, 256), (b3, 4)):
+        a, b = got[at:at + count], one[at:at + count]
+        assert np.abs(b).max() > 0.0
+        assert (np.abs(a - b) <= bound * np.abs(b)).all(), (at, np.abs(a / np.where(b == 0.0, 1.0, b) - 1.0).max())
+    net.destroy()
