@@ -699,8 +699,8 @@ fscc_status fscc_mlp_get_grad(fscc_mlp *net, float *host, size_t count);
 /* X[n][8] from u, r, D. */
 fscc_status fscc_ws_features(const fscc_c128 *u, const fscc_c128 *r, const double *D, size_t n, float *X,
                              void *hip_stream);
-/* Y[n][4] = network(X[n][8]) (row chunks of 2^20; allocates its scratch on
- * first use). */
+/* Y[n][4] = network(X[n][8]), without scratch.  Y may replace X from its start
+ * on (then in row chunks of 2^20 through a buffer allocated on first use). */
 fscc_status fscc_mlp_forward(fscc_mlp *net, const float *X, size_t n, float *Y);
 /* out = u + v + a v + b u from Y (Y may be NULL: out = u + v). */
 fscc_status fscc_ws_apply(const float *Y, const fscc_c128 *u, const fscc_c128 *r, const double *D, size_t n,

@@ -559,6 +559,7 @@ struct fscc_mlp {
           *gpart = nullptr;
     double *spart = nullptr, *lpart = nullptr, *bD = nullptr;
     double2 *bu = nullptr, *br = nullptr, *bt = nullptr;
+    float* yhold = nullptr;   // outputs of a chunk of rows that replace its inputs
     double* hloss = nullptr;
     std::string err;
 
@@ -575,7 +576,7 @@ struct fscc_mlp {
         if (st) (void)hipStreamSynchronize(st);
         else (void)hipDeviceSynchronize();
         free_train();
-        void* ps[] = {p, g, m, w};
+        void* ps[] = {p, g, m, w, yhold};
         for (void* q : ps)
             if (q) (void)hipFree(q);
         if (hloss) (void)hipHostFree(hloss);
@@ -781,8 +782,23 @@ fscc_status fscc_ws_gather(const void* src, size_t elem_bytes, const int64_t* id
 fscc_status fscc_mlp_forward(fscc_mlp* n, const float* X, size_t rows, float* Y) {
     if (!n || (rows && (!X || !Y))) return FSCC_EINVAL;
     if (!rows) return FSCC_OK;
-    // grids of at most 2^30 rows
     hipError_t e = hipSuccess;
+    if (X < Y + rows * F_OUT && Y < X + rows * F_IN) {
+        // Y over X: the workgroups of a launch read and write rows of each
+        // other's, so the outputs of 2^20 rows at a time wait in a buffer
+        // until the chunk's inputs have been read
+        const size_t ch = (size_t)1 << 20;
+        if (!n->yhold) e = dalloc(&n->yhold, ch * F_OUT);
+        for (size_t r0 = 0; r0 < rows && ok(e); r0 += ch) {
+            const size_t m = std::min(rows - r0, ch);
+            launch_fwd<false>(n->p, X + r0 * F_IN, (long long)m, nullptr, nullptr, n->yhold, n->st);
+            e = hipGetLastError();
+            if (ok(e))
+                e = hipMemcpyAsync(Y + r0 * F_OUT, n->yhold, m * F_OUT * sizeof(float), hipMemcpyDeviceToDevice, n->st);
+        }
+        return ok(e) ? FSCC_OK : herr(n, e, "forward");
+    }
+    // grids of at most 2^30 rows
     for (size_t r0 = 0; r0 < rows && ok(e); r0 += (size_t)1 << 30) {
         const size_t m = std::min(rows - r0, (size_t)1 << 30);
         launch_fwd<false>(n->p, X + r0 * F_IN, (long long)m, nullptr, nullptr, Y + r0 * F_OUT, n->st);

@@ -192,3 +192,19 @@ def test_bias_gradients_of_large_minibatches(log2n):
         assert np.abs(b).max() > 0.0
         assert (np.abs(a - b) <= bound * np.abs(b)).all(), (at, np.abs(a / np.where(b == 0.0, 1.0, b) - 1.0).max())
     net.destroy()
+
+
+@pytest.mark.parametrize("rows,shift", [(5, 0), (70, 0), (40001, 0), (40001, 32), ((1 << 20) + 77, 0)])
+def test_outputs_may_replace_the_inputs(rows, shift):
+    """Y in the memory of X (`shift` floats on, within the first row chunk): the same bits as with Y elsewhere."""
+    torch = _torch()
+    import paper_2004_03682_amd as F
+    net = F.MLP(seed=0)
+    net.set_params(_params(31))
+    X = torch.randn(rows, 8, dtype=torch.float32, device="cuda", generator=torch.Generator("cuda").manual_seed(rows))
+    Y = torch.empty(rows, 4, dtype=torch.float32, device="cuda")
+    net.forward(X, Y)
+    over = X.view(-1)[shift:shift + 4 * rows].view(rows, 4)
+    net.forward(X, over)
+    assert torch.equal(over, Y)
+    net.destroy()
