@@ -394,8 +394,9 @@ fscc_status fscc_gather_order(fscc_ctx *ctx, int tiled);
 /* MFMA tile ids of fscc_zgemm / fscc_gemm_config may carry this bit: the
  * complex product is formed from three real matrix products (Ar Br, Ai Bi,
  * (Ar + Ai)(Br + Bi); Re = P1 - P2, Im = P3 - P1 - P2) instead of four.
- * Contexts use it for every MFMA-tile GEMM unless the autotuner measured
- * the four-product form faster.  Rounding: the imaginary part's error bound
+ * Contexts use it for every GEMM on an MFMA tile of its own launch unless the
+ * autotuner measured the four-product form faster; a small GEMM that shares a
+ * launch with other operations always takes four.  Rounding: the imaginary part's error bound
  * grows from ~u sum|Ar Bi| + |Ai Br| to ~u sum(|Ar| + |Ai|)(|Br| + |Bi|). */
 #define FSCC_CFG_3M 256
 

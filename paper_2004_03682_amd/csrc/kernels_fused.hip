@@ -189,26 +189,28 @@ __device__ void fused_elements(const unsigned long long* __restrict__ lds, FOp o
     if (held && in) dst[at] = v;
 }
 
-// Accumulators of one 16 x 16 tile.  Complex: three real products (p = Ar Br,
-// q = Ai Bi, s = (Ar + Ai)(Br + Bi); re = p - q, im = s - p - q).
+// Accumulators of one 16 x 16 tile.  Complex: four real products, so that each
+// part of an output carries the rounding of its own terms only (three products
+// take the imaginary part from a difference as large as the real one).
 struct AccZ {
-    dbl4 p, q, s;
+    dbl4 re, im;
 };
 struct AccD {
     dbl4 p;
 };
-__device__ __forceinline__ void clear(AccZ& c) { c.p = c.q = c.s = dbl4{0.0, 0.0, 0.0, 0.0}; }
+__device__ __forceinline__ void clear(AccZ& c) { c.re = c.im = dbl4{0.0, 0.0, 0.0, 0.0}; }
 __device__ __forceinline__ void clear(AccD& c) { c.p = dbl4{0.0, 0.0, 0.0, 0.0}; }
 __device__ __forceinline__ void mma(AccZ& c, double2 a, double2 b) {
-    c.p = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, c.p, 0, 0, 0);
-    c.q = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.y, c.q, 0, 0, 0);
-    c.s = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x + a.y, b.x + b.y, c.s, 0, 0, 0);
+    c.re = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, c.re, 0, 0, 0);
+    c.im = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.y, c.im, 0, 0, 0);
+    c.re = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, -b.y, c.re, 0, 0, 0);
+    c.im = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.x, c.im, 0, 0, 0);
 }
 __device__ __forceinline__ void mma(AccD& c, double a, double b) {
     c.p = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c.p, 0, 0, 0);
 }
 __device__ __forceinline__ void put(double2* x, const AccZ& c, int e) {
-    *x = make_double2(c.p[e] - c.q[e], c.s[e] - c.p[e] - c.q[e]);
+    *x = make_double2(c.re[e], c.im[e]);
 }
 __device__ __forceinline__ void put(double* x, const AccD& c, int e) { *x = c.p[e]; }
 template <typename T>

@@ -89,3 +89,31 @@ def test_parts_of_a_tile_meet_in_order_on_every_pass(real):
     for a, b in zip(first, (LR.pack_t1(s, R1), LR.pack_t2(s, R2))):
         assert np.abs(a.numpy() - b).max() <= 1e-12 * scale
     ctx.destroy()
+
+
+@pytest.mark.parametrize("nocc,nvirt,nirrep", [(4, 16, 1), (6, 33, 2), (12, 26, 5)])
+def test_imaginary_parts_of_nearly_real_residuals_keep_their_digits(nocc, nvirt, nirrep):
+    """Imaginary parts 1e-9 of the real ones: each part of a product is summed by itself, so the imaginary parts of the
+    residual are as good to their own size as the real ones (the bound of the tests above, per part)."""
+    import torch
+    import paper_2004_03682_amd as F
+    small = 1e-9
+
+    def shrink(x):
+        return x.real + 1j * small * x.imag
+    s = fsgen.make_system(nocc, nvirt, nirrep, 0.05, 93)
+    ctx = F.Context.from_system(s)
+    for C in fsgen.CLASSES:
+        ctx.set_integrals(C, _dev(shrink(fsgen.class_buffer(s, C)[0])))
+    t1, t2 = (shrink(t) for t in _random_t(s, np.random.default_rng(nvirt), False))
+    d1, d2 = _dev(LR.pack_t1(s, t1)), _dev(LR.pack_t2(s, t2))
+    r1, r2 = torch.empty_like(d1), torch.empty_like(d2)
+    ctx.build_residual(d1, d2, r1, r2)
+    be = ccsd.Dense(s)
+    be.cls = {k: shrink(v) for k, v in be.cls.items()}
+    R1, R2 = ccsd.residual(be, t1, t2)
+    for part in (np.real, np.imag):
+        scale = max(np.abs(part(R1)).max(), np.abs(part(R2)).max())
+        for a, b in ((r1, LR.pack_t1(s, R1)), (r2, LR.pack_t2(s, R2))):
+            assert np.abs(part(a.cpu().numpy()) - part(b)).max() <= 1e-12 * scale, part.__name__
+    ctx.destroy()
