@@ -396,7 +396,9 @@ fscc_status fscc_gather_order(fscc_ctx *ctx, int tiled);
  * (Ar + Ai)(Br + Bi); Re = P1 - P2, Im = P3 - P1 - P2) instead of four.
  * Contexts use it for every GEMM on an MFMA tile of its own launch unless the
  * autotuner measured the four-product form faster; a small GEMM that shares a
- * launch with other operations always takes four.  Rounding: the imaginary part's error bound
+ * launch with other operations always takes four, and so, before tuning, does
+ * a thin one (K <= 64 and K N <= 1024, at most eight rows, or blocks that would
+ * leave almost half of 64 x 64 tiles empty).  Rounding: the imaginary part's error bound
  * grows from ~u sum|Ar Bi| + |Ai Br| to ~u sum(|Ar| + |Ai|)(|Br| + |Bi|). */
 #define FSCC_CFG_3M 256
 

@@ -64,6 +64,27 @@ std::vector<int> splitk_chunks(const Op& o, int cfg) {
     return c;
 }
 
+// May an MFMA tile form a complex product from three real ones by default?
+// Not for the products that the vector forms (four real products) are made
+// for: those a vector form takes (few columns of a short K, at most eight rows),
+// and small blocks that would leave almost half of 64 x 64 tiles empty.  Three
+// products take the imaginary part from a difference as large as the real part,
+// which costs nearly real operands those digits; a fourth costs these products
+// at most 10 % (W.t1.ovvv at 30 occupied / 200 virtual spinors in eight irreps
+// 108 -> 116 us), since memory or latency bounds them.  Of the products that
+// the estimate below moves from a vector form to a tile, this holds all but one
+// in 500 (320 systems, 4-44 occupied and 20-300 virtual spinors, 1-16 irreps).
+bool three_products(const Op& o) {
+    if (cfg_ok(o, ZCFG_TALL) || cfg_ok(o, ZCFG_RED) || cfg_ok(o, ZCFG_DOT)) return false;
+    double work = 0.0, padded = 0.0;
+    for (auto& p : o.probs) {
+        if (p.M > 256 || p.N > 256) return true;
+        work += (double)p.M * p.N * p.K;
+        padded += 4096.0 * ((p.M + 63) / 64) * ((p.N + 63) / 64) * p.K;
+    }
+    return padded < 1.75 * work;
+}
+
 // Estimated seconds of a GEMM operation in one kernel form (lds: LDS_STAGED or
 // LDS_DIRECT for the MFMA tiles).  The constants were fitted to the times of
 // every candidate of 522 operations of 14 systems (10-40 occupied, 67-300
@@ -120,7 +141,7 @@ double cfg_cost(const Op& o, int cfg, bool split, int lds, bool real) {
     const bool parts = *std::max_element(chunks.begin(), chunks.end()) > 1;
     // matrix-core cycles of one 16-deep slice of a tile on a SIMD (64 per
     // instruction; a SIMD whose wave is past the edge idles)
-    const double slice = 64.0 * 4 * (real ? 1 : 3) * (bm * bn / 1024.0);
+    const double slice = 64.0 * 4 * (real ? 1 : three_products(o) ? 3 : 4) * (bm * bn / 1024.0);
     double tiles = 0.0, slices = 0.0, longest = 0.0, cache = 0.0, partial = 0.0;
     for (size_t q = 0; q < o.probs.size(); ++q) {
         const GemmProblem& p = o.probs[q];
@@ -476,7 +497,7 @@ void plan_gemm(fscc_ctx* c, const Op& o, GemmDev& g, int cfg, int bk, bool allow
 // Cost-model default of a GEMM operation before (or without) autotuning.
 void plan_gemm_default(fscc_ctx* c, const Op& o, GemmDev& g) {
     const GemmChoice f = pick_form(o, c->real);
-    plan_gemm(c, o, g, f.cfg, 16, f.split);
+    plan_gemm(c, o, g, f.cfg, 16, f.split, three_products(o));
     g.lds = f.lds;
 }
 
@@ -2172,7 +2193,7 @@ fscc_status fscc_zgemm(int cfg, int bk, int tA, int tB, int cA, int cB, int M, i
         if (M > 0 && N > 0) o.probs.push_back(GemmProblem{0, 0, 0, M, N, K, std::max(lda, 1), std::max(ldb, 1), ldc});
         if (cfg >= 0 && !cfg_ok(o, cfg)) return FSCC_EINVAL;
         GemmDev g;
-        plan_gemm(c, o, g, cfg < 0 ? pick_cfg(o) : cfg, bk, allow_split != 0, cfg < 0 || m3);
+        plan_gemm(c, o, g, cfg < 0 ? pick_cfg(o) : cfg, bk, allow_split != 0, cfg < 0 ? three_products(o) : m3);
         g.lds = dl ? LDS_DIRECT : db ? LDS_DOUBLE : LDS_STAGED;
         hipError_t e;
         if (!g.split) {

@@ -85,15 +85,16 @@ fscc_status fscc_zgemm_noalloc(int cfg, int bk, int tA, int tB, int cA, int cB, 
         if (M > 0 && N > 0) o.probs.push_back(GemmProblem{0, 0, 0, M, N, K, std::max(lda, 1), std::max(ldb, 1), ldc});
         if (cfg >= 0 && !cfg_ok(o, cfg)) return free_call_fail(FSCC_EINVAL, "fscc_zgemm_noalloc: shape does not fit the tile form");
         const int form = cfg < 0 ? pick_cfg(o) : cfg;
+        const bool three = cfg < 0 ? three_products(o) : m3;
         GemmHost h;
-        plan_gemm_host(false, o, form, bk, allow_split != 0, cfg < 0 || m3, h);
+        plan_gemm_host(false, o, form, bk, allow_split != 0, three, h);
         // an optional K split whose partial sums do not fit runs unsplit
         // (same kernel, one K chunk per tile)
         if (plan_bytes(h) > kScratchBytes && h.g.split && allow_split)
-            plan_gemm_host(false, o, form, bk, false, cfg < 0 || m3, h);
+            plan_gemm_host(false, o, form, bk, false, three, h);
         // a form of the cost model's choosing whose tables do not fit: the
         // largest tile, which has the fewest
-        if (cfg < 0 && plan_bytes(h) > kScratchBytes) plan_gemm_host(false, o, ZCFG_64x64, bk, false, true, h);
+        if (cfg < 0 && plan_bytes(h) > kScratchBytes) plan_gemm_host(false, o, ZCFG_64x64, bk, false, three, h);
         if (plan_bytes(h) > kScratchBytes)
             return free_call_fail(FSCC_EINVAL, "fscc_zgemm_noalloc: plan needs " + std::to_string(plan_bytes(h)) +
                                                    " bytes of scratch, more than the static " +

@@ -819,6 +819,7 @@ struct GemmChoice {
 };
 GemmChoice pick_form(const Op& o, bool real);
 int pick_cfg(const Op& o, bool real = false);
+bool three_products(const Op& o);
 std::vector<ZTile> xcd_order(const std::vector<ZTile>& logical);
 void free_gemm(GemmDev& g);
 bool mixed_eligible(const Op& o, int prec);

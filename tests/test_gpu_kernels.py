@@ -181,3 +181,31 @@ def test_vector_forms_reject_shapes_they_do_not_fit():
                                    (DOT, 0, 0, 3, 3, 100), (DOT, 1, 1, 3, 3, 100), (DOT, 0, 1, 9, 3, 100)]:
         with pytest.raises(Exception):
             _run(M, N, K, tA, tB, 0, 0, cfg, 16, True, 0)
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+@pytest.mark.parametrize("M,N,K,tA,tB", [(3000, 7, 41, 0, 0), (40000, 3, 41, 0, 1), (12, 12, 7000, 0, 0), (12, 63, 9000, 0, 0),
+                                         (2, 12, 9000, 0, 1), (67, 67, 5000, 0, 0), (5000, 67, 10, 0, 0),
+                                         (82, 21, 4200, 1, 1), (110000, 21, 21, 0, 0),
+                                         (13, 144, 9000, 1, 0)])
+def test_default_form_of_thin_products_keeps_small_imaginary_parts(M, N, K, tA, tB, noalloc):
+    """Imaginary parts 1e-9 of the real ones; the default form of a thin product sums each part by itself:
+    error of an imaginary part at most (K + 16) roundings of its own terms."""
+    import torch
+    import paper_2004_03682_amd as F
+    rng = np.random.default_rng(M + K)
+    small = 1e-9
+    A, B = (x.real + 1j * small * x.imag for x in (_rand(rng, *((K, M) if tA else (M, K))),
+                                                  _rand(rng, *((N, K) if tB else (K, N)))))
+    a, b = (A.T if tA else A), (B.T if tB else B)
+    dA, dB = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
+    dC = torch.zeros(M, N, dtype=torch.complex128, device="cuda")
+    (F.zgemm_noalloc if noalloc else F.zgemm)(dA, dB, dC, M, N, K, A.shape[1], B.shape[1], N, bool(tA), bool(tB))
+    got = dC.cpu().numpy()
+    ab = a.real.astype(np.longdouble), b.real.astype(np.longdouble), a.imag.astype(np.longdouble), b.imag.astype(np.longdouble)
+    im = ab[0] @ ab[3] + ab[2] @ ab[1]
+    mag = np.abs(a.real) @ np.abs(b.imag) + np.abs(a.imag) @ np.abs(b.real)
+    err = np.abs(got.imag - im) / mag
+    assert err.max() <= (K + 16) * 2.0 ** -53, float(err.max())
+    re = ab[0] @ ab[1] - ab[2] @ ab[3]
+    assert (np.abs(got.real - re) <= (K + 16) * 2.0 ** -53 * (np.abs(a) @ np.abs(b))).all()
