@@ -501,7 +501,7 @@ fscc_status fscc_batch_step(fscc_batch* b, fscc_c128* t1, fscc_c128* t2, fscc_c1
             }
         } else {
             const void* key[4] = {t1, t2, r1, r2};
-            if (!b->gexec || b->ggen != c.sched_gen || !std::equal(key, key + 4, b->gkey)) {
+            if (!b->gexec || b->ggen != c.plan_gen || !std::equal(key, key + 4, b->gkey)) {
                 b->drop_graph();
                 hip_check(hipStreamSynchronize(c.st), "pre-capture sync");
                 hip_check(hipStreamBeginCapture(b->gst, hipStreamCaptureModeThreadLocal), "begin capture");
@@ -516,7 +516,7 @@ fscc_status fscc_batch_step(fscc_batch* b, fscc_c128* t1, fscc_c128* t2, fscc_c1
                 hip_check(hipStreamEndCapture(b->gst, &b->graph), "end capture");
                 hip_check(hipGraphInstantiate(&b->gexec, b->graph, nullptr, nullptr, 0), "graph instantiate");
                 std::copy(key, key + 4, b->gkey);
-                b->ggen = c.sched_gen;
+                b->ggen = c.plan_gen;
             }
             hip_check(hipGraphLaunch(b->gexec, c.st), "graph launch");
         }

@@ -326,8 +326,9 @@ void apply_precision(fscc_ctx* c, int prec) {
                 g.mx = plan_mixed(c, ops[k], prec, pick_mcfg(ops[k]));
             }
         }
-    if (c->prec != prec) ++c->sched_gen;
+    if (c->prec != prec) ++c->plan_gen;
     c->prec = prec;
+    c->prepare_schedules();
 }
 
 // Algorithmic bytes of one call of an operation: every destination element
@@ -629,7 +630,8 @@ void ctx_allocate(fscc_ctx* c, bool diis) {
     c->L02.base = (int)(P.ops.size() + P.ops01.size());
     if (diis) {   // a single system (a batch's plan runs every operation on its own kernel)
         setup_diis(c, c->diis[0], c->n1(), c->n2(), P.b_D1, P.b_D2);
-        for (OpList* L : {&c->L00, &c->L01p, &c->L01, &c->L02p, &c->L02}) c->prepare_schedule(*L);
+        c->fusing = true;
+        c->prepare_schedules();
     }
     if (P.has01) {
         setup_diis(c, c->diis[1], P.L_S1.total, P.L_S2.total, P.b_D1x, P.b_D2x);
@@ -1728,7 +1730,8 @@ fscc_status fscc_autotune(fscc_ctx* ctx, int level) {
     if (level < 0 || level > 2) return fail(ctx, FSCC_EINVAL, "autotune level must be 0, 1 or 2");
     return guarded(ctx, [&]() -> fscc_status {
         Plan& P = ctx->plan;
-        ++ctx->sched_gen;   // tables are freed and rebuilt: a graph captured with them is stale
+        ++ctx->plan_gen;   // tables are freed and rebuilt: a graph captured with them is stale
+        if (level < 2) ctx->drop_schedules();
         std::vector<OpList*> lists = {&ctx->L00, &ctx->L01, &ctx->L02};
         if (level == 0) {
             for (OpList* L : lists)
@@ -1743,6 +1746,7 @@ fscc_status fscc_autotune(fscc_ctx* ctx, int level) {
                     plan_gemm_default(ctx, o, L->g[k]);
                     L->g[k].mx = keep;
                 }
+            ctx->prepare_schedules();
             return FSCC_OK;
         }
         ctx->tune_from_cache = false;
@@ -1752,6 +1756,8 @@ fscc_status fscc_autotune(fscc_ctx* ctx, int level) {
             std::vector<std::array<int, 7>> cached;
             if (tune_load(ctx->tune_path, key, cached) && tune_apply(ctx, cached)) {
                 ctx->tune_from_cache = true;
+                ctx->drop_schedules();
+                ctx->prepare_schedules();
                 return FSCC_OK;
             }
         }
@@ -1922,6 +1928,7 @@ fscc_status fscc_autotune(fscc_ctx* ctx, int level) {
         for (size_t b = 0; b < P.bufs.size(); ++b)
             if (caller_buffer(P.bufs[b].kind)) ctx->dbuf[b] = nullptr;
         if (!key.empty()) tune_store(ctx->tune_path, key, tune_collect(ctx));
+        ctx->prepare_schedules();
         return FSCC_OK;
     });
 }
@@ -2016,8 +2023,9 @@ fscc_status fscc_vvvv_out_of_core(fscc_ctx* ctx, size_t staging_bytes) {
             void* d = ctx->dalloc(bytes);
             hip_check(hipMemcpy(d, ctx->sp.host, bytes, hipMemcpyHostToDevice), "operand to device");
             ctx->dbuf[b] = d;
-            ++ctx->sched_gen;
             ctx->free_stream();
+            ctx->drop_schedules();
+            ctx->prepare_schedules();
             return FSCC_OK;
         }
         if (ctx->sp.buf >= 0) return fail(ctx, FSCC_ESTATE, "VVVV is already out of device memory");
@@ -2068,11 +2076,11 @@ fscc_status fscc_gather_order(fscc_ctx* ctx, int tiled) {
                 o.use_rtiles = tiled == 2 && o.d_rtiles != nullptr;
                 o.use_gtiles = !o.use_rtiles && tiled >= 1 && o.d_gtiles != nullptr;
             }
-    if (ctx->gather_forced != (tiled != 0)) {
-        ctx->gather_forced = tiled != 0;
-        ++ctx->sched_gen;
-    }
-    return FSCC_OK;
+    ctx->gather_forced = tiled != 0;
+    return guarded(ctx, [&]() -> fscc_status {
+        ctx->prepare_schedules();
+        return FSCC_OK;
+    });
 }
 
 fscc_status fscc_level_shift(fscc_ctx* ctx, fscc_sector sector, double shift) {

@@ -9,6 +9,7 @@
 #include <cmath>
 #include <cstddef>
 #include <cstring>
+#include <map>
 #include <new>
 #include <stdexcept>
 #include <string>
@@ -109,7 +110,7 @@ struct StreamPlan {
 // other stream that k depends on (-1: none); rec[k]: an event is recorded
 // after k for such a wait.
 struct Schedule {
-    long long gen = -1;       // fscc_ctx::sched_gen it was built for
+    bool ready = false;
     std::vector<ScheduleStep> steps;
     std::vector<int> item0, nitems;
     FItem* items = nullptr;   // in mem
@@ -131,7 +132,11 @@ struct OpList {
     std::vector<double> ms;
     std::vector<int> calls;
     int base = 0;             // number of the first operation (fscc_op_info numbering)
-    Schedule fused, plain;    // with small operations fused; every operation on its own
+    // small operations fused, one schedule per fscc_ctx::schedule_key(): its tables
+    // keep their addresses when precision or traversal change and change back, so
+    // that a graph that a caller captured stays valid
+    std::map<int, Schedule> fused;
+    Schedule plain;           // every operation on its own
 };
 
 // The two-stream form of a schedule: GEMMs with more than 8 flops per
@@ -208,9 +213,9 @@ struct fscc_ctx {
     // created on first use, with the default priority
     int streams = 1;
     hipStream_t st2 = nullptr;
-    // schedules are rebuilt, and a batch's graph captured again, when this
-    // changes (precision, reorder traversal, tuning, a buffer that moved)
-    long long sched_gen = 0;
+    // a batch's graph is captured again when this changes (precision, tuning)
+    long long plan_gen = 0;
+    bool fusing = false;          // single systems: small operations in fused launches
     bool gather_forced = false;   // fscc_gather_order chose a traversal: reorders keep their own kernels
     // real arithmetic (real double groups): every amplitude, integral and
     // intermediate buffer holds doubles instead of complex doubles
@@ -282,7 +287,8 @@ struct fscc_ctx {
     }
 
     static void free_list(OpList& L) {
-        free_schedule(L.fused);
+        for (auto& s : L.fused) free_schedule(s.second);
+        L.fused.clear();
         free_schedule(L.plain);
         if (L.ops)
             for (auto& o : *L.ops)
@@ -567,11 +573,30 @@ struct fscc_ctx {
         }
     }
 
-    // The schedule of a list and its device tables (built once, again when
-    // sched_gen changes).
-    void prepare_schedule(OpList& L) {
-        Schedule& S = L.fused;
-        if (S.gen == sched_gen) return;
+    // What a schedule depends on besides its operation list.
+    int schedule_key() const { return 2 * prec + (gather_forced ? 1 : 0); }
+
+    // The schedules that the residual evaluations need from now on.  Every call
+    // that changes what they depend on ends with this, so that an evaluation
+    // neither allocates nor copies and may be captured into a graph.
+    void prepare_schedules() {
+        if (!fusing) return;
+        for (OpList* L : {&L00, &L01p, &L01, &L02p, &L02}) prepare_schedule(*L);
+    }
+
+    // Tuning rewrites the forms and traversals that schedules rest on; a buffer
+    // has moved.
+    void drop_schedules() {
+        for (OpList* L : {&L00, &L01p, &L01, &L02p, &L02}) {
+            for (auto& s : L->fused) free_schedule(s.second);
+            L->fused.clear();
+        }
+    }
+
+    // The schedule of a list and its device tables (built once per key).
+    Schedule& prepare_schedule(OpList& L) {
+        Schedule& S = L.fused[schedule_key()];
+        if (S.ready) return S;
         free_schedule(S);
         const std::vector<Op>& ops = *L.ops;
         std::vector<char> alone(ops.size(), 0);
@@ -684,7 +709,8 @@ struct fscc_ctx {
             S.fops = (FOp*)m;
             S.items = (FItem*)(m + o1);
         }
-        S.gen = sched_gen;
+        S.ready = true;
+        return S;
     }
 
     void run_fused(const Schedule& S, size_t k) {
@@ -708,14 +734,13 @@ struct fscc_ctx {
         }
         if (timed) collect(L);
         std::vector<std::vector<StreamChunk>>* sc = stream_chunks(L);
-        bool fuse = !sc && !d_active;
-        if (fuse) {
-            prepare_schedule(L);
+        Schedule* fused = fusing && !sc ? &prepare_schedule(L) : nullptr;
+        if (fused && timed) {
             const int sel = prof_sel - L.base;
-            if (timed && (prof_sel < 0 || (sel >= 0 && sel < (int)ops.size() && L.fused.in_fused[sel]))) fuse = false;
+            if (prof_sel < 0 || (sel >= 0 && sel < (int)ops.size() && fused->in_fused[sel])) fused = nullptr;
         }
-        if (!fuse && L.plain.steps.empty()) L.plain.steps = plain_schedule(ops.size());
-        Schedule& S = fuse ? L.fused : L.plain;
+        if (!fused && L.plain.steps.empty()) L.plain.steps = plain_schedule(ops.size());
+        Schedule& S = fused ? *fused : L.plain;
         if (streams == 2 && !sc && !d_active) {
             run_steps_two(L, S, timed);
             return;
