@@ -386,7 +386,8 @@ fscc_status fscc_autotune_cached(const fscc_ctx *ctx, int *from_cache);
  * along its rows; a term without an affine form on a tile uses its map
  * (gathers with a second operand fall back to tiled = 1).  Complex contexts;
  * a real context always uses storage order.  The results are bitwise
- * identical.  Replaces the choice fscc_autotune(ctx, 1) made.  With 0, reorders
+ * identical.  Replaces the choice fscc_autotune(ctx, 1) made, and a later
+ * fscc_autotune(ctx, 0 or 1) replaces this one.  With 0, reorders
  * that share a launch with other operations do so in storage order; with 1 or
  * 2 every reorder runs on its own kernel.  FSCC_EINVAL for another value. */
 fscc_status fscc_gather_order(fscc_ctx *ctx, int tiled);

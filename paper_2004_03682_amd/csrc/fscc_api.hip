@@ -1731,7 +1731,10 @@ fscc_status fscc_autotune(fscc_ctx* ctx, int level) {
     return guarded(ctx, [&]() -> fscc_status {
         Plan& P = ctx->plan;
         ++ctx->plan_gen;   // tables are freed and rebuilt: a graph captured with them is stale
-        if (level < 2) ctx->drop_schedules();
+        if (level < 2) {   // the traversals are chosen anew
+            ctx->drop_schedules();
+            ctx->traversal = fscc_ctx::TRAVERSE_TUNED;
+        }
         std::vector<OpList*> lists = {&ctx->L00, &ctx->L01, &ctx->L02};
         if (level == 0) {
             for (OpList* L : lists)
@@ -1757,6 +1760,7 @@ fscc_status fscc_autotune(fscc_ctx* ctx, int level) {
             if (tune_load(ctx->tune_path, key, cached) && tune_apply(ctx, cached)) {
                 ctx->tune_from_cache = true;
                 ctx->drop_schedules();
+                ctx->traversal = fscc_ctx::TRAVERSE_TUNED;
                 ctx->prepare_schedules();
                 return FSCC_OK;
             }
@@ -2076,7 +2080,7 @@ fscc_status fscc_gather_order(fscc_ctx* ctx, int tiled) {
                 o.use_rtiles = tiled == 2 && o.d_rtiles != nullptr;
                 o.use_gtiles = !o.use_rtiles && tiled >= 1 && o.d_gtiles != nullptr;
             }
-    ctx->gather_forced = tiled != 0;
+    ctx->traversal = tiled ? fscc_ctx::TRAVERSE_TILES : fscc_ctx::TRAVERSE_STORAGE;
     return guarded(ctx, [&]() -> fscc_status {
         ctx->prepare_schedules();
         return FSCC_OK;

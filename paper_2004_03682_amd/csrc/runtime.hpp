@@ -216,7 +216,11 @@ struct fscc_ctx {
     // a batch's graph is captured again when this changes (precision, tuning)
     long long plan_gen = 0;
     bool fusing = false;          // single systems: small operations in fused launches
-    bool gather_forced = false;   // fscc_gather_order chose a traversal: reorders keep their own kernels
+    // who chose the traversal of the reorders: the defaults or tuning (a large one
+    // with a tuned traversal keeps its kernel), fscc_gather_order(0) (storage
+    // order, also in chains), fscc_gather_order(1 or 2) (every one on its kernel)
+    enum Traversal { TRAVERSE_TUNED = 0, TRAVERSE_STORAGE, TRAVERSE_TILES, TRAVERSE_N };
+    int traversal = TRAVERSE_TUNED;
     // real arithmetic (real double groups): every amplitude, integral and
     // intermediate buffer holds doubles instead of complex doubles
     bool real = false;
@@ -574,7 +578,7 @@ struct fscc_ctx {
     }
 
     // What a schedule depends on besides its operation list.
-    int schedule_key() const { return 2 * prec + (gather_forced ? 1 : 0); }
+    int schedule_key() const { return TRAVERSE_N * prec + traversal; }
 
     // The schedules that the residual evaluations need from now on.  Every call
     // that changes what they depend on ends with this, so that an evaluation
@@ -604,9 +608,9 @@ struct fscc_ctx {
             const Op& o = ops[k];
             // a split-precision GEMM and a reorder with a forced traversal have kernels of their own
             if (o.kind == OP_GEMM && prec != FSCC_FP64 && L.g[k].mx && L.g[k].mx->prec == prec) alone[k] = 1;
-            if (o.kind == OP_GATHER && gather_forced) alone[k] = 1;
+            if (o.kind == OP_GATHER && traversal == TRAVERSE_TILES) alone[k] = 1;
             // a large reorder for which tuning found a better traversal keeps it
-            if (o.kind == OP_GATHER && (o.use_rtiles || o.use_gtiles) && !fusable(o, real)) alone[k] = 1;
+            if (o.kind == OP_GATHER && !real && (o.use_rtiles || o.use_gtiles) && !fusable(o, real)) alone[k] = 1;
         }
         S.steps = build_schedule(ops, small_ops(ops, alone, real));
         S.in_fused.assign(ops.size(), 0);

@@ -10,11 +10,11 @@ import fsgen
 pytestmark = pytest.mark.gpu
 
 
-def _setup(real=False):
+def _setup(real=False, size=(9, 37, 5)):
     import torch
     import paper_2004_03682_amd as F
     assert torch.cuda.is_available(), "GPU tests need a GPU"
-    s = fsgen.make_system(9, 37, 5, 0.05, 17, real=real)
+    s = fsgen.make_system(*size, 0.05, 17, real=real)
     st = torch.cuda.Stream()
     with torch.cuda.stream(st):
         ctx = F.Context.from_system(s, stream=st, precision="real_fp64" if real else "fp64")
@@ -94,4 +94,39 @@ def test_a_captured_graph_outlives_changes_of_precision_and_traversal():
         again = _run(st, r, g.replay)
         for a, b in zip(first, again):
             assert torch.equal(a, b)
+    ctx.destroy()
+
+
+def _launches(ctx, st, t, r):
+    """Kernel launches of one evaluation (nodes of its captured graph)."""
+    import ctypes
+    import torch
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(g, stream=st, capture_error_mode="thread_local"):
+        ctx.build_residual(*t, *r)
+    with open("/proc/self/maps") as f:
+        path = next(line.split()[-1] for line in f if "libamdhip64" in line)
+    n = ctypes.c_size_t()
+    assert ctypes.CDLL(path).hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+@pytest.mark.parametrize("nocc,nvirt,nirrep", [(9, 37, 5), (14, 86, 1)])
+@pytest.mark.parametrize("real", [False, True])
+def test_tuning_and_storage_order_replace_a_forced_traversal(nocc, nvirt, nirrep, real):
+    """Tuning chooses the traversals anew and level 0 restores those of a fresh context; storage order lets every reorder
+    into chains again, also one that tuning had put on tiles (the second system has reorders above 2^19 elements)."""
+    ctx, st, t, r = _setup(real, (nocc, nvirt, nirrep))
+    fresh = _launches(ctx, st, t, r)
+    ctx.gather_order(2)
+    forced = _launches(ctx, st, t, r)
+    assert forced > fresh
+    ctx.autotune(0)
+    assert _launches(ctx, st, t, r) == fresh
+    ctx.gather_order(2)
+    ctx.autotune(1)
+    assert _launches(ctx, st, t, r) < forced
+    ctx.autotune(0)
+    ctx.gather_order(0)
+    assert _launches(ctx, st, t, r) == fresh
     ctx.destroy()
