@@ -123,15 +123,6 @@ double cfg_cost(const Op& o, int cfg, bool split, int lds, bool real) {
         const double chain = (double)((wg + 511) / 512) * ((K + ZDOT_KC - 1) / ZDOT_KC) * 1.6e-6;
         return 5e-6 + std::max(std::max(by / 5.5e12, fl / 20e12), chain);
     }
-    if (cfg == ZCFG_SKINNY) {
-        // A re-read once per 32-column block, B once per 64-row block
-        double re = 0.0;
-        for (auto& p : o.probs) {
-            const double tm = (p.M + ZSKINNY_BM - 1) / ZSKINNY_BM, tn = (p.N + ZSKINNY_BN - 1) / ZSKINNY_BN;
-            re += es * ((double)p.M * p.K * tn + (double)p.N * p.K * tm);
-        }
-        return 10e-6 + std::max(re / 2e12, fl / 15e12);
-    }
     // MFMA tiles.  Workgroups resident per CU (by LDS and registers)
     static const int occ_staged[ZCFG_N] = {2, 3, 3, 5, 5, 5, 1, 1, 1, 3, 3, 1, 2, 3};
     static const int occ_direct[ZCFG_N] = {2, 1, 1, 6, 4, 5, 1, 1, 1, 3, 3, 1, 2, 3};
@@ -167,34 +158,33 @@ double cfg_cost(const Op& o, int cfg, bool split, int lds, bool real) {
     return t;
 }
 
-// The cheapest form by cfg_cost.  Not considered, since never the fastest where
-// the fit looked: 128x16 and 16x128 tiles and the skinny form.
-GemmChoice pick_form(const Op& o, bool real) {
-    GemmChoice best;
-    double bc = 1e30;
-    if (o.probs.empty()) return best;
+// The forms of an operation by cfg_cost, cheapest first; split, direct: may
+// K be split, may slices go to LDS directly.  Not considered, since never the
+// fastest where the fit looked: 128x16 and 16x128 tiles and the skinny form.
+std::vector<GemmChoice> forms_by_cost(const Op& o, bool real, bool split, bool direct) {
+    if (o.probs.empty()) return {GemmChoice()};
+    std::vector<std::pair<double, GemmChoice>> f;
     for (int cfg : {ZCFG_64x64, ZCFG_32x32, ZCFG_64x16, ZCFG_16x64, ZCFG_32x64, ZCFG_64x32, ZCFG_64x64R, ZCFG_64x32R,
                     ZCFG_TALL, ZCFG_RED, ZCFG_DOT}) {
         if (!cfg_ok(o, cfg, real)) continue;
         const bool mfma = cfg != ZCFG_TALL && cfg != ZCFG_RED && cfg != ZCFG_DOT;
         bool can_split = false;
-        if (mfma)
+        if (mfma && split)
             for (int c : splitk_chunks(o, cfg)) can_split = can_split || c > 1;
         for (int lds : {(int)LDS_DIRECT, (int)LDS_STAGED}) {
-            if (lds == LDS_DIRECT && !mfma) continue;
-            for (int sp = 0; sp <= (can_split ? 1 : 0); ++sp) {
-                const double c = cfg_cost(o, cfg, sp != 0, lds, real);
-                if (c < bc) {
-                    bc = c;
-                    best = GemmChoice{cfg, sp != 0 || cfg == ZCFG_RED, lds};
-                }
-            }
+            if (lds == LDS_DIRECT && !(mfma && direct)) continue;
+            for (int sp = 0; sp <= (can_split ? 1 : 0); ++sp)
+                f.push_back({cfg_cost(o, cfg, sp != 0, lds, real),
+                             GemmChoice{cfg, sp != 0 || (cfg == ZCFG_RED && split), lds}});
         }
     }
-    return best;
+    std::stable_sort(f.begin(), f.end(), [](const auto& a, const auto& b) { return a.first < b.first; });
+    std::vector<GemmChoice> out;
+    for (auto& x : f) out.push_back(x.second);
+    return out;
 }
 
-int pick_cfg(const Op& o, bool real) { return pick_form(o, real).cfg; }
+GemmChoice pick_form(const Op& o, bool real) { return forms_by_cost(o, real, true, true).front(); }
 
 // Workgroups of one launch are handed to the 8 XCDs round-robin (block b runs on
 // XCD b % 8) and each XCD has its own L2.  Permute the logical tile sequence so
@@ -2205,8 +2195,14 @@ fscc_status fscc_zgemm(int cfg, int bk, int tA, int tB, int cA, int cB, int M, i
         if (M > 0 && N > 0) o.probs.push_back(GemmProblem{0, 0, 0, M, N, K, std::max(lda, 1), std::max(ldb, 1), ldc});
         if (cfg >= 0 && !cfg_ok(o, cfg)) return FSCC_EINVAL;
         GemmDev g;
-        plan_gemm(c, o, g, cfg < 0 ? pick_cfg(o) : cfg, bk, allow_split != 0, cfg < 0 ? three_products(o) : m3);
-        g.lds = dl ? LDS_DIRECT : db ? LDS_DOUBLE : LDS_STAGED;
+        if (cfg < 0) {   // the best of the forms that this call runs
+            const GemmChoice f = forms_by_cost(o, false, allow_split != 0, direct_ok(bk, A, B)).front();
+            plan_gemm(c, o, g, f.cfg, bk, f.split, three_products(o));
+            g.lds = f.lds;
+        } else {
+            plan_gemm(c, o, g, cfg, bk, allow_split != 0, m3);
+            g.lds = dl ? LDS_DIRECT : db ? LDS_DOUBLE : LDS_STAGED;
+        }
         hipError_t e;
         if (!g.split) {
             e = launch_zgemm(g.cfg, g.bk, o.tA, o.tB, (const double2*)A, (const double2*)B, (double2*)C, g.probs, g.tiles,
@@ -2251,8 +2247,14 @@ fscc_status fscc_dgemm(int cfg, int bk, int tA, int tB, int M, int N, int K, con
         if (M > 0 && N > 0) o.probs.push_back(GemmProblem{0, 0, 0, M, N, K, std::max(lda, 1), std::max(ldb, 1), ldc});
         if (cfg >= 0 && !cfg_ok(o, cfg, true)) return FSCC_EINVAL;
         GemmDev g;
-        plan_gemm(c, o, g, cfg < 0 ? pick_cfg(o, true) : cfg, bk, allow_split != 0);
-        g.lds = dl ? LDS_DIRECT : LDS_STAGED;
+        if (cfg < 0) {   // the best of the forms that this call runs
+            const GemmChoice f = forms_by_cost(o, true, allow_split != 0, bk == 16).front();
+            plan_gemm(c, o, g, f.cfg, bk, f.split);
+            g.lds = f.lds;
+        } else {
+            plan_gemm(c, o, g, cfg, bk, allow_split != 0);
+            g.lds = dl ? LDS_DIRECT : LDS_STAGED;
+        }
         hipError_t e;
         if (!g.split) {
             e = launch_dgemm(g.cfg, g.bk, o.tA, o.tB, A, B, C, g.probs, g.tiles, g.ntiles, alpha, o.beta, c->st, 0,

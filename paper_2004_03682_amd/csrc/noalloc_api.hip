@@ -84,17 +84,26 @@ fscc_status fscc_zgemm_noalloc(int cfg, int bk, int tA, int tB, int cA, int cB, 
         o.beta = beta ? 1 : 0;
         if (M > 0 && N > 0) o.probs.push_back(GemmProblem{0, 0, 0, M, N, K, std::max(lda, 1), std::max(ldb, 1), ldc});
         if (cfg >= 0 && !cfg_ok(o, cfg)) return free_call_fail(FSCC_EINVAL, "fscc_zgemm_noalloc: shape does not fit the tile form");
-        const int form = cfg < 0 ? pick_cfg(o) : cfg;
-        const bool three = cfg < 0 ? three_products(o) : m3;
         GemmHost h;
-        plan_gemm_host(false, o, form, bk, allow_split != 0, three, h);
-        // an optional K split whose partial sums do not fit runs unsplit
-        // (same kernel, one K chunk per tile)
-        if (plan_bytes(h) > kScratchBytes && h.g.split && allow_split)
-            plan_gemm_host(false, o, form, bk, false, three, h);
-        // a form of the cost model's choosing whose tables do not fit: the
-        // largest tile, which has the fewest
-        if (cfg < 0 && plan_bytes(h) > kScratchBytes) plan_gemm_host(false, o, ZCFG_64x64, bk, false, three, h);
+        if (cfg < 0) {
+            // the best of the forms that this call runs
+            const GemmChoice f = forms_by_cost(o, false, allow_split != 0, direct_ok(bk, A, B)).front();
+            plan_gemm_host(false, o, f.cfg, bk, f.split, three_products(o), h);
+            h.g.lds = f.lds;
+            if (plan_bytes(h) > kScratchBytes && h.g.split && allow_split) {
+                plan_gemm_host(false, o, f.cfg, bk, false, three_products(o), h);
+                h.g.lds = f.lds;
+            }
+            // tables that do not fit: the largest tile has the fewest
+            if (plan_bytes(h) > kScratchBytes) plan_gemm_host(false, o, ZCFG_64x64, bk, false, three_products(o), h);
+        } else {
+            plan_gemm_host(false, o, cfg, bk, allow_split != 0, m3, h);
+            // an optional K split whose partial sums do not fit runs unsplit
+            // (same kernel, one K chunk per tile)
+            if (plan_bytes(h) > kScratchBytes && h.g.split && allow_split)
+                plan_gemm_host(false, o, cfg, bk, false, m3, h);
+            h.g.lds = dl ? LDS_DIRECT : db ? LDS_DOUBLE : LDS_STAGED;
+        }
         if (plan_bytes(h) > kScratchBytes)
             return free_call_fail(FSCC_EINVAL, "fscc_zgemm_noalloc: plan needs " + std::to_string(plan_bytes(h)) +
                                                    " bytes of scratch, more than the static " +
@@ -107,7 +116,6 @@ fscc_status fscc_zgemm_noalloc(int cfg, int bk, int tA, int tB, int cA, int cB, 
         hip_check(scratch_address(dev, &base), "hipGetSymbolAddress(scratch)");
         unsigned char* p = (unsigned char*)base;
         GemmDev g = h.g;
-        g.lds = dl ? LDS_DIRECT : db ? LDS_DOUBLE : LDS_STAGED;
         g.probs = (ZProb*)p;
         p += align256(h.pr.size() * sizeof(ZProb));
         g.tiles = (ZTile*)p;

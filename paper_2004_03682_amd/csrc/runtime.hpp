@@ -847,7 +847,12 @@ struct GemmChoice {
     int lds = LDS_STAGED;
 };
 GemmChoice pick_form(const Op& o, bool real);
-int pick_cfg(const Op& o, bool real = false);
+// May the default form of a caller's complex operands use direct-to-LDS loads
+// (16-deep slices, 16 bytes per lane)?
+inline bool direct_ok(int bk, const void* A, const void* B) {
+    return bk == 16 && (((uintptr_t)A | (uintptr_t)B) & 15) == 0;
+}
+std::vector<GemmChoice> forms_by_cost(const Op& o, bool real, bool split, bool direct);
 bool three_products(const Op& o);
 std::vector<ZTile> xcd_order(const std::vector<ZTile>& logical);
 void free_gemm(GemmDev& g);

@@ -209,3 +209,40 @@ def test_default_form_of_thin_products_keeps_small_imaginary_parts(M, N, K, tA, 
     assert err.max() <= (K + 16) * 2.0 ** -53, float(err.max())
     re = ab[0] @ ab[1] - ab[2] @ ab[3]
     assert (np.abs(got.real - re) <= (K + 16) * 2.0 ** -53 * (np.abs(a) @ np.abs(b))).all()
+
+
+@pytest.mark.parametrize("bk", [16, 32])
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("M,N,K,tA,tB", [(1, 1, 1, 0, 0), (48, 900, 900, 0, 1), (12, 63, 9000, 0, 0), (4000, 10, 60, 0, 0),
+                                         (129, 65, 33, 1, 1), (2, 700, 512, 0, 1), (300, 300, 300, 1, 0), (5, 7, 0, 0, 0)])
+def test_default_forms_with_every_restriction(M, N, K, tA, tB, bk, shift):
+    """cfg = -1 with and without a K split, 16- and 32-deep slices, and operands 8 bytes off 16-byte alignment (no
+    direct-to-LDS form then), complex with and without allocations, and real: (K + 16) roundings of the magnitudes, twice
+    for three products."""
+    import ctypes
+    import torch
+    import paper_2004_03682_amd as F
+    rng = np.random.default_rng(K + N)
+    a, b, c0 = _rand(rng, M, K), _rand(rng, K, N), _rand(rng, M, N)
+    A, B = np.ascontiguousarray(a.T if tA else a), np.ascontiguousarray(b.T if tB else b)
+    lda, ldb = max(1, A.shape[1]), max(1, B.shape[1])
+    ref = a @ b + c0
+    bound = 4 * (K + 16) * 2.0 ** -53 * (np.abs(a.real) + np.abs(a.imag)) @ (np.abs(b.real) + np.abs(b.imag)) + 1e-15
+
+    def shifted(x):     # a device copy `shift` doubles into its allocation
+        v = np.ascontiguousarray(x).view(np.float64).ravel()
+        d = torch.zeros(v.size + 2, dtype=torch.float64, device="cuda")
+        d[shift:shift + v.size] = torch.from_numpy(v).cuda()
+        return d, ctypes.c_void_p(d.data_ptr() + 8 * shift)
+    st = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    one, zero = ctypes.c_double(1.0), ctypes.c_double(0.0)
+    for split in (0, 1):
+        for f in (F.lib().fscc_zgemm, F.lib().fscc_zgemm_noalloc):
+            (_k1, pa), (_k2, pb), (dc, pc) = shifted(A), shifted(B), shifted(c0)
+            assert f(-1, bk, tA, tB, 0, 0, M, N, K, pa, lda, pb, ldb, pc, N, one, zero, 1, split, st) == 0
+            got = dc.cpu().numpy()[shift:shift + 2 * M * N].view(np.complex128).reshape(M, N)
+            assert (np.abs(got - ref) <= bound).all(), (split, np.abs(got - ref).max())
+        (_k1, pa), (_k2, pb), (dc, pc) = shifted(A.real), shifted(B.real), shifted(c0.real)
+        assert F.lib().fscc_dgemm(-1, bk, tA, tB, M, N, K, pa, lda, pb, ldb, pc, N, one, 1, split, st) == 0
+        got = dc.cpu().numpy()[shift:shift + M * N].reshape(M, N)
+        assert (np.abs(got - (a.real @ b.real + c0.real)) <= bound).all()
