@@ -460,7 +460,8 @@ fscc_status fscc_zgemm(int cfg, int bk, int tA, int tB, int cA, int cB, int M, i
  * one static device array of FSCC_NOALLOC_SCRATCH_BYTES per GPU (held until
  * the process ends) instead of buffers allocated per call; no hipMalloc or
  * hipFree is called.  A K split whose partial sums do not fit the array runs
- * unsplit; a plan whose tables alone do not fit returns FSCC_EINVAL.  Every
+ * unsplit (with cfg = -1 the cheapest form that fits is taken); a plan whose
+ * tables alone do not fit returns FSCC_EINVAL.  Every
  * call on one GPU uses that GPU's array: calls that overlap on one GPU (from
  * two host threads at once) race.  Synchronises hip_stream.  The message of
  * a failed call (of this one or fscc_zgemm) is fscc_last_error(NULL) on the

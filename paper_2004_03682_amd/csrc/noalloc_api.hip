@@ -86,16 +86,26 @@ fscc_status fscc_zgemm_noalloc(int cfg, int bk, int tA, int tB, int cA, int cB, 
         if (cfg >= 0 && !cfg_ok(o, cfg)) return free_call_fail(FSCC_EINVAL, "fscc_zgemm_noalloc: shape does not fit the tile form");
         GemmHost h;
         if (cfg < 0) {
-            // the best of the forms that this call runs
-            const GemmChoice f = forms_by_cost(o, false, allow_split != 0, direct_ok(bk, A, B)).front();
-            plan_gemm_host(false, o, f.cfg, bk, f.split, three_products(o), h);
-            h.g.lds = f.lds;
-            if (plan_bytes(h) > kScratchBytes && h.g.split && allow_split) {
-                plan_gemm_host(false, o, f.cfg, bk, false, three_products(o), h);
+            // the cheapest form that this call runs and whose tables and
+            // partial sums fit; if none does, the forms that the estimate
+            // leaves out (a 128 x 16 tile has the fewest tables for few columns)
+            std::vector<GemmChoice> forms = forms_by_cost(o, false, allow_split != 0, direct_ok(bk, A, B));
+            for (int form : {ZCFG_128x16, ZCFG_16x128, ZCFG_SKINNY}) forms.push_back(GemmChoice{form, false, LDS_STAGED});
+            bool fits = false;
+            for (const GemmChoice& f : forms) {
+                int bm, bn;
+                zcfg_tile(f.cfg, &bm, &bn);
+                const double tiles = std::ceil((double)M / bm) * std::ceil((double)N / bn);
+                const double parts = f.cfg == ZCFG_SKINNY ? (double)M * N : 0.0;
+                if (tiles * sizeof(ZTile) + parts * sizeof(double2) > kScratchBytes) continue;
+                plan_gemm_host(false, o, f.cfg, bk, f.split, three_products(o), h);
                 h.g.lds = f.lds;
+                fits = plan_bytes(h) <= kScratchBytes;
+                if (fits) break;
             }
-            // tables that do not fit: the largest tile has the fewest
-            if (plan_bytes(h) > kScratchBytes) plan_gemm_host(false, o, ZCFG_64x64, bk, false, three_products(o), h);
+            if (!fits)
+                return free_call_fail(FSCC_EINVAL, "fscc_zgemm_noalloc: no form of this size fits the static scratch of " +
+                                                       std::to_string(kScratchBytes) + " bytes");
         } else {
             plan_gemm_host(false, o, cfg, bk, allow_split != 0, m3, h);
             // an optional K split whose partial sums do not fit runs unsplit
