@@ -1508,7 +1508,7 @@ namespace {
 // of the context's plans (kind, name, sizes, GEMM problem shapes); an entry
 // lists per operation the chosen form: GEMM [1, tile, bk, split, 3M, DB,
 // split-precision tile or -1], reorder [0, traversal], other [2].
-constexpr int kTuneVersion = 6;
+constexpr int kTuneVersion = 7;   // to be raised with every change of a kernel that tuning chooses among
 
 std::vector<OpList*> tune_lists(fscc_ctx* c) { return {&c->L00, &c->L01, &c->L02}; }
 

@@ -75,3 +75,26 @@ def test_no_cache_path_measures(tmp_path):
     a.autotune(1)
     assert not a.autotune_cached()
     a.destroy()
+
+
+def test_choices_timed_on_other_kernels_are_not_applied(tmp_path):
+    """The key carries the version of the kernel set: entries up to version 6 were timed before the split-bf16 tiles loaded
+    their operands straight into LDS.  They stay in the file."""
+    import re
+    path = tmp_path / "tune.json"
+    s = fsgen.make_system(6, 14, 4, 0.1, 21)
+    a = _ctx(s)
+    a.tune_cache(path)
+    a.autotune(1)
+    text = path.read_text()
+    version = int(re.search(r"\|v(\d+)\|", text).group(1))
+    path.write_text(text.replace(f"|v{version}|", "|v6|"))
+    b = _ctx(s)
+    b.tune_cache(path)
+    b.autotune(1)
+    assert not b.autotune_cached()
+    assert path.read_text().count('{"key": ') == 2
+    b.autotune(1)
+    assert b.autotune_cached()
+    a.destroy()
+    b.destroy()
