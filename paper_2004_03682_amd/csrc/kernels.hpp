@@ -235,7 +235,7 @@ struct FOp {
 struct FItem {
     int op, first, nops, pad;
 };
-constexpr int kMaxChain = 8;
+constexpr int kMaxChain = 8;   // operations of an item that the kernel has room for
 hipError_t load_fused(bool real);
 hipError_t launch_fused(const FItem* items, int nitems, const FOp* ops, const FIo& io, bool real, hipStream_t st);
 

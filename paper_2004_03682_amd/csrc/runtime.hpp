@@ -124,6 +124,8 @@ struct Schedule {
     hipEvent_t fork = nullptr, join = nullptr;
 };
 
+static_assert(kScheduleChain <= (size_t)kMaxChain, "the fused kernel holds every descriptor of a chain");
+
 struct OpList {
     std::vector<Op>* ops = nullptr;
     std::vector<GemmDev> g;

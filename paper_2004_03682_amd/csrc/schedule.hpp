@@ -130,6 +130,10 @@ inline std::vector<char> small_ops(const std::vector<Op>& ops, const std::vector
     return small;
 }
 
+// Most operations of a chain: their descriptors share a workgroup's LDS in the
+// fused kernel (runtime.hpp checks that it has room for as many).
+constexpr size_t kScheduleChain = 8;
+
 // The schedule of an operation list.
 // Elementwise operations on the same destination are chained when nothing
 // reads the destination between them and the chains can still be ordered.
@@ -137,7 +141,6 @@ inline std::vector<char> small_ops(const std::vector<Op>& ops, const std::vector
 // fused step; if there are none, every other ready operation follows as a step of its own, in
 // list order.
 inline std::vector<ScheduleStep> build_schedule(const std::vector<Op>& ops, const std::vector<char>& small) {
-    constexpr size_t kChain = 8;   // most operations of a chain (their descriptors share a workgroup's LDS)
     const int n = (int)ops.size();
     const std::vector<std::vector<int>> deps = op_dependencies(ops);
     auto elementwise = [&](int k) { return small[k] && ops[k].kind != OP_GEMM; };
@@ -178,7 +181,7 @@ inline std::vector<ScheduleStep> build_schedule(const std::vector<Op>& ops, cons
                 read_since = true;
             }
         }
-        if (elementwise(k) && w >= 0 && !read_since && elementwise(w) && ops[w].n == ops[k].n && !reads(k, ops[k].dst) && chain[node[w]].size() < kChain &&
+        if (elementwise(k) && w >= 0 && !read_since && elementwise(w) && ops[w].n == ops[k].n && !reads(k, ops[k].dst) && chain[node[w]].size() < kScheduleChain &&
             chain[node[w]].back() == w) {
             node[k] = node[w];
             if (!orderable(k)) node[k] = -1;

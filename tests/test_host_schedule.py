@@ -52,3 +52,17 @@ def test_schedules_respect_every_dependency(lib, spec, keep_every, real):
     if keep_every == 0 and nvirt <= 37:
         # a small system's residual runs in fused launches only, a fraction of its operations
         assert steps[0] == fused[0] <= count[0] // 3
+
+
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 16, 17, 40])
+def test_long_chains_are_cut_at_the_kernels_limit(n, tmp_path):
+    """One limit for the planner and the kernel (the build asserts that the kernel has room for it)."""
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("g++ not available")
+    out = str(tmp_path / "libchaincheck.so")
+    subprocess.run([gxx, "-O1", "-std=c++17", "-shared", "-fPIC", "-I" + CSRC, "-o", out,
+                    os.path.join(HERE, "host", "chain_check.cpp")], check=True)
+    limit = ctypes.c_int()
+    chains = ctypes.CDLL(out).chain_check(n, ctypes.byref(limit))
+    assert limit.value == 8 and chains == (n + limit.value - 1) // limit.value
