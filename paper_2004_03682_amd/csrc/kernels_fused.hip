@@ -153,24 +153,20 @@ __device__ void fused_elements(const unsigned long long* __restrict__ lds, FOp o
                     any = any || (m.a[t] != 0xFFFFFFFFu && m.b[t] != 0xFFFFFFFFu);
                     T z = x[t];
                     if (o.conj) conjugate(z);
-                    if (o.bil) z = elem_mul(z, y[t]);
-                    add(s, z);
+                    if (o.bil) s = elem_add_mul(s, z, y[t]);
+                    else add(s, z);
                 }
             // an accumulating gather leaves an element whose terms are all
             // structural zeros as it is
             if (!o.beta || any) {
-                T out = elem_scale(o.ar, o.ai, s);
-                if (o.beta) add(out, v);
-                v = out;
+                v = o.beta ? elem_scale_add(o.ar, o.ai, s, v) : elem_scale(o.ar, o.ai, s);
                 held = true;
             }
         } else if (o.kind == FK_AXPBY) {
             T x = ptr<const T>(o.src[0])[at];
             next();
             if (o.conj) conjugate(x);
-            T out = elem_scale(o.ar, o.ai, x);
-            if (o.beta) add(out, v);
-            v = out;
+            v = o.beta ? elem_scale_add(o.ar, o.ai, x, v) : elem_scale(o.ar, o.ai, x);
             held = true;
         } else {
             const double f = ptr<const double>(o.src2)[at];

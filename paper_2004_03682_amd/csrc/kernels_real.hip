@@ -11,6 +11,7 @@
 //  * gather, elementwise, Jacobi / DIIS / energy reductions on doubles
 #include <hip/hip_runtime.h>
 
+#include "elem_math.hpp"
 #include "kernels.hpp"
 
 namespace fscc {
@@ -446,28 +447,24 @@ __global__ __launch_bounds__(256) void k_dgather(double* __restrict__ dst, const
     double s = 0.0;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-        double x = dmap_load(maps.src[t] ? (const double*)maps.src[t] : src, maps.a[t][k]);
-        if (BIL) x *= dmap_load(src2, maps.b[t][k]);
-        s += x;
+        const double x = dmap_load(maps.src[t] ? (const double*)maps.src[t] : src, maps.a[t][k]);
+        if (BIL) s = elem_add_mul(s, x, dmap_load(src2, maps.b[t][k]));
+        else s += x;
     }
-    double out = alpha * s;
-    if (beta) out += dst[k];
-    dst[k] = out;
+    dst[k] = beta ? elem_scale_add(alpha, 0.0, s, dst[k]) : elem_scale(alpha, 0.0, s);
 }
 
 __global__ __launch_bounds__(256) void k_daxpby(double* __restrict__ dst, const double* __restrict__ src, long long n,
                                                 double alpha, int beta) {
     const long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= n) return;
-    double out = alpha * src[k];
-    if (beta) out += dst[k];
-    dst[k] = out;
+    dst[k] = beta ? elem_scale_add(alpha, 0.0, src[k], dst[k]) : elem_scale(alpha, 0.0, src[k]);
 }
 
 __global__ __launch_bounds__(256) void k_ddiag(double* __restrict__ dst, const double* __restrict__ d,
                                                const double* __restrict__ src, long long n) {
     const long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < n) dst[k] -= d[k] * src[k];
+    if (k < n) dst[k] = elem_sub(dst[k], d[k], src[k]);
 }
 
 __global__ __launch_bounds__(256) void k_dmul(double* __restrict__ dst, const double* __restrict__ d, long long n) {

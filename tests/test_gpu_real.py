@@ -279,3 +279,33 @@ def test_real_context_rejects_what_it_does_not_do():
         ctx.build_residual(*(torch.zeros(n, dtype=torch.complex128, device="cuda")
                              for n in (ctx.n1, ctx.n2, ctx.n1, ctx.n2)))
     ctx.destroy()
+
+
+def test_traversals_are_bitwise_equal_in_every_sector():
+    """Real arithmetic walks every reorder in storage order, in launches shared with others or (tiled = 1, 2) on kernels of
+    their own: the element arithmetic is the same, multiply-adds included, so the residuals are equal bit for bit."""
+    import torch
+    import paper_2004_03682_amd as F
+    s = fsgen.make_system(8, 40, 4, 0.05, 9, nact=6, real=True)
+    ctx = F.Context.from_system(s, precision="real_fp64")
+    for C in fsgen.CLASSES:
+        ctx.set_integrals(C, torch.from_numpy(fsgen.real_buffer(fsgen.class_buffer(s, C)[0])).cuda())
+    rng = np.random.default_rng(3)
+
+    def rnd(n):
+        return torch.from_numpy(0.05 * rng.normal(size=n)).cuda()
+    t1, t2, s1, s2, p2 = (rnd(n) for n in (ctx.n1, ctx.n2, ctx.m1, ctx.m2, ctx.p2))
+    out = {}
+    for tiled in (0, 1, 2):
+        ctx.gather_order(tiled)
+        ctx.prepare_sector(t1, t2)
+        ctx.prepare_sector(s1, s2, sector=F.FSCC_S02)
+        r = [torch.empty_like(x) for x in (t1, t2, s1, s2, p2)]
+        ctx.build_residual(t1, t2, r[0], r[1])
+        ctx.build_residual(s1, s2, r[2], r[3], sector=F.FSCC_S01)
+        ctx.build_residual(None, p2, None, r[4], sector=F.FSCC_S02)
+        out[tiled] = [x.cpu() for x in r]
+    for tiled in (1, 2):
+        for a, b in zip(out[0], out[tiled]):
+            assert torch.equal(a, b), tiled
+    ctx.destroy()
