@@ -426,7 +426,8 @@ fscc_status fscc_gather_order(fscc_ctx *ctx, int tiled);
  * FSCC_CFG_3M set for a three-product MFMA tile, FSCC_CFG_DB for a
  * double-buffered one and FSCC_CFG_DL for a direct-to-LDS one, or -1 if k
  * is not a GEMM;
- * bk = K depth; split = 1 if split along K); host outputs. */
+ * bk = K depth; split = 1 if split along K); host outputs.  An operation that
+ * shares a launch with others runs there in 16 x 16 tiles instead. */
 fscc_status fscc_gemm_config(const fscc_ctx *ctx, int k, int *cfg, int *bk, int *split);
 
 /* One complex GEMM through the grouped MFMA kernel, for kernel-level tests:

@@ -245,8 +245,8 @@ __device__ __forceinline__ double2 part_load(const double2* p) {
 template <typename T>
 __device__ void fused_gemm(const FOp o, int first, T* __restrict__ red) {
     // steps per round of loads; three rounds of registers.  Four steps for
-    // complex as well would take the kernel over 128 registers: 3 % slower at
-    // 8/24 and 20/120 for the waves that are then not resident.
+    // complex as well would take the kernel over 128 registers, which spills
+    // (unspilled at three waves per SIMD: 3 % slower at 8/24 and 20/120).
     constexpr int R = sizeof(T) == 16 ? 2 : 4;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kw = o.kw, g = wave / kw, unit = first + g;

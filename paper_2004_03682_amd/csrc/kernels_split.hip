@@ -131,7 +131,7 @@ __global__ __launch_bounds__(256) void k_split(const double2* __restrict__ src, 
 // (16 bytes per lane; the swizzle is in the source addresses), and the next k
 // block's loads start as soon as the last fragments of this one are in
 // registers, behind the matrix work of the leading piece of A and the FP64
-// sums.  Without the staging registers a 64 x 64 tile fits twice on a CU (248
+// sums.  Without the staging registers a 64 x 64 tile fits twice on a CU (222
 // instead of 296 registers), so one workgroup's loads, LDS reads and FP64
 // sums overlap the other's matrix work.  What bounds it then is the traffic
 // from the L2 (7.5-10 TB/s over all tiles).  Per call at 30 occupied / 200

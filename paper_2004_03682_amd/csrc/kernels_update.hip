@@ -110,7 +110,7 @@ __device__ __forceinline__ double dyn_delta(double d, double S, int n) {
 // Jacobi step of every amplitude (T1 then T2) into history slot `slot`, with
 // the block's largest |step| and the dot products Re <e_j, e> with the m - 1
 // stored steps ord[0..m-1) and with itself: part[j * gridDim.x + block], the
-// maximum in row m.  Bound by memory: 88 + 16 (m - 1) bytes per complex
+// maximum in row m.  Bound by memory: 72 + 16 (m - 1) bytes per complex
 // amplitude, each read or written once (a step pass and a dot pass read the
 // new step twice and took three launches).
 template <typename T>

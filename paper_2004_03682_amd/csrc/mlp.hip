@@ -44,8 +44,10 @@ constexpr size_t OFF_W1 = 0, OFF_B1 = OFF_W1 + F_IN * HID, OFF_W2 = OFF_B1 + HID
 // so the 16 rows of a fragment read 16 different 16-byte bank groups.
 
 // Row fragments per workgroup: 64-row tiles read the weights least often;
-// fewer rows per workgroup where 64 would leave CUs without two workgroups
-// (a training step on 8192 rows: forward and backward 97 -> 52 us).
+// fewer rows per workgroup where 64 (from 16384 rows down) or 32 (from 8192
+// down) would leave CUs without a workgroup (a training step on 8192 rows:
+// forward and backward 97 -> 52 us).  At the lines the forward launch takes
+// 18.7 us for 8192 rows and 27.9 for 8193, 29.5 for 16384 and 43.2 for 16385.
 int mlp_fm(long long rows) { return rows > 32 * 512 ? 4 : rows > 16 * 512 ? 2 : 1; }
 
 __device__ __forceinline__ int lds_chunk(int row, int chunk) { return row * HID + ((chunk ^ (row & 15)) << 2); }

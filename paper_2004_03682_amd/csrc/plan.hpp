@@ -112,7 +112,7 @@ struct Plan {
     int b_t1 = -1, b_t2 = -1, b_r1 = -1, b_r2 = -1;
     int b_D1 = -1, b_D2 = -1;         // real denominators in T1/T2 layouts
     int b_oovv = -1;                  // <ij||ab> in the T2 layout (energy)
-    int b_tau = -1;                   // tau in the T2 layout (energy scratch)
+    int b_tau = -1;                   // tau in the T2 layout (a batch's energy reads it)
     std::vector<double> D1, D2;       // host copies (uploaded once)
 
     // ---- (0h,1p) sector (present when the system has active virtuals)

@@ -78,7 +78,8 @@ struct ScheduleStep {
 //     grouped tiles with operands shared through LDS are faster (twice both:
 //     20/120 in eight irreps 0.7 % slower).  A real operation has less work
 //     to share a launch's cost, and twice the traffic pays: 13/67 in three
-//     irreps 207 us at 48 MB and 0.2 Gflop, 186 us at 96 MB and 0.4 Gflop;
+//     irreps 207 us at 48 MB and 0.2 Gflop, 186 us at 96 MB and 0.4 Gflop (one
+//     system measured);
 //   * elementwise operations and reorders of up to 2^19 elements: above,
 //     their own launch costs less than 5 % of their time (chains: small_ops).
 inline bool fusable(const Op& o, bool real) {
@@ -93,9 +94,9 @@ inline bool fusable(const Op& o, bool real) {
 }
 
 // Waves of a 16 x 16 tile of a fused GEMM: kw waves in a workgroup, one per
-// SIMD, times split workgroups.  The matrix pipe of a SIMD takes 1.3 us for 64
-// k of a complex tile (192 k of a real one), so K is split down to that while
-// the tiles alone do not give the chip its 4096 waves.  Parts of a tile on
+// SIMD, times split workgroups.  The matrix pipe of a SIMD takes 1.7 us for 64
+// k of a complex tile and 0.9 us for 128 k of a real one, so K is split down to
+// that while the tiles alone do not give the chip its 4096 waves.  Parts of a tile on
 // other workgroups have to meet through memory (2 us), so that split is for
 // tiles that would keep a CU for longer than that (real 13/67, split above
 // 1024 or 512 k: 208, 203 us; complex 8/24, above 512 or 256: no difference).
