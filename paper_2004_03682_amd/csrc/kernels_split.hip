@@ -134,7 +134,9 @@ __global__ __launch_bounds__(256) void k_split(const double2* __restrict__ src, 
 // sums.  Without the staging registers a 64 x 64 tile fits twice on a CU (222
 // instead of 296 registers), so one workgroup's loads, LDS reads and FP64
 // sums overlap the other's matrix work.  What bounds it then is the traffic
-// from the L2 (7.5-10 TB/s over all tiles).  Per call at 30 occupied / 200
+// from the L2: by its counters 8.3 (64 x 64 tiles) to 12.3 TB/s (64 x 32) at 40
+// occupied / 300 virtual spinors in sixteen irreps, the matrix pipes busy for
+// 0.23-0.41 of the time.  Per call at 30 occupied / 200
 // virtual spinors in eight irreps, before -> after: W.U and ring (64 x 64)
 // 251 -> 176 us each (27 Gflop), t1-dressed ovvv (32 x 32) 253 -> 118 us,
 // ladder (64 x 32) 254 -> 231 us.
