@@ -443,8 +443,8 @@ fscc_status fscc_gemm_config(const fscc_ctx *ctx, int k, int *cfg, int *bk, int 
  * an MFMA tile id | FSCC_CFG_3M selects the three-product complex form,
  * | FSCC_CFG_DB or | FSCC_CFG_DL the LDS staging form (see above);
  * -1 = cost model (three-product form, four products for thin shapes as under
- * FSCC_CFG_3M; with bk = 16 and 16-byte aligned operands also direct-to-LDS).
- * FSCC_EINVAL if the shape does not
+ * FSCC_CFG_3M; with bk = 16, K a multiple of 16 and 16-byte aligned operands
+ * also direct-to-LDS where K is not split).  FSCC_EINVAL if the shape does not
  * fit the form.
  * bk = 16 or 32, allow_split = 1 permits split-K.  beta is 0 or 1.
  * Synchronises hip_stream. */

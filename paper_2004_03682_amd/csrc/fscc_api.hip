@@ -159,9 +159,9 @@ double cfg_cost(const Op& o, int cfg, bool split, int lds, bool real) {
 }
 
 // The forms of an operation by cfg_cost, cheapest first; split, direct: may
-// K be split, may slices go to LDS directly.  Not considered, since never the
+// K be split, where may slices go to LDS directly.  Not considered, since never the
 // fastest where the fit looked: 128x16 and 16x128 tiles and the skinny form.
-std::vector<GemmChoice> forms_by_cost(const Op& o, bool real, bool split, bool direct) {
+std::vector<GemmChoice> forms_by_cost(const Op& o, bool real, bool split, DirectUse direct) {
     if (o.probs.empty()) return {GemmChoice()};
     std::vector<std::pair<double, GemmChoice>> f;
     for (int cfg : {ZCFG_64x64, ZCFG_32x32, ZCFG_64x16, ZCFG_16x64, ZCFG_32x64, ZCFG_64x32, ZCFG_64x64R, ZCFG_64x32R,
@@ -172,8 +172,8 @@ std::vector<GemmChoice> forms_by_cost(const Op& o, bool real, bool split, bool d
         if (mfma && split)
             for (int c : splitk_chunks(o, cfg)) can_split = can_split || c > 1;
         for (int lds : {(int)LDS_DIRECT, (int)LDS_STAGED}) {
-            if (lds == LDS_DIRECT && !(mfma && direct)) continue;
-            for (int sp = 0; sp <= (can_split ? 1 : 0); ++sp)
+            if (lds == LDS_DIRECT && !(mfma && direct != DIRECT_NO)) continue;
+            for (int sp = 0; sp <= (can_split && !(lds == LDS_DIRECT && direct == DIRECT_UNSPLIT) ? 1 : 0); ++sp)
                 f.push_back({cfg_cost(o, cfg, sp != 0, lds, real),
                              GemmChoice{cfg, sp != 0 || (cfg == ZCFG_RED && split), lds}});
         }
@@ -184,7 +184,7 @@ std::vector<GemmChoice> forms_by_cost(const Op& o, bool real, bool split, bool d
     return out;
 }
 
-GemmChoice pick_form(const Op& o, bool real) { return forms_by_cost(o, real, true, true).front(); }
+GemmChoice pick_form(const Op& o, bool real) { return forms_by_cost(o, real, true, DIRECT_ANY).front(); }
 
 // Workgroups of one launch are handed to the 8 XCDs round-robin (block b runs on
 // XCD b % 8) and each XCD has its own L2.  Permute the logical tile sequence so
@@ -2196,7 +2196,7 @@ fscc_status fscc_zgemm(int cfg, int bk, int tA, int tB, int cA, int cB, int M, i
         if (cfg >= 0 && !cfg_ok(o, cfg)) return FSCC_EINVAL;
         GemmDev g;
         if (cfg < 0) {   // the best of the forms that this call runs
-            const GemmChoice f = forms_by_cost(o, false, allow_split != 0, direct_ok(bk, A, B)).front();
+            const GemmChoice f = forms_by_cost(o, false, allow_split != 0, direct_use(bk, K, A, B)).front();
             plan_gemm(c, o, g, f.cfg, bk, f.split, three_products(o));
             g.lds = f.lds;
         } else {
@@ -2248,7 +2248,8 @@ fscc_status fscc_dgemm(int cfg, int bk, int tA, int tB, int M, int N, int K, con
         if (cfg >= 0 && !cfg_ok(o, cfg, true)) return FSCC_EINVAL;
         GemmDev g;
         if (cfg < 0) {   // the best of the forms that this call runs
-            const GemmChoice f = forms_by_cost(o, true, allow_split != 0, bk == 16).front();
+            // (staged: direct-to-LDS took 170 us against 161 at 1024^3, 373 against 385 at 2048^3)
+            const GemmChoice f = forms_by_cost(o, true, allow_split != 0, DIRECT_NO).front();
             plan_gemm(c, o, g, f.cfg, bk, f.split);
             g.lds = f.lds;
         } else {

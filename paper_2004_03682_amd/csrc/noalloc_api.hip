@@ -89,7 +89,7 @@ fscc_status fscc_zgemm_noalloc(int cfg, int bk, int tA, int tB, int cA, int cB, 
             // the cheapest form that this call runs and whose tables and
             // partial sums fit; if none does, the forms that the estimate
             // leaves out (a 128 x 16 tile has the fewest tables for few columns)
-            std::vector<GemmChoice> forms = forms_by_cost(o, false, allow_split != 0, direct_ok(bk, A, B));
+            std::vector<GemmChoice> forms = forms_by_cost(o, false, allow_split != 0, direct_use(bk, K, A, B));
             for (int form : {ZCFG_128x16, ZCFG_16x128, ZCFG_SKINNY}) forms.push_back(GemmChoice{form, false, LDS_STAGED});
             bool fits = false;
             for (const GemmChoice& f : forms) {

@@ -849,12 +849,15 @@ struct GemmChoice {
     int lds = LDS_STAGED;
 };
 GemmChoice pick_form(const Op& o, bool real);
-// May the default form of a caller's complex operands use direct-to-LDS loads
-// (16-deep slices, 16 bytes per lane)?
-inline bool direct_ok(int bk, const void* A, const void* B) {
-    return bk == 16 && (((uintptr_t)A | (uintptr_t)B) & 15) == 0;
+// Where a default form may use direct-to-LDS loads.
+enum DirectUse { DIRECT_NO = 0, DIRECT_UNSPLIT, DIRECT_ANY };
+// For a single complex call: they move 16 bytes per lane, in 16-deep slices, and
+// past the end of K (or of a chunk of it) they multiply the last
+// element by zero, which is no zero if it is infinite.
+inline DirectUse direct_use(int bk, int K, const void* A, const void* B) {
+    return bk == 16 && K % 16 == 0 && (((uintptr_t)A | (uintptr_t)B) & 15) == 0 ? DIRECT_UNSPLIT : DIRECT_NO;
 }
-std::vector<GemmChoice> forms_by_cost(const Op& o, bool real, bool split, bool direct);
+std::vector<GemmChoice> forms_by_cost(const Op& o, bool real, bool split, DirectUse direct);
 bool three_products(const Op& o);
 std::vector<ZTile> xcd_order(const std::vector<ZTile>& logical);
 void free_gemm(GemmDev& g);

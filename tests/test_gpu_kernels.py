@@ -246,3 +246,22 @@ def test_default_forms_with_every_restriction(M, N, K, tA, tB, bk, shift):
         assert F.lib().fscc_dgemm(-1, bk, tA, tB, M, N, K, pa, lda, pb, ldb, pc, N, one, 1, split, st) == 0
         got = dc.cpu().numpy()[shift:shift + M * N].reshape(M, N)
         assert (np.abs(got - (a.real @ b.real + c0.real)) <= bound).all()
+
+
+@pytest.mark.parametrize("M,N,K", [(64, 64, 48), (64, 64, 47), (40, 40, 1031), (300, 300, 300), (12, 20, 4000), (3000, 7, 41)])
+def test_default_forms_keep_infinities(M, N, K):
+    """An infinity in the last k of a real product (and of a thin complex one, real operands): every default form gives
+    +-infinity where numpy does and finite values elsewhere."""
+    import torch
+    import paper_2004_03682_amd as F
+    rng = np.random.default_rng(K)
+    A, B = rng.normal(size=(M, K)), rng.normal(size=(K, N))
+    A[1, K - 1] = np.inf
+    B[K - 1, 2] = -np.inf
+    A[1, :K - 1] = np.abs(A[1, :K - 1])
+    ref = A @ B
+    same = lambda x, y: np.array_equal(np.isnan(x), np.isnan(y)) and np.array_equal(x[np.isinf(y)], y[np.isinf(y)])  # noqa: E731
+    for split in (True, False):
+        dC = torch.zeros(M, N, dtype=torch.float64, device="cuda")
+        F.dgemm(torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda(), dC, M, N, K, K, N, N, allow_split=split)
+        assert same(dC.cpu().numpy(), ref), split
